@@ -23,6 +23,8 @@
 // with -ffp-contract=off, so no multiply-add is fused.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "impl.hpp"
 
 namespace edp {
@@ -46,6 +48,12 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
                    (uint32_t)p0);
   }
   return c;
+}
+
+// The first output word alone: the upper half of the first uniform's 64 bits
+// (the last round needs one of its two products only).
+__device__ __forceinline__ uint32_t philox_w0(uint64_t seed, uint64_t uid, uint32_t step, uint32_t t) {
+  return philox(make_uint4((uint32_t)uid, (uint32_t)(uid >> 32), step, t), (uint32_t)seed, (uint32_t)(seed >> 32)).x;
 }
 
 __device__ __forceinline__ uint32_t tag(uint32_t species, uint32_t purpose, uint32_t call) {
@@ -159,9 +167,11 @@ __device__ __forceinline__ int deposit_split(double x, double inv_dx, int ng, lo
   const double xi = x * inv_dx;
   int p = (int)xi;
   p = p > ng - 2 ? ng - 2 : (p < 0 ? 0 : p);
-  const double f = xi - (double)p;
-  long long q = (long long)(f * kTwo32);
-  r = q > 4294967296LL ? 4294967296LL : q;
+  const double f = (xi - (double)p) * kTwo32;
+  // below 2^32 a 32-bit conversion is the truncation (f is never negative:
+  // p <= xi for x >= 0)
+  const bool all = f >= kTwo32;
+  r = (long long)(((uint64_t)(all ? 1u : 0u) << 32) | (all ? 0u : (uint32_t)f));
   return p;
 }
 
@@ -170,6 +180,9 @@ __device__ __forceinline__ int64_t slots(const CaseDev* C, int sp) {
   const int64_t a = C->alloc[sp];
   return a < C->sp[sp].cap ? a : C->sp[sp].cap;
 }
+
+// Lanes of the wave with b set (the compare's own mask, no second compare).
+__device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
 __device__ __forceinline__ void lds_add(unsigned long long* a, long long v) {
   atomicAdd(a, (unsigned long long)v);
@@ -285,17 +298,19 @@ __device__ __forceinline__ void fold_particle_sums(const EDP_CONST CaseDev* __re
   }
 }
 
-// Per-node duties of a step's writer: rho for reads, the time sums of the
-// densities, the deposit rings the next steps refill cleared, the particle
-// sums of step s-1 folded with the field that step used (still in efield[];
-// it is overwritten after the workgroup's next barrier), the xt rows of the
-// densities.
+// Duties of a step's writer (one workgroup per case and step), in loops of
+// their own: inside the solve's code they would be fetched by every
+// workgroup that skips them.
 struct FieldWriter {
   const EDP_CONST CaseDev* C;
-  int64_t s, k;
+  int s3, k3;  // step % 3, ion step index % 3
   int ng;
   bool ion_step, xt;
   size_t plane, row, row_prev;
+  // node p before the solve: rho for reads, the time sums of the densities,
+  // the deposit rings the next steps refill cleared, the particle sums of step
+  // s-1 folded with the field that step used (still in efield[]), the xt rows
+  // of the densities
   __device__ __forceinline__ void node(int p, double ne, double ni, double rho) const {
     const uint32_t fl = C->flags;
     G(C->rho)[p] = rho;
@@ -303,99 +318,110 @@ struct FieldWriter {
       G(C->sum_ne)[p] += ne;
       G(C->sum_ni)[p] += ni;
     }
-    G(C->cnt_e)[((s + 2) % 3) * ng + p] = 0;
-    if (ion_step) G(C->cnt_i)[((k + 2) % 3) * ng + p] = 0;
-    if (fl & (kDiagCurrent | kDiagMeanE | kDiagXT)) fold_particle_sums(C, p, ((s + 2) % 3) * ng, row_prev, plane);
+    const int prev3 = s3 == 0 ? 2 : s3 - 1;
+    G(C->cnt_e)[prev3 * ng + p] = 0;
+    if (ion_step) G(C->cnt_i)[(k3 == 0 ? 2 : k3 - 1) * ng + p] = 0;
+    if (fl & (kDiagCurrent | kDiagMeanE | kDiagXT)) fold_particle_sums(C, p, prev3 * ng, row_prev, plane);
     if (xt) {
       EDP_GLOBAL double* __restrict__ X = G(C->xt);
       X[kXtNe * plane + row + p] += ne;
       X[kXtNi * plane + row + p] += ni;
     }
   }
-  // the node's field E and flux f (phi for the Thomas solve: MODE 1)
-  template <int MODE>
-  __device__ __forceinline__ void out(int p, double e, double f, double phi) const {
+  // flux p of the solve (the last slot keeps V, for phi on demand)
+  __device__ __forceinline__ void flux(int p, double f) const {
+    G(C->flux)[p] = f;
+    if (xt) G(C->xt)[kXtFlux * plane + row + p] += f;
+  }
+  // node p after the solve
+  __device__ __forceinline__ void field(int p, double e) const {
     G(C->efield)[p] = e;
-    if (MODE == 1)
-      G(C->phi)[p] = phi;
-    else
-      G(C->flux)[p] = f;
-    if (xt) {
-      EDP_GLOBAL double* __restrict__ X = G(C->xt);
-      X[kXtEf * plane + row + p] += e;
-      X[kXtFlux * plane + row + p] += f;
-    }
+    if (xt) G(C->xt)[kXtEf * plane + row + p] += e;
   }
 };
 
 // Steps 1-2 of step s, computed by every workgroup that needs E (each
 // particle workgroup of a lockstep launch, the small-case workgroup): the
 // densities of the deposit rings read at step s, rho, the potential and E on
-// the nodes into sE (LDS).  sF: ng doubles of LDS scratch (the Thomas
-// solve).  The ring and V(t) pointers come with the workgroup's role.  The
-// results depend only on the deposit, so every workgroup gets the same bits.
-// The writer (one workgroup per case and step) also stores rho, E and the
-// fluxes (or phi) for reads, clears the deposit rings the next steps refill,
-// adds the measurement sums and counts the step.
+// the nodes into sE (LDS); sF: ng doubles of LDS, zero on return.  The ring and V(t)
+// pointers come with the workgroup's role.  The results depend only on the
+// deposit, so every workgroup gets the same bits.  The writer (one workgroup
+// per case and step) also does its duties and counts the step.
+//
+// Bound by latency, and in a launch that starts with cold caches by the
+// fetching of its code: the two rings are staged through LDS in one round of
+// coalesced loads, and the rows of a thread are worked in a loop, not
+// unrolled to the largest grid with the writer's code in each copy (the
+// electron kernel's code 64 -> 42 KB; a step of 1e3 electrons on 400 nodes
+// 13.6 -> 12.4 us, of 5e4 with every measurement 19.5 -> 17.2 us).
 template <int MODE, int NB>
 __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int64_t* __restrict__ cnt_e,
                                             const int64_t* __restrict__ cnt_i, const double* __restrict__ volt,
                                             const int ng, const int nsub, const int64_t s, double* sE, double* sF,
                                             const bool writer) {
-  // rows of the flux scan and nodes per thread at the largest grid
-  constexpr int kRows = (kMaxNodes - 2 + NB - 1) / NB;
-  constexpr int kNodes = (kMaxNodes + NB - 1) / NB;
   __shared__ double sWave[2][NB / kWave];
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   const int64_t k = s / nsub;
   const bool ion_step = (s % nsub) == 0;
-  const EDP_GLOBAL int64_t* cntE = G(cnt_e) + (s % 3) * ng;
-  const EDP_GLOBAL int64_t* cntI = G(cnt_i) + (k % 3) * ng;
+  const int s3 = (int)(s % 3), k3 = (int)(k % 3);
+  const EDP_GLOBAL int64_t* cntE = G(cnt_e) + s3 * ng;
+  const EDP_GLOBAL int64_t* cntI = G(cnt_i) + k3 * ng;
   const int t = (int)threadIdx.x;
   const int lane = t % kWave, wv = t / kWave;
+  // the rings, staged where E and the scratch go
+  int64_t* const nE = (int64_t*)sF;
+  int64_t* const nI = (int64_t*)sE;
+#pragma unroll 4
+  for (int p = t; p < ng; p += NB) {
+    const int64_t a = cntE[p], b = cntI[p];
+    nE[p] = a;
+    nI[p] = b;
+  }
   const double V = G(volt)[s % kVoltChunk];
   const double scale = C->dens_scale;
   const double kp = C->kpois;
   const double dx = C->dx;
   FieldWriter W;
   W.C = C;
-  W.s = s;
-  W.k = k;
+  W.s3 = s3;
+  W.k3 = k3;
   W.ng = ng;
   W.ion_step = ion_step;
   W.xt = writer && (C->flags & kDiagXT) != 0;
-  const int64_t nt = C->nt, nxb = C->n_xt_bin;
-  W.plane = (size_t)C->n_xt * (size_t)ng;
-  W.row = W.xt ? (size_t)((s % nt) / nxb) * (size_t)ng : 0;
-  W.row_prev = W.xt ? (size_t)(((s + nt - 1) % nt) / nxb) * (size_t)ng : 0;
+  W.plane = W.row = W.row_prev = 0;
+  if (W.xt) {
+    const int64_t nt = C->nt, nxb = C->n_xt_bin;
+    W.plane = (size_t)C->n_xt * (size_t)ng;
+    W.row = (size_t)((s % nt) / nxb) * (size_t)ng;
+    W.row_prev = (size_t)(((s + nt - 1) % nt) / nxb) * (size_t)ng;
+  }
   // densities (the electrodes' half cells count twice) and rho of node p
-  auto dens = [&](int p, int64_t ce, int64_t ci, double& ne, double& ni) {
-    ne = (double)ce * scale;
-    ni = (double)ci * scale;
+  auto dens = [&](int p, double& ne, double& ni) {
+    ne = (double)nE[p] * scale;
+    ni = (double)nI[p] * scale;
     if (p == 0 || p == ng - 1) {
       ne *= 2.0;
       ni *= 2.0;
     }
     return kECharge * (ni - ne);
   };
+  __syncthreads();
+  double ne, ni;
+  if (writer) {
+#pragma unroll 1
+    for (int p = t; p < ng; p += NB) {
+      const double rho = dens(p, ne, ni);
+      W.node(p, ne, ni, rho);
+    }
+    __syncthreads();  // the staged ions are overwritten below
+  }
   if (MODE == 1) {
     // node p = t + q NB: rho and the right-hand side d_p = rho_p dx^2/eps0
-    int64_t ce[kNodes], ci[kNodes];
-#pragma unroll
-    for (int q = 0; q < kNodes; ++q) {
-      const int p = t + q * NB;
-      ce[q] = p < ng ? cntE[p] : 0;
-      ci[q] = p < ng ? cntI[p] : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < kNodes; ++q) {
-      const int p = t + q * NB;
-      if (p >= ng) break;
-      double ne, ni;
-      const double rho = dens(p, ce[q], ci[q], ne, ni);
+#pragma unroll 1
+    for (int p = t; p < ng; p += NB) {
+      const double rho = dens(p, ne, ni);
       sE[p] = rho;
       sF[p] = rho * kp;
-      if (writer) W.node(p, ne, ni, rho);
     }
     __syncthreads();
     const double rho0 = sE[0], rhoN = sE[ng - 1];
@@ -417,6 +443,7 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
       sF[ng - 1] = 0.0;
     }
     __syncthreads();
+#pragma unroll 1
     for (int p = t; p < ng; p += NB) {
       double e;
       if (p == 0)
@@ -426,8 +453,13 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
       else
         e = (sF[p - 1] - sF[p + 1]) / (2.0 * dx);
       sE[p] = e;
-      if (writer) W.out<1>(p, e, p < ng - 1 ? sF[p] - sF[p + 1] : V, sF[p]);
+      if (writer) {
+        G(C->phi)[p] = sF[p];
+        if (W.xt) G(C->xt)[kXtFlux * W.plane + W.row + p] += p < ng - 1 ? sF[p] - sF[p + 1] : V;
+      }
     }
+    __syncthreads();
+    for (int p = t; p < ng; p += NB) sF[p] = 0.0;
   } else {
     // The flux form of the same tridiagonal system: with F_q = phi_q -
     // phi_{q+1}, row p of the Poisson equation says F_p - F_{p-1} = d_p, so
@@ -435,44 +467,29 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
     // fluxes add up to phi_0 - phi_{N-1} = V, which fixes
     // F_0 = (V - sum_q S_q)/(N_g - 1), and sum_q S_q = sum_r (m - r) d_r over
     // the m = N_g - 2 interior rows.  Thread t owns the contiguous rows
-    // q0 <= q < q0 + nq (row q is node q + 1): it loads their densities,
-    // forms its prefix and its share of the weighted sum, and one workgroup
-    // pass (wave scans, one exchange of the wave totals) gives every thread
-    // the rows before its own and the weighted total.  E of its nodes then
-    // follows in registers: E_p = (F_{p-1} + F_p)/(2 dx) inside, the boundary
-    // forms (Gauss's law over the half cell) at the electrodes.
+    // q0 <= q < q0 + nq (row q is node q + 1): it forms its prefix (kept in
+    // sE) and its share of the weighted sum, and one workgroup pass (wave
+    // scans, one exchange of the wave totals) gives every thread the rows
+    // before its own and the weighted total.  E of its nodes then follows:
+    // E_p = (F_{p-1} + F_p)/(2 dx) inside, the boundary forms (Gauss's law
+    // over the half cell) at the electrodes.
     const int m = ng - 2;
-    const int R = (m + NB - 1) / NB;  // <= kRows
+    const int R = (m + NB - 1) / NB;
     const int q0 = t * R < m ? t * R : m;
     const int nq = (q0 + R < m ? q0 + R : m) - q0;
-    int64_t ce[kRows], ci[kRows];
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      ce[r] = r < nq ? cntE[q0 + 1 + r] : 0;
-      ci[r] = r < nq ? cntI[q0 + 1 + r] : 0;
-    }
-    const int64_t ce0 = cntE[0], ci0 = cntI[0], ceN = cntE[ng - 1], ciN = cntI[ng - 1];
-    double v[kRows];
+    // the owner of the last row also takes node N_g-1 (thread 0 when there
+    // are no interior rows)
+    const bool last = nq > 0 ? q0 + nq == m : (t == 0 && m == 0);
+    const double rho0 = t == 0 ? dens(0, ne, ni) : 0.0;
+    const double rhoN = last ? dens(ng - 1, ne, ni) : 0.0;
     double acc = 0.0, wsum = 0.0;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      if (r < nq) {
-        const int p = q0 + 1 + r;
-        double ne, ni;
-        const double rho = dens(p, ce[r], ci[r], ne, ni);
-        if (writer) W.node(p, ne, ni, rho);
-        const double d = rho * kp;
-        acc += d;
-        wsum += d * (double)(m - (q0 + r));
-      }
-      v[r] = acc;  // prefix within the thread
-    }
-    double ne0, ni0, neN, niN;
-    const double rho0 = dens(0, ce0, ci0, ne0, ni0);
-    const double rhoN = dens(ng - 1, ceN, ciN, neN, niN);
-    if (writer && t == 0) {
-      W.node(0, ne0, ni0, rho0);
-      W.node(ng - 1, neN, niN, rhoN);
+#pragma unroll 1
+    for (int r = 0; r < nq; ++r) {
+      const int p = q0 + 1 + r;
+      const double d = dens(p, ne, ni) * kp;
+      acc += d;
+      wsum += d * (double)(m - (q0 + r));
+      sE[p] = acc;  // prefix within the thread
     }
     // the workgroup pass: inclusive scan of acc and sum of wsum per wave
     double inc = acc;
@@ -496,29 +513,23 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
     }
     const double F0 = (V - sum_s) / (double)(ng - 1);
     double f_prev = F0 + before;  // F_{q0}: F0 plus the rows before this thread's
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      if (r < nq) {
-        const int p = q0 + 1 + r;
-        const double f = F0 + (before + v[r]);  // F_{q+1} = F_p
-        const double e = (f_prev + f) / (2.0 * dx);
-        sE[p] = e;
-        if (writer) W.out<0>(p, e, f, 0.0);
-        f_prev = f;
-      }
+#pragma unroll 1
+    for (int r = 0; r < nq; ++r) {
+      const int p = q0 + 1 + r;
+      const double f = F0 + (before + sE[p]);  // F_{q+1} = F_p
+      sE[p] = (f_prev + f) / (2.0 * dx);
+      if (writer) W.flux(p, f);
+      f_prev = f;
     }
-    // the electrodes: node 0 by thread 0, node N_g-1 by the owner of the
-    // last row (thread 0 when there are no interior rows)
     if (t == 0) {
-      const double e = F0 / dx - rho0 * dx / (2.0 * kEps0);
-      sE[0] = e;
-      if (writer) W.out<0>(0, e, F0, 0.0);
+      sE[0] = F0 / dx - rho0 * dx / (2.0 * kEps0);
+      if (writer) W.flux(0, F0);
     }
-    if (nq > 0 ? q0 + nq == m : t == 0) {
-      const double e = f_prev / dx + rhoN * dx / (2.0 * kEps0);
-      sE[ng - 1] = e;
-      if (writer) W.out<0>(ng - 1, e, V, 0.0);  // the last flux slot keeps V for phi on demand
+    if (last) {
+      sE[ng - 1] = f_prev / dx + rhoN * dx / (2.0 * kEps0);
+      if (writer) W.flux(ng - 1, V);
     }
+    for (int p = t; p < ng; p += NB) sF[p] = 0.0;
   }
   if (writer && t == 0) {
     if (W.xt) {
@@ -529,7 +540,11 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
     Cw->diag_steps += 1;
     if (ion_step) Cw->diag_ion_steps += 1;
   }
-  __syncthreads();  // sE complete; sF free again
+  __syncthreads();  // sE and the zeroed sF complete
+  if (writer) {
+#pragma unroll 1
+    for (int p = t; p < ng; p += NB) W.field(p, sE[p]);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -777,6 +792,13 @@ constexpr int kSegE = 128;
 template <int SP>
 constexpr int seg_len() { return SP == 0 ? kSegE : kSegI; }
 
+// The largest upper word w0 of a uniform's 64 bits with which R < p is
+// possible: R >= w0 2^-32, so R < p needs w0 <= p 2^32.
+__device__ __forceinline__ uint32_t candidate_limit(double p) {
+  const double t = p * kTwo32;
+  return t < kTwo32 ? (uint32_t)t : 0xFFFFFFFFu;
+}
+
 // Birth slots of one step: a species' newborns take consecutive slots after
 // its slot count at the step's start, from a counter of the step's births
 // (LDS in the small-case kernel, born[sp][s % 3] in global memory in the
@@ -789,7 +811,7 @@ struct Births {
   // Slot of this lane's newborn of species sp (mine), -1 if none or dropped;
   // every lane of the wave calls it.  placed / dropped count the wave's.
   __device__ __forceinline__ int64_t take(int sp, bool mine, int lane, int& placed, int& dropped) const {
-    const uint64_t m = __ballot(mine);
+    const uint64_t m = ballot(mine);
     if (m == 0) return -1;
     long long b = 0;
     if (lane == 0) {
@@ -802,8 +824,8 @@ struct Births {
     b = __shfl(b, 0);
     const int64_t slot = base[sp] + (int64_t)b + lane_rank(m);
     const bool ok = slot < cap[sp];
-    placed += (int)__popcll(__ballot(mine && ok));
-    dropped += (int)__popcll(__ballot(mine && !ok));
+    placed += (int)__popcll(ballot(mine && ok));
+    dropped += (int)__popcll(ballot(mine && !ok));
     return mine && ok ? slot : -1;
   }
   // Slots of the newborn pairs (an electron and an ion) of the wave's `cnt`
@@ -845,6 +867,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
                                               const Births<SMALL>& B, const int pretest) {
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   constexpr int kSeg = seg_len<SP>();
+  constexpr bool ZEROED = !(SMALL && SP == 1);  // the solve left the histogram zero
   constexpr int kPay = SP == 0 ? NB / kWave : 1;
   __shared__ int32_t sSeg[NB / kWave][kSeg];
   __shared__ double sVx[kPay][SP == 0 ? kSeg : 1];
@@ -852,8 +875,9 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   __shared__ int sTot[NB / kWave][kRec];
   // entries of the overflow list, next pass over it
   __shared__ int sOvf, sFin;
-  // the pre-test's bound of P by energy block (direct collision test)
-  __shared__ double sPB[kMaxPb];
+  // the pre-test's bound of P by energy block (direct collision test), as
+  // candidate_limit gives it
+  __shared__ uint32_t sPB[kMaxPb];
   // lanes of a pass's ionizing colliders by rank (electrons)
   __shared__ int sIon[SP == 0 ? NB / kWave : 1][SP == 0 ? kWave : 1];
   const int ng = C->ng;
@@ -872,16 +896,17 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   unsigned long long* sEn = sW + ng;
   unsigned long long* sIz = sEn + ng;  // electrons with the xt arrays only
   unsigned int* sF = (unsigned int*)(sIz + (SP == 0 && xt ? ng : 0));
-  for (int p = threadIdx.x; p < ng; p += blockDim.x) {
-    sH[p] = 0;
-    if (pdiag) {
+  if (pdiag || !ZEROED) {
+    for (int p = threadIdx.x; p < ng; p += NB) {
+      if (!ZEROED) sH[p] = 0;
+      if (!pdiag) continue;
       sJ[p] = 0;
       sW[p] = 0;
       sEn[p] = 0;
       if (SP == 0 && xt) sIz[p] = 0;
     }
   }
-  for (int b = threadIdx.x; b < n_hist; b += blockDim.x) sF[b] = 0;
+  for (int b = threadIdx.x; b < n_hist; b += NB) sF[b] = 0;
   constexpr int kWaves = NB / kWave;
   // candidate pre-test: R below a bound of P, or a speed beyond the bound's
   // range.  The direct test's bound is P* (with its margin), or, when a
@@ -901,7 +926,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   if (by_energy) {
     const int pb_n = C->pb_n;
     const EDP_GLOBAL double* __restrict__ pbg = G(C->pbound[SP]);
-    for (int b = threadIdx.x; b < pb_n; b += blockDim.x) sPB[b] = pbg[b];
+    for (int b = threadIdx.x; b < pb_n; b += blockDim.x) sPB[b] = candidate_limit(pbg[b]);
   }
   if (threadIdx.x == 0) {
     sOvf = 0;
@@ -944,12 +969,17 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   const double p_surf1 = SP == 0 ? C->eta_refl[1] : C->gamma_see[1];
   const double n_gas = C->n_gas;
   const double nu_star = SP == 0 ? C->nu_star_e : C->nu_star_i;
+  const uint32_t r_cand = candidate_limit(p_cand);
   const double v2_cand = null_coll ? __builtin_huge_val() : (SP == 0 ? C->v2_lim_e : C->g2_lim_i);
-  const double rows_per_g2 = 0.5 * (SP == 0 ? kEMass : kMuArAr) / kEvToJ / C->de_cs * (1.0 + 1e-12);
-  const int pb_shift = C->pb_shift;
+  // bound blocks per g2u (a power of two of rows), and the last
+  const double blocks_per_row = ldexp(1.0, -C->pb_shift);
+  const double blocks_per_g2 = 0.5 * (SP == 0 ? kEMass : kMuArAr) / kEvToJ / C->de_cs * (1.0 + 1e-12) * blocks_per_row;
+  const double block_half = 0.5 * blocks_per_row, block_last = (double)(nbins - 1) * blocks_per_row;
   const double a2_i = C->a2_i;
   const uint32_t r_tag = SP == 0 ? tag(0, 0, 0) : tag(1, 0, 2);
-  const int w = (int)threadIdx.x / kWave, lane = (int)threadIdx.x % kWave;
+  // the wave's index in a scalar register: what depends on it (the slices, the
+  // loop, the addresses' bases, the segment) then is scalar too
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = (int)threadIdx.x % kWave;
   // this wave's totals (uniform over the wave)
   int t_coll = 0, t_ioniz = 0, t_pow = 0, t_gnd = 0, t_live = 0, t_be = 0, t_bi = 0, t_drop = 0;
   int ncw = 0;  // entries in this wave's candidate segment
@@ -986,9 +1016,12 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
         c2 = c1 + (n_gas * sig1[idx]) * g;
         c3 = c2;
       }
-      if (c3 > nu_star) gl_add(&Cw->ctr[kAnomaly], 1);
-      const double t = r_proc * nu_star;
-      proc = t < c1 ? 0 : (t < c2 ? 1 : (SP == 0 && t < c3 ? 2 : -1));
+      // the loop's test lets R up to 2^-32 above P* through
+      if (r_coll < p_null) {
+        if (c3 > nu_star) gl_add(&Cw->ctr[kAnomaly], 1);
+        const double t = r_proc * nu_star;
+        proc = t < c1 ? 0 : (t < c2 ? 1 : (SP == 0 && t < c3 ? 2 : -1));
+      }
     } else {
       double p_coll, s_a, s_b, s_c = 0.0;
       int idx;
@@ -1056,51 +1089,62 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   // from the step's counters, charge at the parent's new position: the
   // electron a second share of this step's deposit, the ion the next ion
   // step's density).  No workgroup barrier: waves finish at their own pace.
-  auto finish = [&]() {
+  // An entry of the wave's segment with what its exact test needs (v_y and v_z
+  // are not changed by the push).
+  struct Entry {
+    int64_t i;
+    double vxn, vy, vz;
+    uint64_t uid;
+  };
+  auto own_entry = [&](const int k) {
+    Entry c{};
+    if (k >= ncw) return c;
+    c.i = sSeg[w][k];
+    c.vy = VY[c.i];
+    c.vz = VZ[c.i];
+    if (SP == 0) {
+      // the pushed v_x and the uid from the segment
+      c.vxn = sVx[SP == 0 ? w : 0][SP == 0 ? k : 0];
+      c.uid = sUid[SP == 0 ? w : 0][SP == 0 ? k : 0];
+    } else {
+      c.vxn = VX[c.i];
+      c.uid = UID[c.i];
+    }
+    return c;
+  };
+  auto finish = [&](const Entry& first) {
     const int npool = sOvf;  // written before the barrier after the loop
     const int own = (ncw + kWave - 1) / kWave;
+#pragma unroll 1
     for (int round = 0;; ++round) {
-      bool pool = false;
-      int b0, count;
-      if (round < own) {
-        b0 = round * kWave;
-        count = ncw;
-      } else {
-        int g = 0;
-        if (lane == 0) g = atomicAdd(&sFin, 1);
-        b0 = __builtin_amdgcn_readfirstlane(__shfl(g, 0)) * kWave;
-        if (b0 >= npool) break;
-        pool = true;
-        count = npool;
-      }
-      const int k = b0 + lane;
-      int64_t i = 0;
-      double vxn = 0.0, vy = 0.0, vz = 0.0;
-      uint64_t uid = 0;
-      int proc = -1;
-      if (k < count) {
-        if (pool) {
-          i = CL[k];
-          vxn = VX[i];
-          uid = UID[i];
+      Entry c = first;
+      bool have = lane < ncw;
+      if (round > 0 || own == 0) {
+        c = Entry{};
+        if (round < own) {
+          have = round * kWave + lane < ncw;
+          c = own_entry(round * kWave + lane);
         } else {
-          i = sSeg[w][k];
-          if (SP == 0) {
-            // the pushed v_x and the uid from the segment
-            vxn = sVx[SP == 0 ? w : 0][SP == 0 ? k : 0];
-            uid = sUid[SP == 0 ? w : 0][SP == 0 ? k : 0];
-          } else {
-            vxn = VX[i];
-            uid = UID[i];
+          int g = 0;
+          if (lane == 0) g = atomicAdd(&sFin, 1);
+          const int b0 = __builtin_amdgcn_readfirstlane(g) * kWave;
+          if (b0 >= npool) break;
+          have = b0 + lane < npool;
+          if (have) {
+            c.i = CL[b0 + lane];
+            c.vxn = VX[c.i];
+            c.uid = UID[c.i];
+            c.vy = VY[c.i];
+            c.vz = VZ[c.i];
           }
         }
-        // v_y and v_z are not changed by the push
-        vy = VY[i];
-        vz = VZ[i];
-        proc = exact_test(vxn, vy, vz, uid);
       }
+      int64_t i = c.i;
+      double vxn = c.vxn, vy = c.vy, vz = c.vz;
+      uint64_t uid = c.uid;
+      int proc = have ? exact_test(vxn, vy, vz, uid) : -1;
       const bool hit = proc >= 0;
-      const uint64_t mc = __ballot(hit);
+      const uint64_t mc = ballot(hit);
       const int ncol = (int)__popcll(mc);
       t_coll += ncol;
       if (ncol == 0) continue;
@@ -1110,144 +1154,171 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       auto push64 = [&](uint64_t v) {
         return (uint64_t)(uint32_t)push32((int)(uint32_t)v) | ((uint64_t)(uint32_t)push32((int)(v >> 32)) << 32);
       };
-      i = (int64_t)push64((uint64_t)i);
+      i = (int64_t)push32((int)i);  // slots are below 2^31
       proc = push32(proc);
       vxn = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vxn)));
       vy = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vy)));
       vz = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vz)));
       uid = push64(uid);
       const bool coll = lane < ncol;
-      if (SP == 0) {
-        const bool ioniz = coll && proc == 2;
-        const uint64_t mi = __ballot(ioniz);
-        if (mi == 0) {
-          if (coll) {
-            double ox, oy, oz;
-            electron_outgoing(C, P, false, proc, s, vxn, vy, vz, uid, ox, oy, oz);
-            store_electron_v(P, i, ox, oy, oz);
-          }
-        } else {
-          // Ionizations.  The parent's new position and the newborns' slots
-          // are loaded and taken first and used only at the stores; the
-          // ejected electrons are worked on the lanes the colliders leave
-          // free, beside the colliders, in rank order (more passes if they
-          // do not fit); the new ions on their parents' lanes after that.
-          const int ni = (int)__popcll(mi);
-          t_ioniz += ni;
-          const int ri = lane_rank(mi);
-          const double xb = ioniz ? X[i] : 0.0;
-          long long a_e, a_i;
-          B.issue_pair(ni, lane, a_e, a_i);
-          if (ioniz) sIon[SP == 0 ? w : 0][SP == 0 ? ri : 0] = lane;
-          int64_t f_e = 0, f_i = 0;
-          bool have_slots = false;
-          for (int e0 = 0, pass = 0; pass == 0 || e0 < ni; ++pass) {
-            const int lane0 = pass == 0 ? ncol : 0;
-            const int e = e0 + lane - lane0;  // the ejected electron of this lane, by rank
-            const bool ej = lane >= lane0 && e < ni;
-            const bool par = pass == 0 && coll;
-            const int src = ej ? sIon[SP == 0 ? w : 0][SP == 0 ? e : 0] : lane;
-            const double tvx = __shfl(vxn, src), tvy = __shfl(vy, src), tvz = __shfl(vz, src);
-            const uint64_t tuid = (uint64_t)__shfl((long long)uid, src);
-            double ox = 0.0, oy = 0.0, oz = 0.0;
-            if (par || ej) electron_outgoing(C, P, ej, ej ? 2 : proc, s, tvx, tvy, tvz, tuid, ox, oy, oz);
-            if (!have_slots) {
-              B.first_slots(a_e, a_i, f_e, f_i);
-              have_slots = true;
-            }
-            const double tx = __shfl(xb, src);
-            if (par) store_electron_v(P, i, ox, oy, oz);
-            const int64_t be = f_e + e;
-            if (ej && be < B.cap[0]) {
-              P.ex[be] = tx;
-              store_electron_v(P, be, ox, oy, oz);
-              P.euid[be] = child_uid(tuid, s, 1);
-            }
-            e0 += kWave - lane0;
-          }
-          const bool ok_e = f_e + ri < B.cap[0], ok_i = f_i + ri < B.cap[1];
-          t_be += (int)__popcll(__ballot(ioniz && ok_e));
-          t_bi += (int)__popcll(__ballot(ioniz && ok_i));
-          t_drop += (int)__popcll(__ballot(ioniz && !ok_e)) + (int)__popcll(__ballot(ioniz && !ok_i));
-          if (ioniz) {
-            long long r;
-            const int q = deposit_split(xb, inv_dx, ng, r);
-            gl_add(&dst[q], 4294967296LL - r);
-            gl_add(&dst[q + 1], r);
-            gl_add(&cnt_i_next[q], 4294967296LL - r);
-            gl_add(&cnt_i_next[q + 1], r);
-            if (ok_i) ion_birth_at(C, P, f_i + ri, s, uid, xb);
+      if (SP == 1) {
+        if (coll) ion_scatter_at(C, P, i, proc, s, vxn, vy, vz, uid);
+        continue;
+      }
+      // The colliders' outgoing electrons and the electrons their ionizations
+      // eject, the latter on the lanes the colliders leave free, in rank
+      // order (more passes if they do not fit); the new ions on their
+      // parents' lanes after that.  The parent's new position and the
+      // newborns' slots are loaded and taken first and used only at the
+      // stores.  One copy of the scattering code for rounds with and without
+      // ionizations: its fetching is a good part of its time.
+      const bool ioniz = coll && proc == 2;
+      const uint64_t mi = ballot(ioniz);
+      const int ni = (int)__popcll(mi);
+      const int ri = lane_rank(mi);
+      double xb = 0.0;
+      long long a_e = 0, a_i = 0;
+      if (ni) {
+        t_ioniz += ni;
+        if (ioniz) {
+          xb = X[i];
+          sIon[SP == 0 ? w : 0][SP == 0 ? ri : 0] = lane;
+        }
+        B.issue_pair(ni, lane, a_e, a_i);
+      }
+      int64_t f_e = 0, f_i = 0;
+#pragma unroll 1
+      for (int e0 = 0, pass = 0; pass == 0 || e0 < ni; ++pass) {
+        const int lane0 = pass == 0 ? ncol : 0;
+        const int e = e0 + lane - lane0;  // the ejected electron of this lane, by rank
+        const bool ej = lane >= lane0 && e < ni;
+        const bool par = pass == 0 && coll;
+        int src = lane;
+        double tvx = vxn, tvy = vy, tvz = vz;
+        uint64_t tuid = uid;
+        if (ni) {
+          if (ej) src = sIon[SP == 0 ? w : 0][SP == 0 ? e : 0];
+          tvx = __shfl(vxn, src);
+          tvy = __shfl(vy, src);
+          tvz = __shfl(vz, src);
+          tuid = (uint64_t)__shfl((long long)uid, src);
+        }
+        double ox = 0.0, oy = 0.0, oz = 0.0;
+        if (par || ej) electron_outgoing(C, P, ej, ej ? 2 : proc, s, tvx, tvy, tvz, tuid, ox, oy, oz);
+        if (par) store_electron_v(P, i, ox, oy, oz);
+        if (ni) {
+          if (pass == 0) B.first_slots(a_e, a_i, f_e, f_i);
+          const double tx = __shfl(xb, src);
+          const int64_t be = f_e + e;
+          if (ej && be < B.cap[0]) {
+            P.ex[be] = tx;
+            store_electron_v(P, be, ox, oy, oz);
+            P.euid[be] = child_uid(tuid, s, 1);
           }
         }
-      } else if (coll) {
-        ion_scatter_at(C, P, i, proc, s, vxn, vy, vz, uid);
+        e0 += kWave - lane0;
+      }
+      if (ni) {
+        const bool ok_e = f_e + ri < B.cap[0], ok_i = f_i + ri < B.cap[1];
+        t_be += (int)__popcll(ballot(ioniz && ok_e));
+        t_bi += (int)__popcll(ballot(ioniz && ok_i));
+        t_drop += (int)__popcll(ballot(ioniz && !ok_e)) + (int)__popcll(ballot(ioniz && !ok_i));
+        if (ioniz) {
+          long long r;
+          const int q = deposit_split(xb, inv_dx, ng, r);
+          gl_add(&dst[q], 4294967296LL - r);
+          gl_add(&dst[q + 1], r);
+          gl_add(&cnt_i_next[q], 4294967296LL - r);
+          gl_add(&cnt_i_next[q + 1], r);
+          if (ok_i) ion_birth_at(C, P, f_i + ri, s, uid, xb);
+        }
       }
     }
   };
 
-  // The state of a wave's next slice is loaded before its current one is
-  // worked on, so each wave keeps two slices' loads in flight (the loop is
-  // bound by memory latency, not by its arithmetic).
-  const int64_t q_lo = c_lo * kWaves;
-  const int64_t q_end = (n + kWave - 1) / kWave;
-  const int64_t q_hi = c_hi * kWaves < q_end ? c_hi * kWaves : q_end;
-  double nx = 0.0, nvx = 0.0, nvy = 0.0, nvz = 0.0;
-  float nvp2 = 0.0f;
-  uint64_t nuid = 0;
-  auto fetch = [&](const int64_t q) {
-    const int64_t i = q * kWave + lane;
-    nx = __longlong_as_double(0x7FF8000000000000LL);
-    nvx = nvy = nvz = 0.0;
-    nvp2 = 0.0f;
-    nuid = 0;
-    if (i < n) {
-      nx = X[i];
-      nvx = VX[i];
-      if (SP == 1 || pdiag) {
-        nvy = VY[i];
-        nvz = VZ[i];
-      }
-      if (SP == 0) nvp2 = VP2[i];
-      nuid = UID[i];
-    }
+  // The streaming loop.  The state of a wave's next slice is loaded before its
+  // current one is worked on.  A slice's loads and its two stores are
+  // unconditional, whatever its particles do: the wave's memory counter
+  // counts both in order, and only a fixed number of stores behind the loads
+  // lets the next slice wait for its loads without waiting for this one's
+  // stores.
+  const int q_lo = (int)(c_lo * kWaves);
+  const int q_end = (int)((n + kWave - 1) / kWave);
+  const int q_hi = (int)(c_hi * kWaves < q_end ? c_hi * kWaves : q_end);
+  struct Slice {
+    double x, vx, vy, vz;
+    float vp2;
+    uint64_t uid;
   };
-  int64_t q = q_lo + w;
-  if (q < q_hi) fetch(q);
-  while (q < q_hi) {
-    const int64_t i = q * kWave + lane;
-    const double x = nx, vx = nvx, vy = nvy, vz = nvz, vp2 = (double)nvp2;
-    const uint64_t uid = nuid;
-    const int64_t qn = q + kWaves;
-    if (qn < q_hi) fetch(qn);
-    bool live = x == x;  // past the end, or absorbed earlier (tombstone)
-    t_live += (int)__popcll(__ballot(live));
-    bool abs_pow = false, abs_gnd = false, surf = false, cand = false;
-    double xn = 0.0, vxn = 0.0, v2 = 0.0;
-    if (live) {
+  // the loop's constants in vector registers: left to itself the compiler,
+  // short of scalar ones, reads them from memory again in every slice
+  auto pinned = [](double v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  const double inv_dx_v = pinned(inv_dx), L_v = pinned(L_gap), dt_v = pinned(dt), kick_v = pinned(kick);
+  auto stream = [&](auto diag) {
+    constexpr bool DIAG = decltype(diag)::value;  // some particle measurement is on
+    auto fetch = [&](const int q) {
+      // the slots up to the next multiple of 64 are within the capacity
+      const int64_t i0 = (int64_t)q * kWave;
+      Slice a{};
+      a.x = (X + i0)[lane];
+      a.vx = (VX + i0)[lane];
+      if (SP == 1 || DIAG) {
+        a.vy = (VY + i0)[lane];
+        a.vz = (VZ + i0)[lane];
+      }
+      if (SP == 0) a.vp2 = (VP2 + i0)[lane];
+      a.uid = (UID + i0)[lane];
+      return a;
+    };
+    int q = q_lo + w;
+    if (q >= q_hi) return;
+    Slice next = fetch(q);
+    for (;;) {
+      const Slice a = next;
+      const int qn = q + kWaves;
+      const bool more = qn < q_hi;
+      next = fetch(more ? qn : q);
+      const int i0 = q * kWave;
+      const double vy = a.vy, vz = a.vz;
+      const uint64_t uid = a.uid;
+      double x = a.x, vx = a.vx, vp2 = (double)a.vp2;
+      bool live = x == x;  // not absorbed earlier (tombstone)
+      if (i0 + kWave > n) {  // the last slice: slots from n on hold nothing
+        if (lane >= (int)(n - i0)) {
+          live = false;
+          vx = vp2 = 0.0;
+        }
+      }
+      x = live ? x : 0.0;
+      t_live += (int)__popcll(ballot(live));
+      bool surf = false, cand = false;
       // Steps 3-4: linear interpolation of the nodal field (section 2.1.3)
       // from cell coordinate xi = x/dx, then the leapfrog equations of
       // section 2.1.4, the kick being e dt/m per unit field (subtracted for
       // the electron's negative charge).
-      const double xi = x * inv_dx;
+      const double xi = x * inv_dx_v;
       int cell = (int)xi;
       cell = cell > ng - 2 ? ng - 2 : (cell < 0 ? 0 : cell);
       const double w_lo = (double)(cell + 1) - xi;  // weight of node `cell`
       const double w_hi = xi - (double)cell;        // weight of node `cell + 1`
       const double e_here = sE[cell] * w_lo + sE[cell + 1] * w_hi;
-      vxn = SP == 0 ? vx - e_here * kick : vx + e_here * kick;
-      xn = x + vxn * dt;
-      // the pre-test's bound of P for this particle by energy, looked up now
-      // so that the LDS load is in flight during the wall test, the deposit
-      // and the Philox call (a reflection below keeps |v|)
-      double pc = p_cand, g2u = 0.0;
-      if (by_energy) {
-        v2 = SP == 0 ? vxn * vxn + vp2 : vxn * vxn + vy * vy + vz * vz;
-        g2u = SP == 0 ? v2 : 2.0 * (v2 + a2_i);
-        double rows = g2u * rows_per_g2 + 0.5;
-        rows = rows < (double)(nbins - 1) ? rows : (double)(nbins - 1);
-        pc = sPB[(int)rows >> pb_shift];
-      }
-      if (pdiag) {
+      double vxn = SP == 0 ? vx - e_here * kick_v : vx + e_here * kick_v;
+      double xn = x + vxn * dt_v;
+      // Step 6 pre-test.  A particle can collide only if its R is below the
+      // bound of 1 - exp(-nu dt) over the tables (P* for null collisions), or
+      // if it is faster than the range that bound covers; the upper word of R
+      // decides that but for R within 2^-32 of the bound, which the exact
+      // test settles like every candidate.  The bound by energy is looked up
+      // first, so that the LDS load is in flight beside the rest (a
+      // reflection below keeps |v|).
+      const double v2 = SP == 0 ? vxn * vxn + vp2 : vxn * vxn + vy * vy + vz * vz;
+      const double g2u = SP == 0 ? v2 : 2.0 * (v2 + a2_i);
+      uint32_t r_lim = r_cand;
+      if (by_energy) r_lim = sPB[(int)fmin(g2u * blocks_per_g2 + block_half, block_last)];
+      if (DIAG && live) {
         // measurement at integer time: old position, mean of the half-step
         // velocities; the ionization rate as the expected n sigma_ion |v|
         const double vbar = 0.5 * (vx + vxn);
@@ -1283,6 +1354,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
           }
         }
       }
+      const uint32_t r_word = philox_w0(seed, uid, st, r_tag);
       // Step 5: absorbing electrodes; an absorbed ion adds its impact energy
       // to its electrode's IFEDF (bin n_ifed: beyond the range).  Surface
       // processes (purpose 3 of the particle's counter): an electron is
@@ -1291,8 +1363,8 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       // electron with probability gamma, whose charge goes on the electrode
       // node of the next step's deposit now and which takes its slot from
       // the step's electron births below.
-      abs_pow = xn < 0.0;
-      abs_gnd = xn > L_gap;
+      bool abs_pow = live && xn < 0.0;
+      bool abs_gnd = live && xn > L_v;
       if (surf_on && (abs_pow || abs_gnd)) {
         double r_surf, r_unused;
         uniform2(seed, uid, st, tag(SP, 3, 0), r_surf, r_unused);
@@ -1308,76 +1380,81 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
           } else {
             surf = true;
             long long r;
-            const int q = deposit_split(abs_pow ? 0.0 : L_gap, inv_dx, ng, r);
-            gl_add(&cnt_e_next[q], 4294967296LL - r);
-            if (r) gl_add(&cnt_e_next[q + 1], r);
+            const int p = deposit_split(abs_pow ? 0.0 : L_gap, inv_dx, ng, r);
+            gl_add(&cnt_e_next[p], 4294967296LL - r);
+            if (r) gl_add(&cnt_e_next[p + 1], r);
           }
         }
       }
-      if (abs_pow || abs_gnd) {
-        live = false;
-        if (SP == 1 && (fl & kDiagIfed)) {
-          const double en = 0.5 * kArMass * (vxn * vxn + vy * vy + vz * vz) / kEvToJ;
-          const double t = en / de_ifed;
-          const int b = t < (double)n_ifed ? (int)t : n_ifed;
-          atomicAdd(&sF[(abs_gnd ? n_ifed + 1 : 0) + b], 1u);
-        }
-      } else {
-        // Step 7 for step s+1: deposit the new position.  Step 6 pre-test:
-        // a particle can collide only if its R is below the bound of
-        // 1 - exp(-nu dt) over the tables (exactly P* for null collisions),
-        // or if it is faster than the range that bound covers; the others
-        // are settled here with no table work, the candidates go to the
-        // wave's segment for the exact test.
+      const bool in = live && !(abs_pow || abs_gnd);
+      if (DIAG && SP == 1 && (fl & kDiagIfed) && live && !in) {
+        const double en = 0.5 * kArMass * (vxn * vxn + vy * vy + vz * vz) / kEvToJ;
+        const double t = en / de_ifed;
+        const int b = t < (double)n_ifed ? (int)t : n_ifed;
+        atomicAdd(&sF[(abs_gnd ? n_ifed + 1 : 0) + b], 1u);
+      }
+      // Step 7 for step s+1: deposit the new position
+      if (in) {
         long long r;
-        const int q = deposit_split(xn, inv_dx, ng, r);
-        lds_add(&sH[q], 4294967296LL - r);
-        lds_add(&sH[q + 1], r);
-        double r_coll, r_proc;
-        uniform2(seed, uid, st, r_tag, r_coll, r_proc);
-        if (!by_energy) {
-          v2 = SP == 0 ? vxn * vxn + vp2 : vxn * vxn + vy * vy + vz * vz;
-          g2u = SP == 0 ? v2 : 2.0 * (v2 + a2_i);
-        }
-        cand = r_coll < pc || g2u > v2_cand;
+        const int p = deposit_split(xn, inv_dx_v, ng, r);
+        lds_add(&sH[p], 4294967296LL - r);
+        lds_add(&sH[p + 1], r);
+        cand = r_word <= r_lim || g2u > v2_cand;
       }
-    }
-    if (i < n && x == x) {
-      X[i] = live ? xn : __longlong_as_double(0x7FF8000000000000LL);
-      VX[i] = vxn;
-    }
-    if (surf_on) {
-      // reflections (electrons) or emissions per electrode (ions); an ion's
-      // secondary electron takes its slot after this step's births so far
-      const uint64_t m_s0 = __ballot(surf && (SP == 0 || abs_pow));
-      const uint64_t m_s1 = SP == 1 ? __ballot(surf && abs_gnd) : 0ull;
-      if (lane == 0 && m_s0) gl_add(&Cw->ctr[SP == 0 ? kRefl : kSeePow], (long long)__popcll(m_s0));
-      if (lane == 0 && m_s1) gl_add(&Cw->ctr[kSeeGnd], (long long)__popcll(m_s1));
-      if (SP == 1 && (m_s0 | m_s1)) {
-        const int64_t be = B.take(0, surf, lane, t_be, t_drop);
-        if (surf) see_emit_at(C, P, uid, abs_pow ? 0 : 1, be, s);
+      double x_out = in ? xn : __longlong_as_double(0x7FF8000000000000LL), v_out = vxn;
+      unsigned at = (unsigned)lane;
+      if (i0 + kWave > n) {
+        // a lane without a slot stores what lane 0 stores (slots from n on
+        // may be a newborn's already)
+        const double x_0 = __shfl(x_out, 0), v_0 = __shfl(v_out, 0);
+        const bool none = lane >= (int)(n - i0);
+        x_out = none ? x_0 : x_out;
+        v_out = none ? v_0 : v_out;
+        at = none ? 0 : at;
       }
-    }
-    const uint64_t m_c = __ballot(cand);
-    if (m_c) {
-      if (cand) {
-        const int at = ncw + lane_rank(m_c);
-        sSeg[w][at] = (int32_t)i;
-        if (SP == 0) {
-          sVx[SP == 0 ? w : 0][SP == 0 ? at : 0] = vxn;
-          sUid[SP == 0 ? w : 0][SP == 0 ? at : 0] = uid;
+      (X + (int64_t)i0)[at] = x_out;
+      (VX + (int64_t)i0)[at] = v_out;
+      if (surf_on) {
+        // reflections (electrons) or emissions per electrode (ions); an ion's
+        // secondary electron takes its slot after this step's births so far
+        const uint64_t m_s0 = ballot(surf && (SP == 0 || abs_pow));
+        const uint64_t m_s1 = SP == 1 ? ballot(surf && abs_gnd) : 0ull;
+        if (lane == 0 && m_s0) gl_add(&Cw->ctr[SP == 0 ? kRefl : kSeePow], (long long)__popcll(m_s0));
+        if (lane == 0 && m_s1) gl_add(&Cw->ctr[kSeeGnd], (long long)__popcll(m_s1));
+        if (SP == 1 && (m_s0 | m_s1)) {
+          const int64_t be = B.take(0, surf, lane, t_be, t_drop);
+          if (surf) see_emit_at(C, P, uid, abs_pow ? 0 : 1, be, s);
         }
       }
-      ncw += (int)__popcll(m_c);
-      if (ncw > kSeg - kWave) {
-        spill_segment(ncw);
-        ncw = 0;
+      const uint64_t m_c = ballot(cand);
+      if (m_c) {
+        if (cand) {
+          const int k = ncw + lane_rank(m_c);
+          sSeg[w][k] = i0 + lane;
+          if (SP == 0) {
+            sVx[SP == 0 ? w : 0][SP == 0 ? k : 0] = vxn;
+            sUid[SP == 0 ? w : 0][SP == 0 ? k : 0] = uid;
+          }
+        }
+        ncw += (int)__popcll(m_c);
+        if (ncw > kSeg - kWave) {
+          spill_segment(ncw);
+          ncw = 0;
+        }
       }
+      t_pow += (int)__popcll(ballot(abs_pow));
+      t_gnd += (int)__popcll(ballot(abs_gnd));
+      if (!more) break;
+      q = qn;
     }
-    t_pow += (int)__popcll(__ballot(abs_pow));
-    t_gnd += (int)__popcll(__ballot(abs_gnd));
-    q = qn;
-  }
+  };
+  if (pdiag)
+    stream(std::true_type{});
+  else
+    stream(std::false_type{});
+  // the first round's v_y and v_z are on their way during the barrier and the
+  // flush
+  const Entry first = own_entry(lane);
   __syncthreads();
   // flush first (deposit for step s+1 and diagnostics of step s): the
   // last candidate pass below adds its newborns' charge to global memory
@@ -1397,7 +1474,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   for (int b = threadIdx.x; b < n_hist; b += blockDim.x)
     if (sF[b]) gl_add(&hist[b], (long long)sF[b]);
   // this wave's segment, then the workgroup's overflow list
-  finish();
+  finish(first);
   if (lane == 0) {
     sTot[w][kRecColl] = t_coll;
     sTot[w][kRecIoniz] = t_ioniz;

@@ -318,7 +318,7 @@ void set_pointers(CaseDev& h, char* arena, const Layout& L) {
   h.sig_ion = tabs[4];
   h.sig_iso = tabs[5];
   h.sig_back = tabs[6];
-  for (int sp = 0; sp < 2; ++sp) h.pbound[sp] = (const double*)(arena + L.off_pb[sp]);
+  for (int sp = 0; sp < 2; ++sp) h.pbound[sp] = (const uint32_t*)(arena + L.off_pb[sp]);
   h.rden = (double*)(arena + L.off_rden);
   h.volt = (double*)(arena + L.off_volt);
   h.cnt_e = (int64_t*)(arena + L.off_cnt_e);
@@ -369,18 +369,35 @@ int pb_shift(int nbins) {
   return s;
 }
 
+// The largest upper word w0 of a uniform's 64 bits with which R < p is
+// possible: R >= w0 2^-32, so R < p needs w0 <= p 2^32.
+uint32_t candidate_limit(double p) {
+  const double t = p * kTwo32;
+  return t < kTwo32 ? (uint32_t)t : 0xFFFFFFFFu;
+}
+
+// 1/b for the kernels' div_by; NaN where its theorem does not hold (a
+// significand of all ones) or the reciprocal or the products with it could
+// leave the normal range.
+double exact_recip(double b) {
+  uint64_t u;
+  std::memcpy(&u, &b, sizeof u);
+  const uint64_t ones = (uint64_t(1) << 52) - 1;
+  return (u & ones) == ones || !(b > 1e-100 && b < 1e100) ? std::nan("") : 1.0 / b;
+}
+
 // The pre-test's bound by energy (CaseDev::pbound): for block b the prefix
 // maximum of P = 1 - exp(-nu dt) over rows 0 .. the block's last, with the
 // relative margin of p_bound.
-std::vector<double> pbound_table(const std::vector<double>& nsig, double de_ev, double mass, double dt) {
+std::vector<uint32_t> pbound_table(const std::vector<double>& nsig, double de_ev, double mass, double dt) {
   const int nb = (int)nsig.size();
   const int sh = pb_shift(nb);
-  std::vector<double> t((size_t)kMaxPb, 1.0);
+  std::vector<uint32_t> t((size_t)kMaxPb, 0xFFFFFFFFu);
   double m = 0.0;
   for (int i = 0; i < nb; ++i) {
     m = std::max(m, row_nu(nsig, i, de_ev, mass));
     if (i == nb - 1 || ((i + 1) >> sh) != (i >> sh))
-      t[(size_t)(i >> sh)] = std::min(1.0, (1.0 - std::exp(-m * dt)) * (1.0 + 1e-9));
+      t[(size_t)(i >> sh)] = candidate_limit(std::min(1.0, (1.0 - std::exp(-m * dt)) * (1.0 + 1e-9)));
   }
   return t;
 }
@@ -1329,8 +1346,25 @@ int edp_case_create(edp_ctx* ctx, const edp_case_desc* desc, void* dev_arena, in
     h.a2_i = amax * amax;
     h.pb_shift = pb_shift(nb);
     h.pb_n = ((nb - 1) >> h.pb_shift) + 1;
+    // what the particle loop tests (see CaseDev)
+    const bool null_coll = (D.flags & EDP_NULL_COLLISION) != 0;
+    h.p_cand[0] = null_coll ? h.p_null_e : h.p_bound_e;
+    h.p_cand[1] = null_coll ? h.p_null_i : h.p_bound_i;
+    h.v2_cand[0] = null_coll ? HUGE_VAL : h.v2_lim_e;
+    h.v2_cand[1] = null_coll ? HUGE_VAL : h.g2_lim_i;
+    const double blocks_per_row = std::ldexp(1.0, -h.pb_shift);
+    h.blocks_per_v2[0] = 0.5 * kEMass / kEvToJ / ctx->de * (1.0 + 1e-12) * blocks_per_row;
+    h.blocks_per_v2[1] = 0.5 * kMuArAr / kEvToJ / ctx->de * (1.0 + 1e-12) * blocks_per_row;
+    h.block_half = 0.5 * blocks_per_row;
+    h.block_last = (double)(nb - 1) * blocks_per_row;
+    for (int sp = 0; sp < 2; ++sp) h.r_cand[sp] = candidate_limit(h.p_cand[sp]);
   }
   h.de_cs = ctx->de;
+  h.inv_dx_q = exact_recip(h.dx);
+  h.inv_2dx = exact_recip(2.0 * h.dx);
+  h.inv_cells = exact_recip((double)(ng - 1));
+  h.inv_de_cs = exact_recip(ctx->de);
+  h.inv_de_eepf = exact_recip(D.de_eepf_ev);
   h.thr_exc = ctx->thr_exc;
   h.thr_ion = ctx->thr_ion;
   h.w_ion = ctx->w_ion;
@@ -1382,10 +1416,10 @@ int edp_case_create(edp_ctx* ctx, const edp_case_desc* desc, void* dev_arena, in
   hipError_t e = hipSuccess;
   for (int t = 0; t < 7 && e == hipSuccess; ++t)
     e = hipMemcpyAsync(tabs[t], tsrc[t]->data(), (size_t)nb * 8, hipMemcpyHostToDevice, st);
-  const std::vector<double> pb[2] = {pbound_table(nsig_e, ctx->de, kEMass, h.dt_e),
+  const std::vector<uint32_t> pb[2] = {pbound_table(nsig_e, ctx->de, kEMass, h.dt_e),
                                      pbound_table(nsig_i, ctx->de, kMuArAr, h.dt_i)};
   for (int sp = 0; sp < 2 && e == hipSuccess; ++sp)
-    e = hipMemcpyAsync((void*)h.pbound[sp], pb[sp].data(), (size_t)kMaxPb * 8, hipMemcpyHostToDevice, st);
+    e = hipMemcpyAsync((void*)h.pbound[sp], pb[sp].data(), (size_t)kMaxPb * 4, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync((void*)h.rden, rden.data(), (size_t)ng * 8, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(c->d, &h, sizeof(CaseDev), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

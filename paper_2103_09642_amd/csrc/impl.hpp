@@ -111,7 +111,19 @@ struct CaseDev {
   // up to the last of block b (rows r with r >> pb_shift <= b), a prefix
   // maximum, so that the block of any upper bound of a particle's energy
   // gives a bound of its P
-  const double* pbound[2];
+  // (as the largest upper word of R's 64 bits with which R < P is possible)
+  const uint32_t* pbound[2];
+  // per species: the bound over the whole table (or P* for null collisions),
+  // the same as an upper word, the squared speed it covers (infinite for
+  // null collisions), and blocks of the bound by energy per squared
+  // (relative) speed -- a multiple of rows, with a margin against the rounding
+  // of the exact test's own squared speed and energy --, half a row in blocks
+  // and the last row
+  double p_cand[2], v2_cand[2], blocks_per_v2[2], block_half, block_last;
+  uint32_t r_cand[2];
+  // correctly rounded reciprocals of dx, 2 dx, N_g - 1, de_cs and de_eepf (NaN:
+  // divide), see div_by
+  double inv_dx_q, inv_2dx, inv_cells, inv_de_cs, inv_de_eepf;
   int32_t pb_shift, pb_n;
   double kpois;       // dx*dx/eps0
   // surface processes, [0] powered electrode (x = 0), [1] grounded (x = L)

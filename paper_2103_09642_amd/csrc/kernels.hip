@@ -105,10 +105,23 @@ __device__ __forceinline__ uint64_t child_uid(uint64_t parent, int64_t step, uin
   return mix64(mix64(parent) ^ ((uint64_t)step * 0x9E3779B97F4A7C15ull) ^ kind);
 }
 
+// a / b from y = 1/b correctly rounded: the quotient's estimate a y corrected
+// twice by its exact remainder, which makes it the correctly rounded quotient
+// (Markstein's theorem on division by fused multiply-adds; it excepts a b
+// whose significand is all ones, for which the host sets y to NaN).  Five
+// operations instead of the division's dozen, several slow ones among them.
+// For quotients, and remainders, in the normal range or zero, or not finite.
+__device__ __forceinline__ double div_by(double a, double b, double y) {
+  const double q0 = a * y;
+  double q = __builtin_fma(__builtin_fma(-q0, b, a), y, q0);
+  q = __builtin_fma(__builtin_fma(-q, b, a), y, q);
+  return y == y ? (__builtin_isfinite(q0) ? q : q0) : a / b;
+}
+
 // Cross-section table row of a kinetic energy: the nearest of the tabulated
 // energies i * de (section 3.2), every energy past the end in the last row.
-__device__ __forceinline__ int energy_bin(double e_ev, double de, int nbins) {
-  const double rows = e_ev / de + 0.5;
+__device__ __forceinline__ int energy_bin(double e_ev, double de, double inv_de, int nbins) {
+  const double rows = div_by(e_ev, de, inv_de) + 0.5;
   return rows >= (double)(nbins - 1) ? nbins - 1 : (int)rows;
 }
 
@@ -215,6 +228,13 @@ __device__ __forceinline__ unsigned long long gl_fetch_add(int64_t* a, unsigned 
   return __hip_atomic_fetch_add(G((unsigned long long*)a), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+
+// A uniform value in vector registers from here on (the scalar ones are
+// short, and the compiler would read the value again at every use).
+__device__ __forceinline__ double pin_v(double v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 // Exclusive scan of one integer per thread across the workgroup; *total
 // gets the sum.  scratch: 64 int64 of LDS.
@@ -340,6 +360,74 @@ struct FieldWriter {
   }
 };
 
+// Step s in ion steps: k = s / nsub, the step within it, and the rings' places
+// s % 3 and k % 3.  32-bit division up to 2^31 steps (a 64-bit one is some 150
+// dependent instructions at the start of every launch).
+struct StepIndex {
+  int64_t k;
+  int sub, s3, k3;
+  __device__ __forceinline__ StepIndex(int64_t s, int nsub) {
+    if (s < (int64_t)1 << 31) {
+      const uint32_t q = (uint32_t)s / (uint32_t)nsub;
+      k = q;
+      sub = (int)((uint32_t)s - q * (uint32_t)nsub);
+      s3 = (int)((uint32_t)s % 3u);
+      k3 = (int)(q % 3u);
+    } else {
+      k = s / nsub;
+      sub = (int)(s - k * nsub);
+      s3 = (int)(s % 3);
+      k3 = (int)(k % 3);
+    }
+  }
+};
+
+// The constants of a field solve.
+struct SolveIn {
+  double scale, kpois, dx, inv_dx, inv_2dx, inv_cells;
+  __device__ __forceinline__ explicit SolveIn(const EDP_CONST CaseDev* C)
+      : scale(C->dens_scale), kpois(C->kpois), dx(C->dx), inv_dx(C->inv_dx_q), inv_2dx(C->inv_2dx), inv_cells(C->inv_cells) {
+    asm volatile("" : "+s"(scale), "+s"(kpois), "+s"(dx), "+s"(inv_dx), "+s"(inv_2dx), "+s"(inv_cells));
+  }
+};
+
+// The deposit rings a field solve reads, on their way from global memory: a
+// thread's nodes t, t + NB, ... of both species (the first kRingRegs of them;
+// those beyond are loaded when they are staged), and V(t) of the step.
+constexpr int kRingRegs = 4;
+template <int NB>
+struct RingNodes {
+  const EDP_GLOBAL int64_t *gE, *gI;
+  int64_t e[kRingRegs], i[kRingRegs];
+  double V;
+  __device__ __forceinline__ RingNodes(const int64_t* cnt_e, const int64_t* cnt_i, const double* volt, int64_t s, int s3,
+                                       int k3, int ng) {
+    gE = G(cnt_e) + s3 * ng;
+    gI = G(cnt_i) + k3 * ng;
+#pragma unroll
+    for (int q = 0; q < kRingRegs; ++q) {
+      const int p = (int)threadIdx.x + q * NB;
+      e[q] = p < ng ? gE[p] : 0;
+      i[q] = p < ng ? gI[p] : 0;
+    }
+    V = G(volt)[s % kVoltChunk];
+  }
+  __device__ __forceinline__ void stage(int64_t* nE, int64_t* nI, int ng) const {
+#pragma unroll
+    for (int q = 0; q < kRingRegs; ++q) {
+      const int p = (int)threadIdx.x + q * NB;
+      if (p < ng) {
+        nE[p] = e[q];
+        nI[p] = i[q];
+      }
+    }
+    for (int p = (int)threadIdx.x + kRingRegs * NB; p < ng; p += NB) {
+      nE[p] = gE[p];
+      nI[p] = gI[p];
+    }
+  }
+};
+
 // Steps 1-2 of step s, computed by every workgroup that needs E (each
 // particle workgroup of a lockstep launch, the small-case workgroup): the
 // densities of the deposit rings read at step s, rho, the potential and E on
@@ -353,38 +441,26 @@ struct FieldWriter {
 // coalesced loads, and the rows of a thread are worked in a loop, not
 // unrolled to the largest grid with the writer's code in each copy (the
 // electron kernel's code 64 -> 42 KB; a step of 1e3 electrons on 400 nodes
-// 13.6 -> 12.4 us, of 5e4 with every measurement 19.5 -> 17.2 us).
+// 13.5 -> 12.4 us).
 template <int MODE, int NB>
-__device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int64_t* __restrict__ cnt_e,
-                                            const int64_t* __restrict__ cnt_i, const double* __restrict__ volt,
-                                            const int ng, const int nsub, const int64_t s, double* sE, double* sF,
-                                            const bool writer) {
+__device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int ng, const int64_t s,
+                                            const StepIndex& I, double* sE, double* sF, const bool writer,
+                                            const RingNodes<NB>& N, const SolveIn& S) {
   __shared__ double sWave[2][NB / kWave];
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
-  const int64_t k = s / nsub;
-  const bool ion_step = (s % nsub) == 0;
-  const int s3 = (int)(s % 3), k3 = (int)(k % 3);
-  const EDP_GLOBAL int64_t* cntE = G(cnt_e) + s3 * ng;
-  const EDP_GLOBAL int64_t* cntI = G(cnt_i) + k3 * ng;
+  const bool ion_step = I.sub == 0;
   const int t = (int)threadIdx.x;
-  const int lane = t % kWave, wv = t / kWave;
+  const int lane = t % kWave, wv = __builtin_amdgcn_readfirstlane(t / kWave);
   // the rings, staged where E and the scratch go
   int64_t* const nE = (int64_t*)sF;
   int64_t* const nI = (int64_t*)sE;
-#pragma unroll 4
-  for (int p = t; p < ng; p += NB) {
-    const int64_t a = cntE[p], b = cntI[p];
-    nE[p] = a;
-    nI[p] = b;
-  }
-  const double V = G(volt)[s % kVoltChunk];
-  const double scale = C->dens_scale;
-  const double kp = C->kpois;
-  const double dx = C->dx;
+  N.stage(nE, nI, ng);
+  const double V = N.V;
+  const double scale = S.scale, kp = S.kpois, dx = S.dx;
   FieldWriter W;
   W.C = C;
-  W.s3 = s3;
-  W.k3 = k3;
+  W.s3 = I.s3;
+  W.k3 = I.k3;
   W.ng = ng;
   W.ion_step = ion_step;
   W.xt = writer && (C->flags & kDiagXT) != 0;
@@ -475,31 +551,53 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
     // over the half cell) at the electrodes.
     const int m = ng - 2;
     const int R = (m + NB - 1) / NB;
-    const int q0 = t * R < m ? t * R : m;
-    const int nq = (q0 + R < m ? q0 + R : m) - q0;
+    const int q0 = t * R;
     // the owner of the last row also takes node N_g-1 (thread 0 when there
     // are no interior rows)
-    const bool last = nq > 0 ? q0 + nq == m : (t == 0 && m == 0);
+    const bool last = q0 < m ? q0 + R >= m : (t == 0 && m == 0);
     const double rho0 = t == 0 ? dens(0, ne, ni) : 0.0;
     const double rhoN = last ? dens(ng - 1, ne, ni) : 0.0;
-    double acc = 0.0, wsum = 0.0;
+    double acc = 0.0, wsum = 0.0, weight = (double)(m - q0);
+    // kGroup rows at a time, so that their LDS reads are in flight together
+    constexpr int kGroup = 4;
 #pragma unroll 1
-    for (int r = 0; r < nq; ++r) {
-      const int p = q0 + 1 + r;
-      const double d = dens(p, ne, ni) * kp;
-      acc += d;
-      wsum += d * (double)(m - (q0 + r));
-      sE[p] = acc;  // prefix within the thread
+    for (int r0 = 0; r0 < R; r0 += kGroup) {
+      int64_t ce[kGroup], ci[kGroup];
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r) {
+        const int p = q0 + 1 + r0 + r;
+        const int pc = p < ng ? p : ng - 1;
+        ce[r] = nE[pc];
+        ci[r] = nI[pc];
+      }
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r) {
+        if (r0 + r < R && q0 + r0 + r < m) {
+          const double d = kECharge * ((double)ci[r] * scale - (double)ce[r] * scale) * kp;
+          acc += d;
+          wsum += d * weight;
+          sE[q0 + 1 + r0 + r] = acc;  // prefix within the thread
+        }
+        weight -= 1.0;
+      }
     }
     // the workgroup pass: inclusive scan of acc and sum of wsum per wave
     double inc = acc;
+    const int lane4 = lane * 4;
+    auto permute = [&](int from4, double v) {
+      const uint64_t u = (uint64_t)__double_as_longlong(v);
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(uint32_t)u);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(u >> 32));
+      return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+    };
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const double y = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc += y;
+    for (int u = 0; u < 6; ++u) {
+      const int off = 1 << u, xo = kWave / 2 >> u;
+      const double y = permute(lane4 + 4 * (kWave - off), inc);  // from lane - off
+      const double z = permute(lane4 ^ (4 * xo), wsum);
+      inc = lane >= off ? inc + y : inc;
+      wsum += z;
     }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off, kWave);
     if (lane == kWave - 1) {
       sWave[0][wv] = inc;
       sWave[1][wv] = wsum;
@@ -511,22 +609,32 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int6
       if (u < wv) before += sWave[0][u];
       sum_s += sWave[1][u];
     }
-    const double F0 = (V - sum_s) / (double)(ng - 1);
+    const double F0 = div_by(V - sum_s, (double)(ng - 1), S.inv_cells);
     double f_prev = F0 + before;  // F_{q0}: F0 plus the rows before this thread's
 #pragma unroll 1
-    for (int r = 0; r < nq; ++r) {
-      const int p = q0 + 1 + r;
-      const double f = F0 + (before + sE[p]);  // F_{q+1} = F_p
-      sE[p] = (f_prev + f) / (2.0 * dx);
-      if (writer) W.flux(p, f);
-      f_prev = f;
+    for (int r0 = 0; r0 < R; r0 += kGroup) {
+      double v[kGroup];
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r) {
+        const int p = q0 + 1 + r0 + r;
+        v[r] = sE[p < ng ? p : ng - 1];
+      }
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r)
+        if (r0 + r < R && q0 + r0 + r < m) {
+          const int p = q0 + 1 + r0 + r;
+          const double f = F0 + (before + v[r]);  // F_{q+1} = F_p
+          sE[p] = div_by(f_prev + f, 2.0 * dx, S.inv_2dx);
+          if (writer) W.flux(p, f);
+          f_prev = f;
+        }
     }
     if (t == 0) {
-      sE[0] = F0 / dx - rho0 * dx / (2.0 * kEps0);
+      sE[0] = div_by(F0, dx, S.inv_dx) - div_by(rho0 * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
       if (writer) W.flux(0, F0);
     }
     if (last) {
-      sE[ng - 1] = f_prev / dx + rhoN * dx / (2.0 * kEps0);
+      sE[ng - 1] = div_by(f_prev, dx, S.inv_dx) + div_by(rhoN * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
       if (writer) W.flux(ng - 1, V);
     }
     for (int p = t; p < ng; p += NB) sF[p] = 0.0;
@@ -563,23 +671,24 @@ struct ScatterPtrs {
   int64_t* anomaly;
 };
 
-// The arrays of buffer sets ce (electrons) and ci (ions).
-__device__ __forceinline__ ScatterPtrs scatter_ptrs_at(CaseDev* __restrict__ Cw, int ce, int ci) {
-  const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
-  ScatterPtrs P;
-  P.anomaly = &Cw->ctr[kAnomaly];
-  P.ex = G(C->sp[0].x[ce]);
-  P.evx = G(C->sp[0].vx[ce]);
-  P.evy = G(C->sp[0].vy[ce]);
-  P.evz = G(C->sp[0].vz[ce]);
-  P.evp2 = G(C->sp[0].vp2[ce]);
-  P.euid = G(C->sp[0].uid[ce]);
-  P.ix = G(C->sp[1].x[ci]);
-  P.ivx = G(C->sp[1].vx[ci]);
-  P.ivy = G(C->sp[1].vy[ci]);
-  P.ivz = G(C->sp[1].vz[ci]);
-  P.iuid = G(C->sp[1].uid[ci]);
-  return P;
+// The arrays of species sp's buffer set `cur`, read where they are needed
+// (the other species' arrays, by the few workgroups with a newborn).
+__device__ __forceinline__ void read_scatter_ptrs(ScatterPtrs& P, const EDP_CONST CaseDev* __restrict__ C, int sp, int cur) {
+  const EDP_CONST SpeciesDev& S = C->sp[sp];
+  if (sp == 0) {
+    P.ex = G(S.x[cur]);
+    P.evx = G(S.vx[cur]);
+    P.evy = G(S.vy[cur]);
+    P.evz = G(S.vz[cur]);
+    P.evp2 = G(S.vp2[cur]);
+    P.euid = G(S.uid[cur]);
+  } else {
+    P.ix = G(S.x[cur]);
+    P.ivx = G(S.vx[cur]);
+    P.ivy = G(S.vy[cur]);
+    P.ivz = G(S.vz[cur]);
+    P.iuid = G(S.uid[cur]);
+  }
 }
 
 // Electron-Ar collisions, from the colliding electron's state after the push
@@ -624,18 +733,17 @@ __device__ __forceinline__ void ionization_angle(const EDP_CONST CaseDev* __rest
 // An outgoing electron of a collision: the colliding electron itself
 // (process proc: 0 elastic, 1 excitation, 2 ionization) or, with `eject`,
 // the electron its ionization ejects (proc 2), from the parent's pushed
-// velocity and identity.  Both take the frame of g and the draws of the
-// parent's counter; the ejected one leaves with the other share of the
+// velocity and identity, with the draws r_chi and r_eta of the parent's
+// counter.  Both take the frame of g; the ejected one leaves with the other share of the
 // energy at the azimuth eta + pi.  Returns the new velocity.
 __device__ __forceinline__ void electron_outgoing(const EDP_CONST CaseDev* __restrict__ C, const ScatterPtrs& P,
                                                   bool eject, int proc, int64_t s, double vxn, double vy,
-                                                  double vz, uint64_t uid, double& ox, double& oy, double& oz) {
+                                                  double vz, uint64_t uid, double r_chi, double r_eta, double& ox,
+                                                  double& oy, double& oz) {
   const uint32_t st = (uint32_t)s;
   // squared speed, the squares summed from x to z as the collision test does
   const double v2 = vxn * vxn + vy * vy + vz * vz;
   const double v = sqrt(v2);
-  double r_chi, r_eta;
-  uniform2(C->seed, uid, st, tag(0, 0, 1), r_chi, r_eta);
   double gnew = v, cos_chi, sin_chi;
   if (proc < 2) {
     if (proc == 1) {
@@ -792,13 +900,6 @@ constexpr int kSegE = 128;
 template <int SP>
 constexpr int seg_len() { return SP == 0 ? kSegE : kSegI; }
 
-// The largest upper word w0 of a uniform's 64 bits with which R < p is
-// possible: R >= w0 2^-32, so R < p needs w0 <= p 2^32.
-__device__ __forceinline__ uint32_t candidate_limit(double p) {
-  const double t = p * kTwo32;
-  return t < kTwo32 ? (uint32_t)t : 0xFFFFFFFFu;
-}
-
 // Birth slots of one step: a species' newborns take consecutive slots after
 // its slot count at the step's start, from a counter of the step's births
 // (LDS in the small-case kernel, born[sp][s % 3] in global memory in the
@@ -850,21 +951,95 @@ struct Births {
   }
 };
 
+// Every line of the case block is asked for at a launch's start, where the
+// scalar cache is cold: what a later phase reads is then there, instead of a
+// wait of about 500 cycles at the first touch of each line.
+__device__ __forceinline__ void touch_case(const EDP_CONST CaseDev* C) {
+  constexpr int kLines = (int)((sizeof(CaseDev) + 63) / 64);
+  static_assert(kLines <= 20, "lines of the case block");
+  uint32_t d[20];
+#pragma unroll
+  for (int k = 0; k < 20; ++k) d[k] = ((const EDP_CONST uint32_t*)C)[16 * (k < kLines ? k : 0)];
+  asm volatile("" ::"s"(d[0]), "s"(d[1]), "s"(d[2]), "s"(d[3]), "s"(d[4]), "s"(d[5]), "s"(d[6]), "s"(d[7]), "s"(d[8]),
+               "s"(d[9]), "s"(d[10]), "s"(d[11]), "s"(d[12]), "s"(d[13]), "s"(d[14]), "s"(d[15]), "s"(d[16]), "s"(d[17]),
+               "s"(d[18]), "s"(d[19]));
+}
+
+// What a pass over a species needs before its loop, read in one go: left
+// where they are used, the reads are a dozen scalar loads one after another,
+// each a wait of a few hundred cycles (more in a launch, whose caches start
+// cold).  Both buffer sets' pointers are read, so that no read waits for the
+// index of the current one.
+template <int SP>
+struct PassIn {
+  double *x[2], *vx[2], *vy[2], *vz[2];
+  uint64_t* uid[2];
+  float* vp2[2];
+  const uint32_t* pbound;
+  int64_t *cnt_e, *cnt_i;
+  double inv_dx, L, dt, kick, p_cand, v2_cand, blocks_per_v2, block_half, block_last;
+  uint64_t seed;
+  uint32_t flags, r_cand;
+  int pb_n, surf_on;
+  __device__ __forceinline__ explicit PassIn(const EDP_CONST CaseDev* C) {
+    const EDP_CONST SpeciesDev& S = C->sp[SP];
+    for (int c = 0; c < 2; ++c) {
+      x[c] = S.x[c];
+      vx[c] = S.vx[c];
+      vy[c] = S.vy[c];
+      vz[c] = S.vz[c];
+      uid[c] = S.uid[c];
+      vp2[c] = S.vp2[c];
+    }
+    pbound = C->pbound[SP];
+    cnt_e = C->cnt_e;
+    cnt_i = C->cnt_i;
+    inv_dx = C->inv_dx;
+    L = C->L;
+    dt = SP == 0 ? C->dt_e : C->dt_i;
+    kick = SP == 0 ? C->factor_e : C->factor_i;
+    p_cand = C->p_cand[SP];
+    v2_cand = C->v2_cand[SP];
+    blocks_per_v2 = C->blocks_per_v2[SP];
+    block_half = C->block_half;
+    block_last = C->block_last;
+    r_cand = C->r_cand[SP];
+    seed = C->seed;
+    flags = C->flags;
+    pb_n = C->pb_n;
+    surf_on = SP == 0 ? C->refl_on : C->see_on;
+    // one point that needs them all
+    asm volatile(""
+                 : "+s"(x[0]), "+s"(x[1]), "+s"(vx[0]), "+s"(vx[1]), "+s"(vy[0]), "+s"(vy[1]), "+s"(vz[0]), "+s"(vz[1]),
+                   "+s"(uid[0]), "+s"(uid[1]), "+s"(vp2[0]), "+s"(vp2[1]), "+s"(pbound), "+s"(inv_dx), "+s"(L), "+s"(dt),
+                   "+s"(kick), "+s"(p_cand), "+s"(v2_cand), "+s"(blocks_per_v2), "+s"(seed), "+s"(flags), "+s"(r_cand),
+                   "+s"(block_half), "+s"(block_last), "+s"(pb_n), "+s"(surf_on), "+s"(cnt_e), "+s"(cnt_i));
+  }
+};
+
 // Totals of one species' step in one workgroup (kRec fields, summed over the
-// waves).
+// waves): in the small-case kernel v, in every thread; in a lockstep launch
+// the wave's own, field f in lane f.
 struct SpTot {
   int v[kRec];
+  int field;
 };
 
 // Steps 3-6 of species SP at step s over chunks [c_lo, c_hi) of slots [0, n)
 // of buffer set `cur` (the other species' current set `cur_o`), E in sE,
 // `reg` the LDS region for the deposit histogram (and the particle
-// diagnostics), B the step's birth counters.
-template <int SP, bool SMALL, int NB>
+// diagnostics), B the step's birth counters.  `solve` fills sE (and leaves
+// the histogram zero) and ends with a barrier; it runs after the pass has
+// read its constants and sent the loads of its first slice on their way, so
+// that neither is waited for again: a launch starts with cold caches, and
+// with the constants read where they are used the loop began a dozen
+// dependent scalar loads after the solve.
+template <int SP, bool SMALL, int NB, class Solve>
 __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const double* sE, double* reg,
-                                              const int64_t s, const int64_t n, const int64_t c_lo,
+                                              const int64_t s, const StepIndex& I, const int64_t n, const int64_t c_lo,
                                               const int64_t c_hi, const int cur, const int cur_o,
-                                              const Births<SMALL>& B, const int pretest) {
+                                              const Births<SMALL>& B, const int pretest, const PassIn<SP>& A,
+                                              const Solve& solve) {
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   constexpr int kSeg = seg_len<SP>();
   constexpr bool ZEROED = !(SMALL && SP == 1);  // the solve left the histogram zero
@@ -872,7 +1047,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   __shared__ int32_t sSeg[NB / kWave][kSeg];
   __shared__ double sVx[kPay][SP == 0 ? kSeg : 1];
   __shared__ uint64_t sUid[kPay][SP == 0 ? kSeg : 1];
-  __shared__ int sTot[NB / kWave][kRec];
+  __shared__ int sTot[SMALL ? NB / kWave : 1][kRec];
   // entries of the overflow list, next pass over it
   __shared__ int sOvf, sFin;
   // the pre-test's bound of P by energy block (direct collision test), as
@@ -881,9 +1056,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   // lanes of a pass's ionizing colliders by rank (electrons)
   __shared__ int sIon[SP == 0 ? NB / kWave : 1][SP == 0 ? kWave : 1];
   const int ng = C->ng;
-  const int nsub = C->nsub;
-  const int64_t kion = s / nsub;
-  const uint32_t fl = C->flags;
+  const uint32_t fl = A.flags;
   const bool pdiag = (fl & kDiagParticle) != 0;
   const bool xt = (fl & kDiagXT) != 0;
   const int n_eepf = C->n_eepf;
@@ -919,62 +1092,71 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   // quarter round of candidates (measured: 2% slower on the large case with
   // 8 per wave, 4-12% faster on the batched sets with 20-400).
   const bool null_coll = (fl & kNullCollision) != 0;
-  const double p_null = SP == 0 ? C->p_null_e : C->p_null_i;
-  const double p_cand = null_coll ? p_null : (SP == 0 ? C->p_bound_e : C->p_bound_i);
+  const double p_cand = A.p_cand;
   const bool by_energy =
       !null_coll && (pretest == 2 || (pretest == 0 && (double)(c_hi - c_lo) * kWave * p_cand > (double)(kWave / 4)));
   if (by_energy) {
-    const int pb_n = C->pb_n;
-    const EDP_GLOBAL double* __restrict__ pbg = G(C->pbound[SP]);
-    for (int b = threadIdx.x; b < pb_n; b += blockDim.x) sPB[b] = candidate_limit(pbg[b]);
+    const int pb_n = A.pb_n;
+    const EDP_GLOBAL uint32_t* __restrict__ pbg = G(A.pbound);
+    for (int b = threadIdx.x; b < pb_n; b += blockDim.x) sPB[b] = pbg[b];
   }
   if (threadIdx.x == 0) {
     sOvf = 0;
     sFin = 0;
   }
-  __syncthreads();
-  EDP_GLOBAL double* __restrict__ X = G(C->sp[SP].x[cur]);
+  EDP_GLOBAL double* X = G(cur ? A.x[1] : A.x[0]);
   // this workgroup's overflow list of candidates: its chunk range of the
   // species' list (as many entries as the range has slots)
   EDP_GLOBAL int64_t* __restrict__ CL = G(C->clist[SP]) + c_lo * NB;
-  EDP_GLOBAL double* __restrict__ VX = G(C->sp[SP].vx[cur]);
-  const EDP_GLOBAL double* __restrict__ VY = G(C->sp[SP].vy[cur]);
-  const EDP_GLOBAL double* __restrict__ VZ = G(C->sp[SP].vz[cur]);
-  const EDP_GLOBAL uint64_t* __restrict__ UID = G(C->sp[SP].uid[cur]);
+  EDP_GLOBAL double* VX = G(cur ? A.vx[1] : A.vx[0]);
+  EDP_GLOBAL double* VY = G(cur ? A.vy[1] : A.vy[0]);
+  EDP_GLOBAL double* VZ = G(cur ? A.vz[1] : A.vz[0]);
+  EDP_GLOBAL uint64_t* UID = G(cur ? A.uid[1] : A.uid[0]);
   // electrons: a float bound of vy*vy + vz*vz per slot, read in place of vy
   // and vz for the pre-test (those only by the candidates' exact test and the
   // measurement sums)
-  const EDP_GLOBAL float* __restrict__ VP2 = G(C->sp[SP].vp2[cur]);
-  const ScatterPtrs P = SP == 0 ? scatter_ptrs_at(Cw, cur, cur_o) : scatter_ptrs_at(Cw, cur_o, cur);
-  const double inv_dx = C->inv_dx, L_gap = C->L;
-  const double dt = SP == 0 ? C->dt_e : C->dt_i;
-  const double kick = SP == 0 ? C->factor_e : C->factor_i;
+  EDP_GLOBAL float* VP2 = G(cur ? A.vp2[1] : A.vp2[0]);
+  ScatterPtrs P;
+  P.anomaly = &Cw->ctr[kAnomaly];
+  if (SP == 0) {
+    P.ex = X;
+    P.evx = VX;
+    P.evy = VY;
+    P.evz = VZ;
+    P.evp2 = VP2;
+    P.euid = UID;
+  } else {
+    P.ix = X;
+    P.ivx = VX;
+    P.ivy = VY;
+    P.ivz = VZ;
+    P.iuid = UID;
+  }
+  // the loop's constants, in vector registers (the scalar ones are short)
+  const double inv_dx = pin_v(A.inv_dx), L_gap = pin_v(A.L), dt = pin_v(A.dt), kick = pin_v(A.kick);
   const EDP_GLOBAL double* __restrict__ nsig = G(SP == 0 ? C->nsig_e : C->nsig_i);
   const EDP_GLOBAL double* __restrict__ sig0 = G(SP == 0 ? C->sig_el : C->sig_iso);
   const EDP_GLOBAL double* __restrict__ sig1 = G(SP == 0 ? C->sig_exc : C->sig_back);
   const EDP_GLOBAL double* __restrict__ sig2 = G(C->sig_ion);
-  int64_t* const cnt_i_next = C->cnt_i + ((kion + 1) % 3) * ng;
-  // this species' deposit for step s+1 (next ion step for ions)
-  int64_t* const dst = SP == 0 ? C->cnt_e + ((s + 1) % 3) * ng : C->cnt_i + ((kion + 1) % 3) * ng;
-  int64_t* const cnt_e_next = C->cnt_e + ((s + 1) % 3) * ng;
-  const double de_cs = C->de_cs;
+  // the deposits of the next step and of the next ion step
+  int64_t* const cnt_e_next = A.cnt_e + (I.s3 == 2 ? 0 : I.s3 + 1) * ng;
+  int64_t* const cnt_i_next = A.cnt_i + (I.k3 == 2 ? 0 : I.k3 + 1) * ng;
+  int64_t* const dst = SP == 0 ? cnt_e_next : cnt_i_next;
+  const double de_cs = C->de_cs, inv_de_cs = C->inv_de_cs;
   const int nbins = C->nbins;
-  const uint64_t seed = C->seed;
+  const uint64_t seed = A.seed;
   const uint32_t st = (uint32_t)s;
   const double x_lo = C->x_lo, x_hi = C->x_hi, de_eepf = C->de_eepf, de_ifed = C->de_ifed;
   const double sa = C->sigma_a;
   // surface processes of this species' electrode hits
-  const bool surf_on = SP == 0 ? C->refl_on != 0 : C->see_on != 0;
+  const bool surf_on = A.surf_on != 0;
   const double p_surf0 = SP == 0 ? C->eta_refl[0] : C->gamma_see[0];
   const double p_surf1 = SP == 0 ? C->eta_refl[1] : C->gamma_see[1];
   const double n_gas = C->n_gas;
   const double nu_star = SP == 0 ? C->nu_star_e : C->nu_star_i;
-  const uint32_t r_cand = candidate_limit(p_cand);
-  const double v2_cand = null_coll ? __builtin_huge_val() : (SP == 0 ? C->v2_lim_e : C->g2_lim_i);
-  // bound blocks per g2u (a power of two of rows), and the last
-  const double blocks_per_row = ldexp(1.0, -C->pb_shift);
-  const double blocks_per_g2 = 0.5 * (SP == 0 ? kEMass : kMuArAr) / kEvToJ / C->de_cs * (1.0 + 1e-12) * blocks_per_row;
-  const double block_half = 0.5 * blocks_per_row, block_last = (double)(nbins - 1) * blocks_per_row;
+  const uint32_t r_cand = A.r_cand;
+  const double v2_cand = pin_v(A.v2_cand);
+  const double blocks_per_g2 = A.blocks_per_v2, block_half = A.block_half, block_last = A.block_last;
   const double a2_i = C->a2_i;
   const uint32_t r_tag = SP == 0 ? tag(0, 0, 0) : tag(1, 0, 2);
   // the wave's index in a scalar register: what depends on it (the slices, the
@@ -988,84 +1170,49 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   // (direct: P = 1 - exp(-n sigma_tot g dt), collide iff R < P, process by
   // sigma_k / sigma_tot; null collision: process by R nu* against the
   // cumulative nu_k, the rest null) from its pushed v_x, v_y, v_z and uid;
-  // returns the process or -1.
-  auto exact_test = [&](const double vxn, const double vy, const double vz, const uint64_t uid) -> int {
-    int proc = -1;
+  // returns the process or -1.  The table entries are asked for before the
+  // random numbers are formed, so that those (for electrons also the
+  // scattering angles' r_chi and r_eta) are formed while they come.
+  auto exact_test = [&](const double vxn, const double vy, const double vz, const uint64_t uid, double& r_chi,
+                        double& r_eta) -> int {
+    double g2, energy;
+    if (SP == 0) {
+      // squared speed summed from x to z (Algorithm 6)
+      g2 = vxn * vxn + vy * vy + vz * vz;
+      energy = div_by(0.5 * kEMass * g2, kEvToJ, 1.0 / kEvToJ);
+    } else {
+      double z0, z1, z2;
+      normals3(seed, uid, st, 1u, 0u, 0u, z0, z1, z2);
+      const double gx = vxn - sa * z0, gy = vy - sa * z1, gz = vz - sa * z2;
+      g2 = gx * gx + gy * gy + gz * gz;
+      energy = div_by(0.5 * kMuArAr * g2, kEvToJ, 1.0 / kEvToJ);
+    }
+    // a valid row whatever the outcome
+    const int idx = energy_bin(energy, de_cs, inv_de_cs, nbins);
+    const double s_a = sig0[idx], s_b = sig1[idx], s_c = SP == 0 ? sig2[idx] : 0.0, s_n = nsig[idx];
     double r_coll, r_proc;
     uniform2(seed, uid, st, r_tag, r_coll, r_proc);
+    if (SP == 0) uniform2(seed, uid, st, tag(0, 0, 1), r_chi, r_eta);
+    const double g = sqrt(g2);
     if (null_coll) {
-      double g, c1, c2, c3;
-      int idx;
-      if (SP == 0) {
-        const double v2 = vxn * vxn + vy * vy + vz * vz;
-        g = sqrt(v2);
-        const double energy = 0.5 * kEMass * v2 / kEvToJ;
-        idx = energy_bin(energy, de_cs, nbins);
-        c1 = (n_gas * sig0[idx]) * g;
-        c2 = c1 + (n_gas * sig1[idx]) * g;
-        c3 = c2 + (n_gas * sig2[idx]) * g;
-      } else {
-        double z0, z1, z2;
-        normals3(seed, uid, st, 1u, 0u, 0u, z0, z1, z2);
-        const double gx = vxn - sa * z0, gy = vy - sa * z1, gz = vz - sa * z2;
-        const double g2 = gx * gx + gy * gy + gz * gz;
-        g = sqrt(g2);
-        const double energy = 0.5 * kMuArAr * g2 / kEvToJ;
-        idx = energy_bin(energy, de_cs, nbins);
-        c1 = (n_gas * sig0[idx]) * g;
-        c2 = c1 + (n_gas * sig1[idx]) * g;
-        c3 = c2;
-      }
+      const double c1 = (n_gas * s_a) * g;
+      const double c2 = c1 + (n_gas * s_b) * g;
+      const double c3 = SP == 0 ? c2 + (n_gas * s_c) * g : c2;
       // the loop's test lets R up to 2^-32 above P* through
-      if (r_coll < p_null) {
-        if (c3 > nu_star) gl_add(&Cw->ctr[kAnomaly], 1);
-        const double t = r_proc * nu_star;
-        proc = t < c1 ? 0 : (t < c2 ? 1 : (SP == 0 && t < c3 ? 2 : -1));
-      }
-    } else {
-      double p_coll, s_a, s_b, s_c = 0.0;
-      int idx;
-      if (SP == 0) {
-        // squared speed summed from x to z (Algorithm 6)
-        const double v2 = vxn * vxn + vy * vy + vz * vz;
-        const double v = sqrt(v2);
-        const double energy = 0.5 * kEMass * v2 / kEvToJ;
-        idx = energy_bin(energy, de_cs, nbins);
-        // the process tables with the total (one round trip; idx is a
-        // valid bin whatever the outcome)
-        s_a = sig0[idx];
-        s_b = sig1[idx];
-        s_c = sig2[idx];
-        const double nu = nsig[idx] * v;
-        p_coll = 1.0 - exp(-nu * dt);
-      } else {
-        double z0, z1, z2;
-        normals3(seed, uid, st, 1u, 0u, 0u, z0, z1, z2);
-        const double gx = vxn - sa * z0, gy = vy - sa * z1, gz = vz - sa * z2;
-        const double g2 = gx * gx + gy * gy + gz * gz;
-        const double g = sqrt(g2);
-        const double energy = 0.5 * kMuArAr * g2 / kEvToJ;
-        idx = energy_bin(energy, de_cs, nbins);
-        s_a = sig0[idx];
-        s_b = sig1[idx];
-        const double nu = nsig[idx] * g;
-        p_coll = 1.0 - exp(-nu * dt);
-      }
-      if (r_coll < p_coll) {
-        if (SP == 0) {
-          const double s_tot = s_a + s_b + s_c;
-          if (!(s_tot > 0.0) || r_proc < s_a / s_tot)
-            proc = 0;
-          else if (r_proc < (s_a + s_b) / s_tot)
-            proc = 1;
-          else
-            proc = 2;
-        } else {
-          proc = (!(s_a + s_b > 0.0) || r_proc < s_a / (s_a + s_b)) ? 0 : 1;
-        }
-      }
+      if (!(r_coll < p_cand)) return -1;
+      if (c3 > nu_star) gl_add(&Cw->ctr[kAnomaly], 1);
+      const double t = r_proc * nu_star;
+      return t < c1 ? 0 : (t < c2 ? 1 : (SP == 0 && t < c3 ? 2 : -1));
     }
-    return proc;
+    const double nu = s_n * g;
+    const double p_coll = 1.0 - exp(-nu * dt);
+    if (!(r_coll < p_coll)) return -1;
+    if (SP == 0) {
+      const double s_tot = s_a + s_b + s_c;
+      if (!(s_tot > 0.0) || r_proc < s_a / s_tot) return 0;
+      return r_proc < (s_a + s_b) / s_tot ? 1 : 2;
+    }
+    return (!(s_a + s_b > 0.0) || r_proc < s_a / (s_a + s_b)) ? 0 : 1;
   };
 
   // A wave's full segment inside the streaming loop goes to the
@@ -1139,40 +1286,28 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
           }
         }
       }
-      int64_t i = c.i;
-      double vxn = c.vxn, vy = c.vy, vz = c.vz;
-      uint64_t uid = c.uid;
-      int proc = have ? exact_test(vxn, vy, vz, uid) : -1;
+      const int64_t i = c.i;
+      const double vxn = c.vxn, vy = c.vy, vz = c.vz;
+      const uint64_t uid = c.uid;
+      double r_chi = 0.0, r_eta = 0.0;
+      const int proc = have ? exact_test(vxn, vy, vz, uid, r_chi, r_eta) : -1;
       const bool hit = proc >= 0;
       const uint64_t mc = ballot(hit);
       const int ncol = (int)__popcll(mc);
       t_coll += ncol;
       if (ncol == 0) continue;
-      // colliders to lanes [0, ncol), the others after them
-      const int to = 4 * (hit ? lane_rank(mc) : ncol + lane_rank(~mc));
-      auto push32 = [&](int v) { return __builtin_amdgcn_ds_permute(to, v); };
-      auto push64 = [&](uint64_t v) {
-        return (uint64_t)(uint32_t)push32((int)(uint32_t)v) | ((uint64_t)(uint32_t)push32((int)(v >> 32)) << 32);
-      };
-      i = (int64_t)push32((int)i);  // slots are below 2^31
-      proc = push32(proc);
-      vxn = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vxn)));
-      vy = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vy)));
-      vz = __longlong_as_double((long long)push64((uint64_t)__double_as_longlong(vz)));
-      uid = push64(uid);
-      const bool coll = lane < ncol;
       if (SP == 1) {
-        if (coll) ion_scatter_at(C, P, i, proc, s, vxn, vy, vz, uid);
+        if (hit) ion_scatter_at(C, P, i, proc, s, vxn, vy, vz, uid);
         continue;
       }
       // The colliders' outgoing electrons and the electrons their ionizations
-      // eject, the latter on the lanes the colliders leave free, in rank
-      // order (more passes if they do not fit); the new ions on their
-      // parents' lanes after that.  The parent's new position and the
-      // newborns' slots are loaded and taken first and used only at the
-      // stores.  One copy of the scattering code for rounds with and without
-      // ionizations: its fetching is a good part of its time.
-      const bool ioniz = coll && proc == 2;
+      // eject, the latter on the lanes without a collider, in rank order
+      // (more passes if they do not fit); the new ions on their parents'
+      // lanes after that.  The parent's new position and the newborns' slots
+      // are loaded and taken first and used only at the stores.  One copy of
+      // the scattering code for rounds with and without ionizations: its
+      // fetching is a good part of its time.
+      const bool ioniz = proc == 2;
       const uint64_t mi = ballot(ioniz);
       const int ni = (int)__popcll(mi);
       const int ri = lane_rank(mi);
@@ -1180,6 +1315,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       long long a_e = 0, a_i = 0;
       if (ni) {
         t_ioniz += ni;
+        read_scatter_ptrs(P, C, 1, cur_o);
         if (ioniz) {
           xb = X[i];
           sIon[SP == 0 ? w : 0][SP == 0 ? ri : 0] = lane;
@@ -1189,22 +1325,23 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       int64_t f_e = 0, f_i = 0;
 #pragma unroll 1
       for (int e0 = 0, pass = 0; pass == 0 || e0 < ni; ++pass) {
-        const int lane0 = pass == 0 ? ncol : 0;
-        const int e = e0 + lane - lane0;  // the ejected electron of this lane, by rank
-        const bool ej = lane >= lane0 && e < ni;
-        const bool par = pass == 0 && coll;
+        // the ejected electron of this lane, by rank
+        const int e = pass == 0 ? lane_rank(~mc) : e0 + lane;
+        const bool ej = (pass > 0 || !hit) && e < ni;
+        const bool par = pass == 0 && hit;
         int src = lane;
-        double tvx = vxn, tvy = vy, tvz = vz;
+        double tvx = vxn, tvy = vy, tvz = vz, t_eta = r_eta;
         uint64_t tuid = uid;
         if (ni) {
           if (ej) src = sIon[SP == 0 ? w : 0][SP == 0 ? e : 0];
           tvx = __shfl(vxn, src);
           tvy = __shfl(vy, src);
           tvz = __shfl(vz, src);
+          t_eta = __shfl(r_eta, src);
           tuid = (uint64_t)__shfl((long long)uid, src);
         }
         double ox = 0.0, oy = 0.0, oz = 0.0;
-        if (par || ej) electron_outgoing(C, P, ej, ej ? 2 : proc, s, tvx, tvy, tvz, tuid, ox, oy, oz);
+        if (par || ej) electron_outgoing(C, P, ej, ej ? 2 : proc, s, tvx, tvy, tvz, tuid, r_chi, t_eta, ox, oy, oz);
         if (par) store_electron_v(P, i, ox, oy, oz);
         if (ni) {
           if (pass == 0) B.first_slots(a_e, a_i, f_e, f_i);
@@ -1216,7 +1353,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
             P.euid[be] = child_uid(tuid, s, 1);
           }
         }
-        e0 += kWave - lane0;
+        e0 += pass == 0 ? kWave - ncol : kWave;
       }
       if (ni) {
         const bool ok_e = f_e + ri < B.cap[0], ok_i = f_i + ri < B.cap[1];
@@ -1250,41 +1387,49 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
     float vp2;
     uint64_t uid;
   };
-  // the loop's constants in vector registers: left to itself the compiler,
-  // short of scalar ones, reads them from memory again in every slice
-  auto pinned = [](double v) {
-    asm volatile("" : "+v"(v));
-    return v;
+  // the slots up to the next multiple of 64 are within the capacity (and a
+  // wave without a slice loads the first one, unused)
+  auto fetch = [&](Slice& a, const int q) {
+    const int64_t i0 = (int64_t)q * kWave;
+    a.x = (X + i0)[lane];
+    a.vx = (VX + i0)[lane];
+    if (SP == 0) a.vp2 = (VP2 + i0)[lane];
+    a.uid = (UID + i0)[lane];
+    if (SP == 1) {
+      a.vy = (VY + i0)[lane];
+      a.vz = (VZ + i0)[lane];
+    }
   };
-  const double inv_dx_v = pinned(inv_dx), L_v = pinned(L_gap), dt_v = pinned(dt), kick_v = pinned(kick);
+  auto fetch_vyz = [&](Slice& a, const int q) {
+    const int64_t i0 = (int64_t)q * kWave;
+    a.vy = (VY + i0)[lane];
+    a.vz = (VZ + i0)[lane];
+  };
+  const int q_first = q_lo + w;
+  Slice next;
+  fetch(next, q_first < q_hi ? q_first : 0);
+  if (SP == 0) {
+    // v_y and v_z of the first slice for the measurements; without them a
+    // second read of the same x, so that these loads need no branch either
+    const int64_t i0 = (int64_t)(q_first < q_hi ? q_first : 0) * kWave;
+    next.vy = ((pdiag ? VY : X) + i0)[lane];
+    next.vz = ((pdiag ? VZ : X) + i0)[lane];
+  }
+  solve();
   auto stream = [&](auto diag) {
     constexpr bool DIAG = decltype(diag)::value;  // some particle measurement is on
-    auto fetch = [&](const int q) {
-      // the slots up to the next multiple of 64 are within the capacity
-      const int64_t i0 = (int64_t)q * kWave;
-      Slice a{};
-      a.x = (X + i0)[lane];
-      a.vx = (VX + i0)[lane];
-      if (SP == 1 || DIAG) {
-        a.vy = (VY + i0)[lane];
-        a.vz = (VZ + i0)[lane];
-      }
-      if (SP == 0) a.vp2 = (VP2 + i0)[lane];
-      a.uid = (UID + i0)[lane];
-      return a;
-    };
-    int q = q_lo + w;
+    int q = q_first;
     if (q >= q_hi) return;
-    Slice next = fetch(q);
     for (;;) {
       const Slice a = next;
       const int qn = q + kWaves;
       const bool more = qn < q_hi;
-      next = fetch(more ? qn : q);
+      fetch(next, more ? qn : q);
+      if (SP == 0 && DIAG) fetch_vyz(next, more ? qn : q);
       const int i0 = q * kWave;
-      const double vy = a.vy, vz = a.vz;
+      const double vy = SP == 1 || DIAG ? a.vy : 0.0, vz = SP == 1 || DIAG ? a.vz : 0.0;
       const uint64_t uid = a.uid;
-      double x = a.x, vx = a.vx, vp2 = (double)a.vp2;
+      double x = a.x, vx = a.vx, vp2 = SP == 0 ? (double)a.vp2 : 0.0;
       bool live = x == x;  // not absorbed earlier (tombstone)
       if (i0 + kWave > n) {  // the last slice: slots from n on hold nothing
         if (lane >= (int)(n - i0)) {
@@ -1299,14 +1444,14 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       // from cell coordinate xi = x/dx, then the leapfrog equations of
       // section 2.1.4, the kick being e dt/m per unit field (subtracted for
       // the electron's negative charge).
-      const double xi = x * inv_dx_v;
+      const double xi = x * inv_dx;
       int cell = (int)xi;
       cell = cell > ng - 2 ? ng - 2 : (cell < 0 ? 0 : cell);
       const double w_lo = (double)(cell + 1) - xi;  // weight of node `cell`
       const double w_hi = xi - (double)cell;        // weight of node `cell + 1`
       const double e_here = sE[cell] * w_lo + sE[cell + 1] * w_hi;
-      double vxn = SP == 0 ? vx - e_here * kick_v : vx + e_here * kick_v;
-      double xn = x + vxn * dt_v;
+      double vxn = SP == 0 ? vx - e_here * kick : vx + e_here * kick;
+      double xn = x + vxn * dt;
       // Step 6 pre-test.  A particle can collide only if its R is below the
       // bound of 1 - exp(-nu dt) over the tables (P* for null collisions), or
       // if it is faster than the range that bound covers; the upper word of R
@@ -1328,17 +1473,17 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
         }
         if (SP == 1) {
           if (xt) {
-            const double en = 0.5 * kArMass * (vbar * vbar + vy * vy + vz * vz) / kEvToJ;
+            const double en = div_by(0.5 * kArMass * (vbar * vbar + vy * vy + vz * vz), kEvToJ, 1.0 / kEvToJ);
             lds_add(&sW[cell], (long long)(w_lo * kDiagWS));
             lds_add(&sW[cell + 1], (long long)(w_hi * kDiagWS));
             lds_add(&sEn[cell], (long long)(w_lo * en * kDiagES));
             lds_add(&sEn[cell + 1], (long long)(w_hi * en * kDiagES));
           }
         } else if (fl & (kDiagMeanE | kDiagEepf | kDiagXT)) {
-          const double en = 0.5 * kEMass * (vbar * vbar + vy * vy + vz * vz) / kEvToJ;
+          const double en = div_by(0.5 * kEMass * (vbar * vbar + vy * vy + vz * vz), kEvToJ, 1.0 / kEvToJ);
           if (xt) {
             const double vmag = sqrt(vbar * vbar + vy * vy + vz * vz);
-            const double pdt = (n_gas * sig2[energy_bin(en, de_cs, nbins)]) * vmag * dt;
+            const double pdt = (n_gas * sig2[energy_bin(en, de_cs, inv_de_cs, nbins)]) * vmag * dt;
             lds_add(&sIz[cell], (long long)(w_lo * pdt * kDiagIZS));
             lds_add(&sIz[cell + 1], (long long)(w_hi * pdt * kDiagIZS));
           }
@@ -1349,7 +1494,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
             lds_add(&sEn[cell + 1], (long long)(w_hi * en * kDiagES));
           }
           if ((fl & kDiagEepf) && x >= x_lo && x <= x_hi) {
-            const double t = en / de_eepf;
+            const double t = div_by(en, de_eepf, C->inv_de_eepf);
             if (t < (double)n_eepf) atomicAdd(&sF[(int)t], 1u);
           }
         }
@@ -1364,7 +1509,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       // node of the next step's deposit now and which takes its slot from
       // the step's electron births below.
       bool abs_pow = live && xn < 0.0;
-      bool abs_gnd = live && xn > L_v;
+      bool abs_gnd = live && xn > L_gap;
       if (surf_on && (abs_pow || abs_gnd)) {
         double r_surf, r_unused;
         uniform2(seed, uid, st, tag(SP, 3, 0), r_surf, r_unused);
@@ -1396,7 +1541,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       // Step 7 for step s+1: deposit the new position
       if (in) {
         long long r;
-        const int p = deposit_split(xn, inv_dx_v, ng, r);
+        const int p = deposit_split(xn, inv_dx, ng, r);
         lds_add(&sH[p], 4294967296LL - r);
         lds_add(&sH[p + 1], r);
         cand = r_word <= r_lim || g2u > v2_cand;
@@ -1422,6 +1567,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
         if (lane == 0 && m_s0) gl_add(&Cw->ctr[SP == 0 ? kRefl : kSeePow], (long long)__popcll(m_s0));
         if (lane == 0 && m_s1) gl_add(&Cw->ctr[kSeeGnd], (long long)__popcll(m_s1));
         if (SP == 1 && (m_s0 | m_s1)) {
+          read_scatter_ptrs(P, C, 0, cur_o);
           const int64_t be = B.take(0, surf, lane, t_be, t_drop);
           if (surf) see_emit_at(C, P, uid, abs_pow ? 0 : 1, be, s);
         }
@@ -1463,7 +1609,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
     const unsigned long long h = sH[q];
     if (h) gl_add(&dst[q], (long long)h);
     if (pdiag) {
-      const int64_t off3 = (s % 3) * ng + q;
+      const int64_t off3 = (int64_t)I.s3 * ng + q;
       if (sJ[q]) gl_add(&(SP == 0 ? C->acc_je : C->acc_ji)[off3], (long long)sJ[q]);
       if (sW[q]) gl_add(&(SP == 0 ? C->acc_w : C->acc_wi)[off3], (long long)sW[q]);
       if (sEn[q]) gl_add(&(SP == 0 ? C->acc_e : C->acc_ei)[off3], (long long)sEn[q]);
@@ -1475,31 +1621,33 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
     if (sF[b]) gl_add(&hist[b], (long long)sF[b]);
   // this wave's segment, then the workgroup's overflow list
   finish(first);
-  if (lane == 0) {
-    sTot[w][kRecColl] = t_coll;
-    sTot[w][kRecIoniz] = t_ioniz;
-    sTot[w][kRecAbsPow] = t_pow;
-    sTot[w][kRecAbsGnd] = t_gnd;
-    sTot[w][kRecLive] = t_live;
-    sTot[w][kRecBornE] = t_be;
-    sTot[w][kRecBornI] = t_bi;
-    sTot[w][kRecDropped] = t_drop;
-  }
-  __syncthreads();
+  const int v[kRec] = {t_coll, t_ioniz, t_pow, t_gnd, t_live, t_be, t_bi, t_drop};
   SpTot T;
+  if constexpr (SMALL) {
+    if (lane == 0)
 #pragma unroll
-  for (int f = 0; f < kRec; ++f) T.v[f] = 0;
+      for (int f = 0; f < kRec; ++f) sTot[w][f] = v[f];
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < kRec; ++f) T.v[f] = 0;
 #pragma unroll 1
-  for (int u = 0; u < NB / kWave; ++u)
+    for (int u = 0; u < NB / kWave; ++u)
 #pragma unroll
-    for (int f = 0; f < kRec; ++f) T.v[f] += sTot[u][f];
-  __syncthreads();  // sTot, the segments and the histograms are free again
+      for (int f = 0; f < kRec; ++f) T.v[f] += sTot[u][f];
+    __syncthreads();  // sTot, the segments and the histograms are free again
+  } else {
+    // lane f has field f
+    T.field = 0;
+#pragma unroll
+    for (int f = 0; f < kRec; ++f) T.field = lane == f ? v[f] : T.field;
+  }
   return T;
 }
 
-// Slot count of species sp at the start of step s inside a window.
-__device__ __forceinline__ int64_t step_slots(const EDP_CONST CaseDev* __restrict__ C, int sp, int64_t s) {
-  const int r = (int)((s + 2) % 3);
+// Slot count of species sp at the start of a step inside a window (s3: the
+// step mod 3).
+__device__ __forceinline__ int64_t step_slots(const EDP_CONST CaseDev* __restrict__ C, int sp, int s3) {
+  const int r = s3 == 0 ? 2 : s3 - 1;
   const int64_t a = C->nbase[sp][r] + C->born[sp][r];
   return a < C->sp[sp].cap ? a : C->sp[sp].cap;
 }
@@ -1520,42 +1668,53 @@ k_particles(const BlockRole* __restrict__ R, int dstep, int pretest) {
   const EDP_CONST BlockRole* r = KC(R) + blockIdx.x;
   CaseDev* Cw = r->c;
   const int ng = r->ng, nsub = r->nsub, j = r->j;
+  const uint32_t f_lo = r->f_lo, f_hi = r->f_hi;
   const int64_t s = r->step0 + dstep;
-  if (SP == 1 && (s % nsub) != 0) return;  // ions move on ion steps only
+  const StepIndex I(s, nsub);
+  if (SP == 1 && I.sub != 0) return;  // ions move on ion steps only
   double* sE = psm;
   double* reg = psm + ng;
   const bool writer = SP == 0 && j == 0;
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
-  const int64_t n_e = step_slots(C, 0, s), n_i = step_slots(C, 1, s);
-  const int64_t n = SP == 0 ? n_e : n_i;
-  const uint64_t nch = (uint64_t)((n + kPartBlock - 1) / kPartBlock);
-  const int64_t c_lo = (int64_t)((nch * r->f_lo) >> 31);
-  const int64_t c_hi = (int64_t)((nch * r->f_hi) >> 31);
-  const int cur = C->cur[SP];
-  solve_field<MODE, kPartBlock>(Cw, r->cnt_e, r->cnt_i, r->volt, ng, nsub, s, sE, reg, writer);
-  if (writer && threadIdx.x == 0) {
-    for (int sp = 0; sp < 2; ++sp) {
-      Cw->nbase[sp][s % 3] = sp == 0 ? n_e : n_i;
-      Cw->born[sp][(s + 1) % 3] = 0;
-    }
-  }
-  if (c_lo >= c_hi) return;  // whole workgroup: nothing to do this step
+  const RingNodes<kPartBlock> N(r->cnt_e, r->cnt_i, r->volt, s, I.s3, I.k3, ng);
+  // the slot counts and the current buffer sets, with what the pass needs;
+  // every line of the case block is touched now, so that what is read later
+  // comes from the scalar cache (cold at a launch's start, and each first
+  // touch a wait of its own)
+  touch_case(C);
+  const int64_t n_e = step_slots(C, 0, I.s3), n_i = step_slots(C, 1, I.s3);
+  const int cur = C->cur[SP], cur_o = C->cur[1 - SP];
   Births<false> B;
-  B.base[0] = n_e;
-  B.base[1] = n_i;
   B.cap[0] = C->sp[0].cap;
   B.cap[1] = C->sp[1].cap;
+  const PassIn<SP> A(C);
+  const SolveIn SI(C);
+  const int64_t n = SP == 0 ? n_e : n_i;
+  const uint32_t nch = (uint32_t)((n + kPartBlock - 1) / kPartBlock);
+  const int64_t c_lo = (int64_t)(((uint64_t)nch * f_lo) >> 31);
+  const int64_t c_hi = (int64_t)(((uint64_t)nch * f_hi) >> 31);
+  if (c_lo >= c_hi && !writer) return;  // whole workgroup: nothing to do this step
+  auto solve = [&]() __attribute__((always_inline)) {
+    solve_field<MODE, kPartBlock>(Cw, ng, s, I, sE, reg, writer, N, SI);
+    if (writer && threadIdx.x == 0) {
+      for (int sp = 0; sp < 2; ++sp) {
+        Cw->nbase[sp][I.s3] = sp == 0 ? n_e : n_i;
+        Cw->born[sp][I.s3 == 2 ? 0 : I.s3 + 1] = 0;
+      }
+    }
+  };
+  B.base[0] = n_e;
+  B.base[1] = n_i;
   B.lds = nullptr;
-  B.glob[0] = &Cw->born[0][s % 3];
-  B.glob[1] = &Cw->born[1][s % 3];
-  const SpTot T = species_pass<SP, false, kPartBlock>(Cw, sE, reg, s, n, c_lo, c_hi, cur, C->cur[1 - SP], B, pretest);
-  if (threadIdx.x == 0) {
-    int64_t* sh = C->shard + ((int64_t)SP * kShards + j % kShards) * kRec;
-#pragma unroll
-    for (int f = 0; f < kRec; ++f)
-      if (T.v[f]) gl_add(&sh[f], T.v[f]);
-    if (T.v[kRecDropped]) Cw->error = 1;
-  }
+  B.glob[0] = &Cw->born[0][I.s3];
+  B.glob[1] = &Cw->born[1][I.s3];
+  const SpTot T = species_pass<SP, false, kPartBlock>(Cw, sE, reg, s, I, n, c_lo, c_hi, cur, cur_o, B, pretest, A, solve);
+  // every wave adds its own totals (spread over the shards): no wave waits
+  // for the others at the end
+  const int t = (int)threadIdx.x, f = t % kWave;
+  int64_t* sh = C->shard + ((int64_t)SP * kShards + (j * (kPartBlock / kWave) + t / kWave) % kShards) * kRec;
+  if (T.field) gl_add(&sh[f], T.field);  // lanes beyond the fields have 0
+  if (f == kRecDropped && T.field) Cw->error = 1;
 }
 
 // First kernel of a lockstep window: every role's step0 from its case, and
@@ -1749,7 +1908,8 @@ __global__ void __launch_bounds__(kBlock) k_small(const BlockRole* __restrict__ 
     const int64_t s = sState[0];
     int64_t n_e = sState[1], n_i = sState[2];
     int cur_e = (int)sState[3], cur_i = (int)sState[4];
-    const bool ion_step = (s % nsub) == 0;
+    const StepIndex I(s, nsub);
+    const bool ion_step = I.sub == 0;
     // compaction + cell sort on the lockstep path's schedule
     if (s % sort_every == 0) {
       n_e = small_sort(Cw, 0, cur_e, n_e, (unsigned int*)ssm2);
@@ -1761,7 +1921,10 @@ __global__ void __launch_bounds__(kBlock) k_small(const BlockRole* __restrict__ 
     }
     if (threadIdx.x < 2) sBirth[threadIdx.x] = 0;
     // steps 1-2
-    solve_field<MODE, kBlock>(Cw, C->cnt_e, C->cnt_i, C->volt, ng, nsub, s, sE, reg, true);
+    auto solve = [&]() __attribute__((always_inline)) {
+      const RingNodes<kBlock> N(C->cnt_e, C->cnt_i, C->volt, s, I.s3, I.k3, ng);
+      solve_field<MODE, kBlock>(Cw, ng, s, I, sE, reg, true, N, SolveIn(C));
+    };
     Births<true> B;
     B.base[0] = n_e;
     B.base[1] = n_i;
@@ -1770,9 +1933,9 @@ __global__ void __launch_bounds__(kBlock) k_small(const BlockRole* __restrict__ 
     B.lds = sBirth;
     B.glob[0] = B.glob[1] = nullptr;
     const int64_t nch_e = (n_e + kChunk - 1) / kChunk, nch_i = (n_i + kChunk - 1) / kChunk;
-    const SpTot te = species_pass<0, true, kBlock>(Cw, sE, reg, s, n_e, 0, nch_e, cur_e, cur_i, B, pretest);
+    const SpTot te = species_pass<0, true, kBlock>(Cw, sE, reg, s, I, n_e, 0, nch_e, cur_e, cur_i, B, pretest, PassIn<0>(C), solve);
     SpTot ti{};
-    if (ion_step) ti = species_pass<1, true, kBlock>(Cw, sE, reg, s, n_i, 0, nch_i, cur_i, cur_e, B, pretest);
+    if (ion_step) ti = species_pass<1, true, kBlock>(Cw, sE, reg, s, I, n_i, 0, nch_i, cur_i, cur_e, B, pretest, PassIn<1>(C), [] { __syncthreads(); });
     if (threadIdx.x == 0) {
       int64_t* ctr = Cw->ctr;
       ctr[kCollE] += te.v[kRecColl];
@@ -1891,7 +2054,7 @@ __global__ void __launch_bounds__(256) k_sort_hist(const BlockRole* __restrict__
   __syncthreads();
   const int cur = C->cur[sp];
   const EDP_GLOBAL double* __restrict__ X = G(C->sp[sp].x[cur]);
-  const int64_t n = step_slots(KC(C), sp, s);
+  const int64_t n = step_slots(KC(C), sp, (int)(s % 3));
   const int64_t nb = r->n, per = (n + nb - 1) / nb;
   const int64_t lo = (int64_t)r->j * per, hi = lo + per < n ? lo + per : n;
   const double inv_dx = C->inv_dx;
@@ -1951,7 +2114,7 @@ __global__ void __launch_bounds__(256) k_sort_scatter(const BlockRole* __restric
   const int cur = C->cur[sp], nxt = cur ^ 1;
   const SpeciesDev& S = C->sp[sp];
   const EDP_GLOBAL double* __restrict__ X = G(S.x[cur]);
-  const int64_t n = step_slots(KC(C), sp, s);
+  const int64_t n = step_slots(KC(C), sp, (int)(s % 3));
   const int64_t nb = r->n, per = (n + nb - 1) / nb;
   const int64_t lo = (int64_t)r->j * per, hi = lo + per < n ? lo + per : n;
   const double inv_dx = C->inv_dx;

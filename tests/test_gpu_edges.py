@@ -1,0 +1,59 @@
+"""The particle kernels at the edges of their work split, against the CPU
+oracle: grids below, at and beyond one node per thread, one row group per
+thread and the staged ring registers; particle counts around a wave's slice of
+64 and a workgroup's chunk of 256; steps on both sides of the 32-bit step
+arithmetic.  Bounds as in the one-step parity tests: with the Thomas solve the
+fields are the oracle's bit for bit, with the flux solve E is within 1e-14 of
+an extended-precision solution; states within 1e-12 after one step."""
+import numpy as np
+import pytest
+
+from gpu_common import compare_states, gpu_context, make_pair, poisson_reference, say, set_both
+from paper_2103_09642_amd.workloads import base_case, random_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx(xs_default):
+    c = gpu_context()
+    c.set_xsec(xs_default)
+    return c
+
+
+@pytest.mark.parametrize("small", [0, 1 << 20], ids=["lockstep", "one-workgroup"])
+@pytest.mark.parametrize("ng,n,step", [(2, 65, 0), (3, 64, 5), (5, 63, 7), (257, 1, 5), (258, 129, 10),
+                                       (1025, 257, 2**31 - 3), (1027, 4097, 2**31 + 2), (2048, 1000, 2**33 + 3)])
+def test_edges_match_oracle(ctx, xs_default, orc, ng, n, step, small):
+    from paper_2103_09642_amd import edupic
+    say(f"test_edges_match_oracle ng={ng} n={n} step={step} small={small}")
+    c = base_case(n_init_e=0, n_init_i=0, pressure_pa=50.0, weight=2e5, n_grid=ng, ion_subcycle=5, cap_e=20_000,
+                  cap_i=20_000, flags=["allow_unstable"])
+    st = random_state(n, n, c["gap_m"], seed=ng + n, te_ev=4.0, hot_frac=0.3, hot_ev=90.0, ion_energy_ev=30.0)
+    try:
+        ctx.set_option(edupic.OPT_SMALL_MAX, small)
+        for poisson in (edupic.POISSON_THOMAS, edupic.POISSON_FLUX):
+            ctx.set_option(edupic.OPT_POISSON, poisson)
+            g, o = make_pair(ctx, c, xs_default, orc)
+            set_both(g, o, st, step)
+            g.advance_steps(1)
+            o.step(1)
+            rg, pg, eg = g.fields()
+            ro, po, eo = o.fields()
+            assert np.array_equal(rg, ro), "rho"
+            if poisson == edupic.POISSON_THOMAS:
+                assert np.array_equal(pg, po) and np.array_equal(eg, eo), "phi, E"
+                cg, co = g.counts(), o.counts()
+                for k in ("abs_e_pow", "abs_e_gnd", "abs_i_pow", "abs_i_gnd", "coll_e", "coll_i", "ioniz"):
+                    assert cg[k] == co[k], k
+                for sp in (0, 1):
+                    compare_states(g.get_state(sp), o.get_state(sp), 1e-12, f"sp{sp}")
+                for a, b in zip(g.deposit(), o.deposit()):
+                    assert int(a.sum()) == int(b.sum())
+            else:
+                eref = poisson_reference(rg, c["gap_m"] / (ng - 1), float(pg[0]))
+                assert float(np.max(np.abs(eg - eref))) <= 1e-14 * float(np.abs(eref).max()), "E"
+            g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_SMALL_MAX, 0)
+        ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_FLUX)

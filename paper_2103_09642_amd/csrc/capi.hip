@@ -24,13 +24,13 @@
 #include "impl.hpp"
 
 namespace edp {
-hipError_t launch_particles(const BlockRole* roles, int sp, int blocks, size_t lds, int mode, int dstep, int pretest,
+hipError_t launch_particles(const BlockRole* roles, int sp, int blocks, int nb, size_t lds, int mode, int dstep, int pretest,
                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_window_begin(BlockRole* roles, int nroles, const BlockRole* cases, int ncase, hipStream_t st);
 hipError_t launch_window_end(const BlockRole* cases, int ncase, int steps, hipStream_t st);
 size_t particle_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed, int sp);
-size_t particle_static_lds(int sp);
-int particle_occupancy(int sp, size_t lds);
+size_t particle_static_lds(int sp, int nb);
+int particle_occupancy(int sp, int nb, size_t lds);
 hipError_t launch_seed(CaseDev* d, int sp, int64_t n, double sigma, hipStream_t st);
 hipError_t launch_deposit(CaseDev* d, int sp, int64_t* dst1, int64_t* dst2, int ng, int blocks,
                           hipStream_t st);
@@ -113,6 +113,7 @@ struct Batch {
   size_t nroles = 0;
   int max_ng = 2;
   size_t lds[2] = {0, 0};
+  int nb[2] = {256, 256};  // threads of a particle workgroup per species
   // graph of one window of g_steps steps, valid for these cases at these
   // step phases and sort grids
   hipGraphExec_t gexec = nullptr;
@@ -241,7 +242,7 @@ int validate(const edp_case_desc* c) {
   const uint32_t meas = EDP_DIAG_EEPF | EDP_DIAG_CURRENT | EDP_DIAG_MEANE | EDP_DIAG_XT | EDP_DIAG_IFED;
   if ((c->flags & meas) && c->n_grid > 1024) return fail(EDP_EINVAL, "measurements support n_grid <= 1024");
   for (int sp = 0; sp < 2; ++sp)
-    if (particle_lds_bytes(c->n_grid, c->flags, c->n_eepf, c->n_ifed, sp) + particle_static_lds(sp) > 65536)
+    if (particle_lds_bytes(c->n_grid, c->flags, c->n_eepf, c->n_ifed, sp) + particle_static_lds(sp, 256) > 65536)
       return fail(EDP_EINVAL, "measurement histograms and grid exceed the workgroup's LDS");
   return EDP_OK;
 }
@@ -438,7 +439,7 @@ int blocks_for(const edp_ctx* ctx, int64_t n) {
 }
 
 // Expected chunks of a species of a case (10% headroom over the estimate).
-int64_t est_chunks(const Case* c, int sp) { return (c->est[sp] + c->est[sp] / 10 + kChunk) / kChunk; }
+int64_t est_chunks(const Case* c, int sp, int chunk = kChunk) { return (c->est[sp] + c->est[sp] / 10 + chunk) / chunk; }
 
 // Expected work of a case's electron share of a particle launch: its chunks
 // weighted by the collision work per particle step.  Timestamps of every
@@ -644,6 +645,25 @@ void particle_roles(std::vector<BlockRole>& roles, const std::vector<Case*>& cs,
 // Workgroups of a case's sort histogram and scatter.
 int sort_blocks(const edp_ctx* ctx, const Case* c, int sp) { return std::max(1, blocks_for(ctx, c->est[sp]) / 4); }
 
+// Threads of a species' particle workgroups in a launch of the cases `cs`
+// (most nodes max_ng, `lds` dynamic bytes).  Every workgroup solves its
+// case's field, takes in the whole grid and gives the whole grid's deposit
+// back; workgroups of 512 do that half as often.  They pay where the chip is
+// full anyway -- every resident workgroup of 256 has its chunk -- and on
+// large grids; a launch that leaves CUs or wave slots idle is better spread
+// over twice as many workgroups.  Measured, us a step with 256 and 512: one
+// case of 777 nodes, 6e4 electrons 16.0 16.9, 1.8e5 20.3 20.9, 2.4e5 22.7
+// 21.5, 6e5 27.4 24.7; of 400 nodes, 1.8e5 19.8 20.1, 3e5 23.5 21.7; of 2048
+// nodes, 6e4 15.5 14.7, 3e5 21.6 20.1.
+int particle_block(const edp_ctx* ctx, const std::vector<Case*>& cs, int sp, int max_ng, size_t lds) {
+  // an explicit single workgroup per CU is one of 256 threads
+  if (ctx->part_wg_per_cu == 1 || lds + particle_static_lds(sp, 512) > 65536) return 256;
+  int64_t chunks = 0;
+  for (const Case* c : cs) chunks += est_chunks(c, sp);
+  const int64_t resident = (int64_t)ctx->num_cu * particle_occupancy(sp, 256, lds);
+  return chunks >= resident || max_ng > 1024 ? 512 : 256;
+}
+
 // Build the batch table for `cs` (in this order) and upload it.  Particle
 // workgroups: the chip's resident workgroups (at most part_wg_per_cu per CU
 // when that option is set) shared out in proportion to each case's expected
@@ -663,10 +683,13 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
       lds[sp] = std::max(lds[sp], particle_lds_bytes(c->desc.n_grid, c->desc.flags, c->desc.n_eepf, c->desc.n_ifed, sp));
     max_ng = std::max(max_ng, (int)c->desc.n_grid);
   }
+  int nb[2];
+  for (int sp = 0; sp < 2; ++sp) nb[sp] = particle_block(ctx, cs, sp, max_ng, lds[sp]);
   std::vector<int> want[2];
   for (int sp = 0; sp < 2; ++sp) {
-    const int occ = particle_occupancy(sp, lds[sp]);
-    const int per_cu = ctx->part_wg_per_cu > 0 ? std::min(ctx->part_wg_per_cu, occ) : occ;
+    const int occ = particle_occupancy(sp, nb[sp], lds[sp]);
+    // the option counts workgroups of 256 threads
+    const int per_cu = ctx->part_wg_per_cu > 0 ? std::min(std::max(1, ctx->part_wg_per_cu * 256 / nb[sp]), occ) : occ;
     const int64_t slots = (int64_t)ctx->num_cu * per_cu;
     double total = 0.0;
     for (const Case* c : cs) total += est_cost(c, sp);
@@ -679,7 +702,7 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
     std::vector<double> frac(nc, 0.0);
     int64_t used = 0;
     for (size_t k = 0; k < nc; ++k) {
-      const int64_t ch = est_chunks(cs[k], sp);
+      const int64_t ch = est_chunks(cs[k], sp, nb[sp]);
       const double ideal = est_cost(cs[k], sp) * (double)slots / std::max(1e-9, total);
       const int64_t w = std::max<int64_t>(1, std::min<int64_t>({(int64_t)ideal, ch, (int64_t)kMaxPartWG}));
       want[sp][k] = (int)w;
@@ -691,7 +714,7 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return frac[a] > frac[b]; });
     for (size_t k : order) {
       if (used >= slots) break;
-      if (frac[k] <= 0.0 || want[sp][k] >= std::min<int64_t>(kMaxPartWG, est_chunks(cs[k], sp))) continue;
+      if (frac[k] <= 0.0 || want[sp][k] >= std::min<int64_t>(kMaxPartWG, est_chunks(cs[k], sp, nb[sp]))) continue;
       ++want[sp][k];
       ++used;
     }
@@ -712,7 +735,7 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
     }
     for (int sp = 0; sp < 2 && same; ++sp) same = near(want_sort[sp][k], B.h.sort_off[sp][k + 1] - B.h.sort_off[sp][k]);
   }
-  for (int sp = 0; sp < 2 && same; ++sp) same = 16 * moved[sp] <= B.parts[sp];
+  for (int sp = 0; sp < 2 && same; ++sp) same = nb[sp] == B.nb[sp] && 16 * moved[sp] <= B.parts[sp];
   if (same) return EDP_OK;
   HIPCHK(hipStreamSynchronize(G.stream));
   drop_graph(G);
@@ -721,8 +744,10 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   B.h = BatchTable{};
   B.h.ncase = (int32_t)nc;
   B.max_ng = max_ng;
-  B.lds[0] = lds[0];
-  B.lds[1] = lds[1];
+  for (int sp = 0; sp < 2; ++sp) {
+    B.lds[sp] = lds[sp];
+    B.nb[sp] = nb[sp];
+  }
   for (size_t k = 0; k < nc; ++k) {
     for (int sp = 0; sp < 2; ++sp) B.h.part_off[sp][k + 1] = B.h.part_off[sp][k] + want[sp][k];
     for (int sp = 0; sp < 2; ++sp) B.h.sort_off[sp][k + 1] = B.h.sort_off[sp][k] + want_sort[sp][k];
@@ -794,12 +819,12 @@ int enqueue_batch_step(edp_ctx* ctx, Group& G, const std::vector<int64_t>& s, in
     const int r = take_event_pair(ctx, e0, e1);
     if (r) return r;
   }
-  HIPCHK(launch_particles(G.roles_d + B.role_off[0], 0, B.parts[0], B.lds[0], ctx->poisson, dj, ctx->pretest, st, e0,
-                          e1));
+  HIPCHK(launch_particles(G.roles_d + B.role_off[0], 0, B.parts[0], B.nb[0], B.lds[0], ctx->poisson, dj, ctx->pretest,
+                          st, e0, e1));
   if (e0) ctx->ev_pairs.emplace_back(e0, e1);
   if (any_ion)
-    HIPCHK(launch_particles(G.roles_d + B.role_off[1], 1, B.parts[1], B.lds[1], ctx->poisson, dj, ctx->pretest, st,
-                            nullptr, nullptr));
+    HIPCHK(launch_particles(G.roles_d + B.role_off[1], 1, B.parts[1], B.nb[1], B.lds[1], ctx->poisson, dj, ctx->pretest,
+                            st, nullptr, nullptr));
   return EDP_OK;
 }
 

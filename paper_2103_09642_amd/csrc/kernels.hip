@@ -461,7 +461,11 @@ template <int MODE, int NB>
 __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int ng, const int64_t s,
                                             const StepIndex& I, double* sE, double* sF, const bool writer,
                                             const RingNodes<NB>& N, const SolveIn& S) {
-  __shared__ double sWave[2][NB / kWave];
+  // the flux solve is always worked by the first 256 threads (its sums then
+  // have the same order, and the same bits, whatever the workgroup)
+  constexpr int NS = 256;
+  static_assert(NB >= NS && NB % kWave == 0, "threads of the field solve");
+  __shared__ double sWave[2][NS / kWave];
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   const bool ion_step = I.sub == 0;
   const int t = (int)threadIdx.x;
@@ -568,94 +572,100 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int 
     // E_p = (F_{p-1} + F_p)/(2 dx) inside, the boundary forms (Gauss's law
     // over the half cell) at the electrodes.
     const int m = ng - 2;
-    const int R = (m + NB - 1) / NB;
+    const int R = (m + NS - 1) / NS;
     const int q0 = t * R;
+    const bool solver = NB == NS || wv < NS / kWave;
     // the owner of the last row also takes node N_g-1 (thread 0 when there
     // are no interior rows)
     const bool last = q0 < m ? q0 + R >= m : (t == 0 && m == 0);
-    const double rho0 = t == 0 ? dens(0, ne, ni) : 0.0;
-    const double rhoN = last ? dens(ng - 1, ne, ni) : 0.0;
-    double acc = 0.0, wsum = 0.0, weight = (double)(m - q0);
     // kGroup rows at a time, so that their LDS reads are in flight together
     constexpr int kGroup = 4;
+    double inc = 0.0, rho0 = 0.0, rhoN = 0.0, acc = 0.0;
+    if (solver) {
+      rho0 = t == 0 ? dens(0, ne, ni) : 0.0;
+      rhoN = last ? dens(ng - 1, ne, ni) : 0.0;
+      double wsum = 0.0, weight = (double)(m - q0);
 #pragma unroll 1
-    for (int r0 = 0; r0 < R; r0 += kGroup) {
-      int64_t ce[kGroup], ci[kGroup];
+      for (int r0 = 0; r0 < R; r0 += kGroup) {
+        int64_t ce[kGroup], ci[kGroup];
 #pragma unroll
-      for (int r = 0; r < kGroup; ++r) {
-        const int p = q0 + 1 + r0 + r;
-        const int pc = p < ng ? p : ng - 1;
-        ce[r] = nE[pc];
-        ci[r] = nI[pc];
-      }
-#pragma unroll
-      for (int r = 0; r < kGroup; ++r) {
-        if (r0 + r < R && q0 + r0 + r < m) {
-          const double d = kECharge * ((double)ci[r] * scale - (double)ce[r] * scale) * kp;
-          acc += d;
-          wsum += d * weight;
-          sE[q0 + 1 + r0 + r] = acc;  // prefix within the thread
+        for (int r = 0; r < kGroup; ++r) {
+          const int p = q0 + 1 + r0 + r;
+          const int pc = p < ng ? p : ng - 1;
+          ce[r] = nE[pc];
+          ci[r] = nI[pc];
         }
-        weight -= 1.0;
-      }
-    }
-    // the workgroup pass: inclusive scan of acc and sum of wsum per wave
-    double inc = acc;
-    const int lane4 = lane * 4;
-    auto permute = [&](int from4, double v) {
-      const uint64_t u = (uint64_t)__double_as_longlong(v);
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(uint32_t)u);
-      const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(u >> 32));
-      return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
-    };
 #pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      const int off = 1 << u, xo = kWave / 2 >> u;
-      const double y = permute(lane4 + 4 * (kWave - off), inc);  // from lane - off
-      const double z = permute(lane4 ^ (4 * xo), wsum);
-      inc = lane >= off ? inc + y : inc;
-      wsum += z;
-    }
-    if (lane == kWave - 1) {
-      sWave[0][wv] = inc;
-      sWave[1][wv] = wsum;
+        for (int r = 0; r < kGroup; ++r) {
+          if (r0 + r < R && q0 + r0 + r < m) {
+            const double d = kECharge * ((double)ci[r] * scale - (double)ce[r] * scale) * kp;
+            acc += d;
+            wsum += d * weight;
+            sE[q0 + 1 + r0 + r] = acc;  // prefix within the thread
+          }
+          weight -= 1.0;
+        }
+      }
+      // the workgroup pass: inclusive scan of acc and sum of wsum per wave
+      inc = acc;
+      const int lane4 = lane * 4;
+      auto permute = [&](int from4, double v) {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(uint32_t)u);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from4, (int)(u >> 32));
+        return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+      };
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const int off = 1 << u, xo = kWave / 2 >> u;
+        const double y = permute(lane4 + 4 * (kWave - off), inc);  // from lane - off
+        const double z = permute(lane4 ^ (4 * xo), wsum);
+        inc = lane >= off ? inc + y : inc;
+        wsum += z;
+      }
+      if (lane == kWave - 1) {
+        sWave[0][wv] = inc;
+        sWave[1][wv] = wsum;
+      }
     }
     __syncthreads();
-    double before = inc - acc, sum_s = 0.0;
-#pragma unroll
-    for (int u = 0; u < NB / kWave; ++u) {
-      if (u < wv) before += sWave[0][u];
-      sum_s += sWave[1][u];
-    }
-    const double F0 = div_by(V - sum_s, (double)(ng - 1), S.inv_cells);
-    double f_prev = F0 + before;  // F_{q0}: F0 plus the rows before this thread's
-#pragma unroll 1
-    for (int r0 = 0; r0 < R; r0 += kGroup) {
-      double v[kGroup];
-#pragma unroll
-      for (int r = 0; r < kGroup; ++r) {
-        const int p = q0 + 1 + r0 + r;
-        v[r] = sE[p < ng ? p : ng - 1];
-      }
-#pragma unroll
-      for (int r = 0; r < kGroup; ++r)
-        if (r0 + r < R && q0 + r0 + r < m) {
-          const int p = q0 + 1 + r0 + r;
-          const double f = F0 + (before + v[r]);  // F_{q+1} = F_p
-          sE[p] = div_by(f_prev + f, 2.0 * dx, S.inv_2dx);
-          if (writer) W.flux(p, f);
-          f_prev = f;
-        }
-    }
-    if (t == 0) {
-      sE[0] = div_by(F0, dx, S.inv_dx) - div_by(rho0 * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
-      if (writer) W.flux(0, F0);
-    }
-    if (last) {
-      sE[ng - 1] = div_by(f_prev, dx, S.inv_dx) + div_by(rhoN * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
-      if (writer) W.flux(ng - 1, V);
-    }
     for (int p = t; p < ng; p += NB) sF[p] = 0.0;
+    if (solver) {
+      double before = inc - acc, sum_s = 0.0;
+#pragma unroll
+      for (int u = 0; u < NS / kWave; ++u) {
+        if (u < wv) before += sWave[0][u];
+        sum_s += sWave[1][u];
+      }
+      const double F0 = div_by(V - sum_s, (double)(ng - 1), S.inv_cells);
+      double f_prev = F0 + before;  // F_{q0}: F0 plus the rows before this thread's
+#pragma unroll 1
+      for (int r0 = 0; r0 < R; r0 += kGroup) {
+        double v[kGroup];
+#pragma unroll
+        for (int r = 0; r < kGroup; ++r) {
+          const int p = q0 + 1 + r0 + r;
+          v[r] = sE[p < ng ? p : ng - 1];
+        }
+#pragma unroll
+        for (int r = 0; r < kGroup; ++r)
+          if (r0 + r < R && q0 + r0 + r < m) {
+            const int p = q0 + 1 + r0 + r;
+            const double f = F0 + (before + v[r]);  // F_{q+1} = F_p
+            sE[p] = div_by(f_prev + f, 2.0 * dx, S.inv_2dx);
+            if (writer) W.flux(p, f);
+            f_prev = f;
+          }
+      }
+      if (t == 0) {
+        sE[0] = div_by(F0, dx, S.inv_dx) - div_by(rho0 * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
+        if (writer) W.flux(0, F0);
+      }
+      if (last) {
+        sE[ng - 1] = div_by(f_prev, dx, S.inv_dx) + div_by(rhoN * dx, 2.0 * kEps0, 1.0 / (2.0 * kEps0));
+        if (writer) W.flux(ng - 1, V);
+      }
+    }
   }
   if (writer && t == 0) {
     if (W.xt) {
@@ -1678,9 +1688,10 @@ __device__ __forceinline__ int64_t step_slots(const EDP_CONST CaseDev* __restric
 // LDS, then takes its chunk range.  The electron launch's workgroup 0 of
 // each case is the writer of the step (field outputs, ring clearing,
 // measurement sums) and publishes the step's slot counts.  Each workgroup
-// adds its totals to its shard of the case's counters.
-template <int SP, int MODE>
-__global__ void __launch_bounds__(kPartBlock) __attribute__((amdgpu_waves_per_eu(4)))
+// adds its totals to its shard of the case's counters.  NB threads: see
+// particle_block in the host code.
+template <int SP, int MODE, int NB>
+__global__ void __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(4)))
 k_particles(const BlockRole* __restrict__ R, int dstep, int pretest) {
   extern __shared__ double psm[];
   const EDP_CONST BlockRole* r = KC(R) + blockIdx.x;
@@ -1694,7 +1705,7 @@ k_particles(const BlockRole* __restrict__ R, int dstep, int pretest) {
   double* reg = psm + ng;
   const bool writer = SP == 0 && j == 0;
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
-  const RingNodes<kPartBlock> N(r->cnt_e, r->cnt_i, r->volt, s, I.s3, I.k3, ng);
+  const RingNodes<NB> N(r->cnt_e, r->cnt_i, r->volt, s, I.s3, I.k3, ng);
   // the slot counts and the current buffer sets, with what the pass needs;
   // every line of the case block is touched now, so that what is read later
   // comes from the scalar cache (cold at a launch's start, and each first
@@ -1708,12 +1719,12 @@ k_particles(const BlockRole* __restrict__ R, int dstep, int pretest) {
   const PassIn<SP> A(C);
   const SolveIn SI(C);
   const int64_t n = SP == 0 ? n_e : n_i;
-  const uint32_t nch = (uint32_t)((n + kPartBlock - 1) / kPartBlock);
+  const uint32_t nch = (uint32_t)((n + NB - 1) / NB);
   const int64_t c_lo = (int64_t)(((uint64_t)nch * f_lo) >> 31);
   const int64_t c_hi = (int64_t)(((uint64_t)nch * f_hi) >> 31);
   if (c_lo >= c_hi && !writer) return;  // whole workgroup: nothing to do this step
   auto solve = [&]() __attribute__((always_inline)) {
-    solve_field<MODE, kPartBlock>(Cw, ng, s, I, sE, reg, writer, N, SI);
+    solve_field<MODE, NB>(Cw, ng, s, I, sE, reg, writer, N, SI);
     if (writer && threadIdx.x == 0) {
       for (int sp = 0; sp < 2; ++sp) {
         Cw->nbase[sp][I.s3] = sp == 0 ? n_e : n_i;
@@ -1726,11 +1737,11 @@ k_particles(const BlockRole* __restrict__ R, int dstep, int pretest) {
   B.lds = nullptr;
   B.glob[0] = &Cw->born[0][I.s3];
   B.glob[1] = &Cw->born[1][I.s3];
-  const SpTot T = species_pass<SP, false, kPartBlock>(Cw, sE, reg, s, I, n, c_lo, c_hi, cur, cur_o, B, pretest, A, solve);
+  const SpTot T = species_pass<SP, false, NB>(Cw, sE, reg, s, I, n, c_lo, c_hi, cur, cur_o, B, pretest, A, solve);
   // every wave adds its own totals (spread over the shards): no wave waits
   // for the others at the end
   const int t = (int)threadIdx.x, f = t % kWave;
-  int64_t* sh = C->shard + ((int64_t)SP * kShards + (j * (kPartBlock / kWave) + t / kWave) % kShards) * kRec;
+  int64_t* sh = C->shard + ((int64_t)SP * kShards + (j * (NB / kWave) + t / kWave) % kShards) * kRec;
   if (T.field) gl_add(&sh[f], T.field);  // lanes beyond the fields have 0
   if (f == kRecDropped && T.field) Cw->error = 1;
 }
@@ -2236,11 +2247,11 @@ __global__ void k_zero(int64_t* __restrict__ p, int64_t n) {
 // Host-side launchers (same translation unit as the kernels).
 // ---------------------------------------------------------------------------
 // Static LDS of a species' particle kernel: the candidate segments with
-// their payload, plus a bound on the counters, the totals, a round's
-// colliders and the field scan's scratch.
-size_t particle_static_lds(int sp) {
-  const size_t waves = kPartBlock / kWave;
-  return (sp == 0 ? waves * kSegE * (4 + 8 + 8) : waves * kSegI * 4) + kMaxPb * 8 + 2048;
+// their payload and the ionizing lanes, the pre-test's bound, plus a bound on
+// the counters and the field scan's scratch.
+size_t particle_static_lds(int sp, int nb) {
+  const size_t waves = (size_t)nb / kWave;
+  return (sp == 0 ? waves * (kSegE * (4 + 8 + 8) + kWave * 4) : waves * kSegI * 4) + kMaxPb * 4 + 1024;
 }
 
 size_t particle_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed, int sp) {
@@ -2255,27 +2266,35 @@ size_t particle_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed, int sp
 }
 
 // One species of a window step of a batch: `blocks` workgroups with their
-// roles; `lds` = the largest per-case need; mode 1: the Thomas solve.  With
+// roles and nb threads each; `lds` = the largest per-case need; mode 1: the Thomas solve.  With
 // ev0/ev1 the launch records its own start and end (the dispatch's
 // timestamps, not those of separate event packets around it).
-template <int SP, int MODE>
+template <int SP, int MODE, int NB>
 void launch_particles_t(const BlockRole* roles, int blocks, size_t lds, int dstep, int pretest, hipStream_t st, hipEvent_t ev0,
                         hipEvent_t ev1) {
   if (ev0)
-    hipExtLaunchKernelGGL((k_particles<SP, MODE>), dim3(blocks), dim3(kPartBlock), lds, st, ev0, ev1, 0, roles, dstep,
-                          pretest);
+    hipExtLaunchKernelGGL((k_particles<SP, MODE, NB>), dim3(blocks), dim3(NB), lds, st, ev0, ev1, 0, roles, dstep, pretest);
   else
-    hipLaunchKernelGGL((k_particles<SP, MODE>), dim3(blocks), dim3(kPartBlock), lds, st, roles, dstep, pretest);
+    hipLaunchKernelGGL((k_particles<SP, MODE, NB>), dim3(blocks), dim3(NB), lds, st, roles, dstep, pretest);
 }
 
-hipError_t launch_particles(const BlockRole* roles, int sp, int blocks, size_t lds, int mode, int dstep, int pretest,
-                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+template <int NB>
+void launch_particles_nb(const BlockRole* roles, int sp, int blocks, size_t lds, int mode, int dstep, int pretest,
+                         hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   switch (sp * 2 + (mode == 1)) {
-    case 0: launch_particles_t<0, 0>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
-    case 1: launch_particles_t<0, 1>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
-    case 2: launch_particles_t<1, 0>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
-    default: launch_particles_t<1, 1>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
+    case 0: launch_particles_t<0, 0, NB>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
+    case 1: launch_particles_t<0, 1, NB>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
+    case 2: launch_particles_t<1, 0, NB>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
+    default: launch_particles_t<1, 1, NB>(roles, blocks, lds, dstep, pretest, st, ev0, ev1); break;
   }
+}
+
+hipError_t launch_particles(const BlockRole* roles, int sp, int blocks, int nb, size_t lds, int mode, int dstep,
+                            int pretest, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (nb == 512)
+    launch_particles_nb<512>(roles, sp, blocks, lds, mode, dstep, pretest, st, ev0, ev1);
+  else
+    launch_particles_nb<256>(roles, sp, blocks, lds, mode, dstep, pretest, st, ev0, ev1);
   return hipGetLastError();
 }
 
@@ -2293,13 +2312,17 @@ hipError_t launch_window_end(const BlockRole* cases, int ncase, int steps, hipSt
   return hipGetLastError();
 }
 
-// Resident workgroups per CU of a species' particle kernel with `lds` bytes
+// Resident workgroups (of nb threads) per CU of a species' particle kernel with `lds` bytes
 // of dynamic LDS.
-int particle_occupancy(int sp, size_t lds) {
-  int nb = 0;
-  const hipError_t e = sp == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_particles<0, 0>, kPartBlock, lds)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_particles<1, 0>, kPartBlock, lds);
-  return e == hipSuccess && nb > 0 ? nb : 1;
+template <int SP>
+int particle_occupancy_t(int nb, size_t lds) {
+  int n = 0;
+  const hipError_t e = nb == 512 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_particles<SP, 0, 512>, nb, lds)
+                                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_particles<SP, 0, 256>, nb, lds);
+  return e == hipSuccess && n > 0 ? n : 1;
+}
+int particle_occupancy(int sp, int nb, size_t lds) {
+  return sp == 0 ? particle_occupancy_t<0>(nb, lds) : particle_occupancy_t<1>(nb, lds);
 }
 
 // Dynamic LDS of the small-case kernel for a case: E, then the largest of

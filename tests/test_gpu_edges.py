@@ -1,7 +1,8 @@
 """The particle kernels at the edges of their work split, against the CPU
 oracle: grids below, at and beyond one node per thread, one row group per
 thread and the staged ring registers; particle counts around a wave's slice of
-64 and a workgroup's chunk of 256; steps on both sides of the 32-bit step
+64 and a workgroup's chunk of 256; enough particles (or nodes) for workgroups
+of 512; steps on both sides of the 32-bit step
 arithmetic.  Bounds as in the one-step parity tests: with the Thomas solve the
 fields are the oracle's bit for bit, with the flux solve E is within 1e-14 of
 an extended-precision solution; states within 1e-12 after one step."""
@@ -23,12 +24,13 @@ def ctx(xs_default):
 
 @pytest.mark.parametrize("small", [0, 1 << 20], ids=["lockstep", "one-workgroup"])
 @pytest.mark.parametrize("ng,n,step", [(2, 65, 0), (3, 64, 5), (5, 63, 7), (257, 1, 5), (258, 129, 10),
-                                       (1025, 257, 2**31 - 3), (1027, 4097, 2**31 + 2), (2048, 1000, 2**33 + 3)])
+                                       (1025, 257, 2**31 - 3), (1027, 4097, 2**31 + 2), (2048, 1000, 2**33 + 3),
+                                       (401, 300_001, 5)])
 def test_edges_match_oracle(ctx, xs_default, orc, ng, n, step, small):
     from paper_2103_09642_amd import edupic
     say(f"test_edges_match_oracle ng={ng} n={n} step={step} small={small}")
-    c = base_case(n_init_e=0, n_init_i=0, pressure_pa=50.0, weight=2e5, n_grid=ng, ion_subcycle=5, cap_e=20_000,
-                  cap_i=20_000, flags=["allow_unstable"])
+    c = base_case(n_init_e=0, n_init_i=0, pressure_pa=50.0, weight=2e5, n_grid=ng, ion_subcycle=5, cap_e=n + 20_000,
+                  cap_i=n + 20_000, flags=["allow_unstable"])
     st = random_state(n, n, c["gap_m"], seed=ng + n, te_ev=4.0, hot_frac=0.3, hot_ev=90.0, ion_energy_ev=30.0)
     try:
         ctx.set_option(edupic.OPT_SMALL_MAX, small)

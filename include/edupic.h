@@ -126,13 +126,17 @@ extern "C" {
 #define EDP_OPT_POISSON 8     /* field solve: 0 parallel flux scans (default),
                                  1 sequential Thomas, bit-reproducible           */
 #define EDP_OPT_GROUPS 11     /* lockstep groups of a multi-case advance, 1..4
-                                 (default 2; at most one per case, so a
-                                 single case runs alone): the cases are split
-                                 by expected work (particles x steps), group 0
-                                 runs on the context's stream and the others
-                                 on streams the library creates (default
+                                 (default 2).  1: all cases advance in one
+                                 group, a launch advances each of them by a
+                                 step.  2 and more, all alike: the cases are
+                                 split by expected work (particles x steps)
+                                 into as many blocks as keep each one's
+                                 particles within the Infinity Cache, the
+                                 blocks' windows follow one another, and a
+                                 block runs as two groups side by side on
+                                 streams the library creates (default
                                  priority), so that one group's launch ramp
-                                 and tail overlap another's streaming; work
+                                 and tail overlap the other's streaming; work
                                  enqueued later on the context's
                                  stream is ordered after every group.
                                  Results do not depend on it, speed does: the
@@ -247,9 +251,10 @@ typedef struct {
 /* Create a context on `device` issuing work on `hip_stream` (a hipStream_t,
  * NULL = the legacy default stream).  *out receives the context.  The
  * context also creates and owns three non-blocking streams of default
- * priority for lockstep groups 1-3 of a multi-case advance (EDP_OPT_GROUPS);
- * every advance joins them back into `hip_stream`, and edp_destroy destroys
- * them.  EDP_EHIP if they cannot be created. */
+ * priority, two for lockstep groups side by side (EDP_OPT_GROUPS) and one for
+ * the persistent small cases (EDP_OPT_SMALL_MAX); every advance joins them
+ * back into `hip_stream`, and edp_destroy destroys them.  EDP_EHIP if they
+ * cannot be created. */
 int edp_create(edp_ctx **out, int device, void *hip_stream);
 /* Destroy a context; cases still alive are destroyed (arenas stay the
  * caller's). */

@@ -14,6 +14,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <map>
 #include <mutex>
 #include <numeric>
@@ -114,6 +115,7 @@ struct Batch {
   int max_ng = 2;
   size_t lds[2] = {0, 0};
   int nb[2] = {256, 256};  // threads of a particle workgroup per species
+  bool side = false;       // laid out for a launch beside another group's
   // graph of one window of g_steps steps, valid for these cases at these
   // step phases and sort grids
   hipGraphExec_t gexec = nullptr;
@@ -123,22 +125,21 @@ struct Batch {
 
 // One lockstep group of cases: its batch tables, its device role table, and
 // the stream its launches go to.  A multi-case advance runs as one group on
-// the caller's stream, or as up to kMaxGroups groups whose launches go to
-// streams of their own, so that one group's launch tail overlaps another's
-// streaming (the groups share nothing; each keeps its own order).
-constexpr int kMaxGroups = 4;
+// the caller's stream or as several (see run_lockstep).
+constexpr int kMaxGroups = 4;  // largest value of EDP_OPT_GROUPS
+constexpr int kSide = 2;       // groups side by side, each on a stream of its own
 constexpr int kAutoSkew = -1;  // EDP_OPT_PART_SKEW default
 struct Group {
   Batch batch;
   BlockRole* roles_d = nullptr;
   size_t roles_cap = 0;
-  std::vector<BlockRole> roles_h;  // host copy of the last upload
+  // the last upload's host copy, pinned (the allocation-free advance's: pageable)
+  BlockRole* roles_pin = nullptr;
+  std::vector<BlockRole> roles_h;
   bool valid = false;  // the tables match batch.cases
   hipStream_t stream = nullptr;  // where this advance enqueues the group's work
-  // groups 1.. : the library's own stream (default priority) and the event
-  // the caller's stream waits on at the end of an advance
-  hipStream_t own = nullptr;
-  hipEvent_t join = nullptr;
+  hipEvent_t last = nullptr;     // the end of what was enqueued with the tables
+  bool side = false;             // another group's launches run beside this one's
   // the allocation-free advance's group: its role table is the device's
   // file-scope array (roles_d, roles_cap fixed), it launches plainly (no
   // graph, no timing events) on the context's stream and never allocates
@@ -175,7 +176,7 @@ struct edp_ctx {
   int part_wg_per_cu = 0;  // 0: every resident slot
   int pretest = 0;  // EDP_OPT_PRETEST
   int part_skew = kAutoSkew;  // per mille: the last layer's weight below the first's; -1 automatic
-  int groups = 2;  // lockstep groups of a multi-case advance (1..kMaxGroups)
+  int groups = 2;  // EDP_OPT_GROUPS: 1 one lockstep group, 2.. blocks of two side by side
   // cases of at most this many slots per species (estimate) run in the
   // persistent one-workgroup-per-case kernel (0: none)
   int64_t small_max = 0;
@@ -188,7 +189,11 @@ struct edp_ctx {
   // the groups' tables and run state; group 0 runs on `stream`, the others
   // on streams of their own, forked from and joined back into `stream` by an
   // advance
-  Group grp[kMaxGroups];
+  std::deque<Group> grp;
+  // the streams of groups side by side (default priority) and the events the
+  // caller's stream waits on
+  hipStream_t side[kSide] = {};
+  hipEvent_t side_end[kSide] = {};
   hipEvent_t fork_ev = nullptr;
   // the allocation-free advance (edp_advance_steps_noalloc): one group on
   // `stream` whose role table is the device's scratch array
@@ -552,27 +557,33 @@ void drop_graph(Group& G) {
   G.batch.g_steps = 0;
 }
 
-void destroy_group_streams(edp_ctx* ctx) {
+void destroy_streams(edp_ctx* ctx) {
   if (ctx->fork_ev) (void)hipEventDestroy(ctx->fork_ev);
   ctx->fork_ev = nullptr;
   if (ctx->small_stream) (void)hipStreamDestroy(ctx->small_stream);
   if (ctx->small_join) (void)hipEventDestroy(ctx->small_join);
   ctx->small_stream = nullptr;
   ctx->small_join = nullptr;
-  for (Group& G : ctx->grp) {
-    if (G.own) (void)hipStreamDestroy(G.own);
-    if (G.join) (void)hipEventDestroy(G.join);
-    G.own = nullptr;
-    G.join = nullptr;
+  for (int g = 0; g < kSide; ++g) {
+    if (ctx->side[g]) (void)hipStreamDestroy(ctx->side[g]);
+    if (ctx->side_end[g]) (void)hipEventDestroy(ctx->side_end[g]);
+    ctx->side[g] = nullptr;
+    ctx->side_end[g] = nullptr;
   }
 }
 
-// Drain every group's stream and forget their graphs and tables.
+int sync_sides(edp_ctx* ctx) {
+  for (int g = 0; g < kSide; ++g)
+    if (ctx->side[g]) HIPCHK(hipStreamSynchronize(ctx->side[g]));
+  return EDP_OK;
+}
+
+// Drain the streams and forget the groups' graphs and tables.
 int reset_groups(edp_ctx* ctx) {
   HIPCHK(hipStreamSynchronize(ctx->stream));
   if (ctx->small_stream) HIPCHK(hipStreamSynchronize(ctx->small_stream));
-  for (Group& G : ctx->grp)
-    if (G.own) HIPCHK(hipStreamSynchronize(G.own));
+  const int r = sync_sides(ctx);
+  if (r) return r;
   for (Group& G : ctx->grp) {
     drop_graph(G);
     G.valid = false;
@@ -670,8 +681,7 @@ int particle_block(const edp_ctx* ctx, const std::vector<Case*>& cs, int sp, int
 // work (est_cost), so every workgroup has about the same amount of it (any
 // count is still covered: the kernels split the live chunks over whatever
 // workgroups a case has).  The table is read by
-// kernels still in flight, so the stream is drained before it changes;
-// grids are rebuilt only when a case's share has moved by a quarter or the
+// kernels still in flight, so they are waited for before it changes; grids are rebuilt only when a case's share has moved by a quarter or the
 // shares by a sixteenth of the workgroups in all.
 int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   Batch& B = G.batch;
@@ -690,7 +700,12 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
     const int occ = particle_occupancy(sp, nb[sp], lds[sp]);
     // the option counts workgroups of 256 threads
     const int per_cu = ctx->part_wg_per_cu > 0 ? std::min(std::max(1, ctx->part_wg_per_cu * 256 / nb[sp]), occ) : occ;
-    const int64_t slots = (int64_t)ctx->num_cu * per_cu;
+    // of two groups side by side each asks for three quarters of the slots: the
+    // second's workgroups fill what the first's leave at their ends (all of
+    // them, three quarters, half, us a step: 8 mixed cases 32.8 29.2 27.4, 32
+    // of them 54.8 51.5 53.2, 64 of them 100.6 100.4 109.9, 32 dual-frequency
+    // cases 274.7 271.0 279.8)
+    const int64_t slots = (int64_t)ctx->num_cu * per_cu * (G.side ? 3 : 4) / 4;
     double total = 0.0;
     for (const Case* c : cs) total += est_cost(c, sp);
     // every case at least one workgroup, the slots in proportion to the
@@ -725,7 +740,7 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   // rebuilt when a case's share has moved by a quarter, or the shares by a
   // sixteenth of the workgroups in all
   auto near = [](int a, int a0) { return a <= a0 * 5 / 4 + 1 && a >= a0 * 3 / 4; };
-  bool same = G.valid && B.cases == cs;
+  bool same = G.valid && B.cases == cs && B.side == G.side;
   int64_t moved[2] = {0, 0};
   for (size_t k = 0; k < nc && same; ++k) {
     for (int sp = 0; sp < 2 && same; ++sp) {
@@ -737,10 +752,16 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   }
   for (int sp = 0; sp < 2 && same; ++sp) same = nb[sp] == B.nb[sp] && 16 * moved[sp] <= B.parts[sp];
   if (same) return EDP_OK;
-  HIPCHK(hipStreamSynchronize(G.stream));
+  // what was enqueued with the old tables has ended (not the other groups'
+  // windows before this one on the same stream)
+  if (G.fixed)
+    HIPCHK(hipStreamSynchronize(G.stream));
+  else if (G.last)
+    HIPCHK(hipEventSynchronize(G.last));
   drop_graph(G);
   G.valid = false;
   B.cases = cs;
+  B.side = G.side;
   B.h = BatchTable{};
   B.h.ncase = (int32_t)nc;
   B.max_ng = max_ng;
@@ -774,19 +795,27 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   if (roles.size() > G.roles_cap && G.fixed)
     return fail(EDP_EINVAL, "the batch needs %zu workgroup roles; the allocation-free advance holds at most %d",
                 roles.size(), kScratchRoles);
-  if (roles.size() > G.roles_cap) {
-    // no kernel of this group is in flight (drained above)
-    if (G.roles_d) HIPCHK(hipFree(G.roles_d));
-    G.roles_d = nullptr;
-    G.roles_cap = 0;
-    HIPCHK(hipMalloc((void**)&G.roles_d, roles.size() * sizeof(BlockRole)));
-    G.roles_cap = roles.size();
+  const BlockRole* src;
+  if (G.fixed) {
+    G.roles_h.swap(roles);
+    src = G.roles_h.data();
+  } else {
+    if (roles.size() > G.roles_cap) {
+      // with room to grow: a free waits for everything on the device
+      if (G.roles_d) HIPCHK(hipFree(G.roles_d));
+      if (G.roles_pin) HIPCHK(hipHostFree(G.roles_pin));
+      G.roles_d = G.roles_pin = nullptr;
+      G.roles_cap = 0;
+      const size_t cap = roles.size() + roles.size() / 4;
+      HIPCHK(hipMalloc((void**)&G.roles_d, cap * sizeof(BlockRole)));
+      HIPCHK(hipHostMalloc((void**)&G.roles_pin, cap * sizeof(BlockRole), hipHostMallocDefault));
+      G.roles_cap = cap;
+    }
+    std::copy(roles.begin(), roles.end(), G.roles_pin);
+    src = G.roles_pin;
   }
-  // ordered on the group's own stream (a blocking copy would also wait for
-  // the other group's work when the caller's stream is the null stream)
-  G.roles_h.swap(roles);
-  HIPCHK(hipMemcpyAsync(G.roles_d, G.roles_h.data(), G.roles_h.size() * sizeof(BlockRole), hipMemcpyHostToDevice,
-                        G.stream));
+  // ordered on the group's stream
+  HIPCHK(hipMemcpyAsync(G.roles_d, src, B.nroles * sizeof(BlockRole), hipMemcpyHostToDevice, G.stream));
   G.valid = true;
   return EDP_OK;
 }
@@ -828,19 +857,21 @@ int enqueue_batch_step(edp_ctx* ctx, Group& G, const std::vector<int64_t>& s, in
   return EDP_OK;
 }
 
-// A window of `steps` steps of the group from the cases' steps s: the
-// window's first kernel (roles' steps, slot-count rings), the steps, its
-// last kernel (counters, steps, slot counts).
-int enqueue_window(edp_ctx* ctx, Group& G, const std::vector<int64_t>& s, int64_t steps, bool capture) {
+// Steps [j0, j1) of a window of `steps` steps of the group from the cases'
+// steps s: with its first step the window's first kernel (roles' steps,
+// slot-count rings), after its last one the last kernel (counters, steps,
+// slot counts).
+int enqueue_window(edp_ctx* ctx, Group& G, const std::vector<int64_t>& s, int64_t steps, int64_t j0, int64_t j1,
+                   bool capture) {
   Batch& B = G.batch;
   const int nc = (int)B.cases.size();
   const BlockRole* case_roles = G.roles_d + B.role_off[2];
-  HIPCHK(launch_window_begin(G.roles_d, (int)B.nroles, case_roles, nc, G.stream));
-  for (int64_t j = 0; j < steps; ++j) {
+  if (j0 == 0) HIPCHK(launch_window_begin(G.roles_d, (int)B.nroles, case_roles, nc, G.stream));
+  for (int64_t j = j0; j < j1; ++j) {
     const int r = enqueue_batch_step(ctx, G, s, j, capture);
     if (r) return r;
   }
-  HIPCHK(launch_window_end(case_roles, nc, (int)steps, G.stream));
+  if (j1 == steps) HIPCHK(launch_window_end(case_roles, nc, (int)steps, G.stream));
   return EDP_OK;
 }
 
@@ -855,7 +886,7 @@ int build_graph(edp_ctx* ctx, Group& G, const std::vector<int64_t>& s, int steps
   hipStream_t st = G.stream;
   hipGraph_t g = nullptr;
   HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-  const int r = enqueue_window(ctx, G, s, steps, true);
+  const int r = enqueue_window(ctx, G, s, steps, 0, steps, true);
   const hipError_t ec = hipStreamEndCapture(st, &g);
   if (r) {
     if (g) (void)hipGraphDestroy(g);
@@ -877,79 +908,91 @@ bool graph_matches(const Group& G, const std::vector<int64_t>& s, int steps) {
   return true;
 }
 
-// One window (up to 4096 steps) of the cases of group G that still have
+// One window (up to 4096 steps) of the cases of a group that still have
 // steps to go, all in lockstep: the group's tables, the voltages, then graph
 // replays (whole graphs of a multiple of sort_every * N_SUB steps) or plain
-// steps on the group's stream.  `done`: no case had steps left.
-int group_window(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::vector<int64_t>& left, bool& done) {
+// steps on the group's stream.  open() prepares it (act empty: no case had
+// steps left), some() enqueues its next steps, close() advances the cases.
+struct Window {
   std::vector<Case*> act;
-  std::vector<int64_t> s;
-  int64_t w = 4096;
-  int64_t base = 1;
-  for (size_t k = 0; k < cases.size(); ++k) {
-    if (left[k] <= 0) continue;
-    act.push_back(cases[k]);
-    s.push_back(cases[k]->step);
-    w = std::min(w, left[k]);
-    const int64_t p = (int64_t)ctx->sort_every * cases[k]->desc.ion_subcycle;
-    base = std::lcm(base, p);
-  }
-  done = act.empty();
-  if (done) return EDP_OK;
-  for (Case* c : act) poll_estimate(c);
-  int r = set_batch(ctx, G, act);
-  if (r) return r;
-  int gsteps = 0;
-  if (ctx->mode == 1 && base <= 4096 && !G.fixed) {
-    gsteps = ctx->graph_steps > 0 ? ctx->graph_steps : (int)(base * std::max<int64_t>(1, 200 / base));
-    if (gsteps % base != 0) gsteps = (int)((gsteps / base + 1) * base);
-    if (gsteps <= w) w = (w / gsteps) * gsteps; else gsteps = 0;
-  }
-  for (Case* c : act) {
-    r = upload_volt(c, c->step, c->step + w, G.stream);
+  std::vector<int64_t> s;  // their steps at the window's start
+  int64_t w = 0, j = 0;    // steps of the window, steps enqueued
+  int64_t plain = -1;      // first step of the plain part
+  int gsteps = 0;          // steps of a graph, 0: plain launches
+
+  int open(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, const std::vector<int64_t>& left) {
+    int64_t base = 1;
+    for (size_t k = 0; k < cases.size(); ++k) {
+      if (left[k] <= 0) continue;
+      act.push_back(cases[k]);
+      s.push_back(cases[k]->step);
+      w = std::min(w > 0 ? w : (int64_t)4096, left[k]);
+      const int64_t p = (int64_t)ctx->sort_every * cases[k]->desc.ion_subcycle;
+      base = std::lcm(base, p);
+    }
+    if (act.empty()) return EDP_OK;
+    for (Case* c : act) poll_estimate(c);
+    int r = set_batch(ctx, G, act);
     if (r) return r;
+    if (ctx->mode == 1 && base <= 4096 && !G.fixed) {
+      gsteps = ctx->graph_steps > 0 ? ctx->graph_steps : (int)(base * std::max<int64_t>(1, 200 / base));
+      if (gsteps % base != 0) gsteps = (int)((gsteps / base + 1) * base);
+      if (gsteps <= w) w = (w / gsteps) * gsteps; else gsteps = 0;
+    }
+    for (Case* c : act) {
+      r = upload_volt(c, c->step, c->step + w, G.stream);
+      if (r) return r;
+    }
+    return EDP_OK;
   }
-  int64_t j = 0;
-  while (j < w) {
+  // a graph, or up to `most` plain steps
+  int some(edp_ctx* ctx, Group& G, int64_t most) {
+    if (j >= w) return EDP_OK;
+    std::vector<int64_t> sj(s);
     if (gsteps > 0) {
-      std::vector<int64_t> sj(s);
       for (auto& v : sj) v += j;
       if (!graph_matches(G, sj, gsteps)) {
-        r = build_graph(ctx, G, sj, gsteps);
+        const int r = build_graph(ctx, G, sj, gsteps);
         if (r) return r;
       }
       HIPCHK(hipGraphLaunch(G.batch.gexec, G.stream));
       j += gsteps;
-      continue;
+      return EDP_OK;
     }
     // plain launches: the rest of the window as one window of its own
-    std::vector<int64_t> sj(s);
-    for (auto& v : sj) v += j;
-    r = enqueue_window(ctx, G, sj, w - j, false);
-    if (r) return r;
-    j = w;
+    if (plain < 0) plain = j;
+    for (auto& v : sj) v += plain;
+    const int64_t to = std::min(w, j + most);
+    const int r = enqueue_window(ctx, G, sj, w - plain, j - plain, to - plain, false);
+    j = to;
+    return r;
   }
-  for (size_t k = 0, a = 0; k < cases.size(); ++k) {
-    if (left[k] <= 0) continue;
-    cases[k]->step += w;
-    left[k] -= w;
-    r = request_estimate(act[a++], G.stream);
-    if (r) return r;
+  int close(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::vector<int64_t>& left) {
+    for (size_t k = 0, a = 0; k < cases.size(); ++k) {
+      if (left[k] <= 0) continue;
+      cases[k]->step += w;
+      left[k] -= w;
+      const int r = request_estimate(act[a++], G.stream);
+      if (r) return r;
+    }
+    if (!G.fixed) {
+      if (!G.last) HIPCHK(hipEventCreateWithFlags(&G.last, hipEventDisableTiming));
+      HIPCHK(hipEventRecord(G.last, G.stream));
+    }
+    return ctx->ev_pairs.size() > 8192 ? drain_profile(ctx) : EDP_OK;
   }
-  if (ctx->ev_pairs.size() > 8192) {
-    r = drain_profile(ctx);
-    if (r) return r;
-  }
-  return EDP_OK;
+};
+
+// A whole window of one group.  `done`: no case had steps left.
+int group_window(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::vector<int64_t>& left, bool& done) {
+  Window W;
+  int r = W.open(ctx, G, cases, left);
+  done = W.act.empty();
+  if (r || done) return r;
+  while (r == EDP_OK && W.j < W.w) r = W.some(ctx, G, W.w);
+  return r ? r : W.close(ctx, G, cases, left);
 }
 
-// Advance cases[k] by n[k] steps.  With G groups (the option, at most one
-// per case) the cases are split into G lockstep groups balanced by expected
-// work (particles x steps, largest first onto the least loaded group), each
-// keeping the call's order; the streams of groups 1.. wait for everything
-// enqueued on the caller's stream before they start, windows of the groups
-// are enqueued in turn, and the caller's stream waits for every group at
-// the end, so every later call on it is ordered after all of them.
 // Whether a case runs in the persistent one-workgroup-per-case kernel: few
 // enough slots (estimate) and its LDS within one workgroup's 64 KiB.
 bool small_case(const edp_ctx* ctx, const Case* c) {
@@ -1043,53 +1086,131 @@ int run_batch(edp_ctx* ctx, const std::vector<Case*>& all, const std::vector<int
   return r;
 }
 
-int run_lockstep(edp_ctx* ctx, const std::vector<Case*>& cases, const std::vector<int64_t>& n) {
-  const int ng = (int)std::min<size_t>((size_t)ctx->groups, std::max<size_t>(1, cases.size()));
-  std::vector<Case*> gc[kMaxGroups];
-  std::vector<int64_t> gl[kMaxGroups];
+// Advance cases[k] by n[k] steps in lockstep groups: a group's launches
+// advance all of its cases by a step each.
+//
+// Blocks: cases whose particles the Infinity Cache holds together read them
+// from there step after step, more of them read from HBM.  So the cases are
+// cut into as few blocks as keep a block's streamed bytes a step within
+// kGroupBytes, and the blocks' windows follow one another on the caller's
+// stream.  Measured with one group a block, us a step: 32 dual-frequency cases
+// of 27 MB each in 1, 3, 4, 5 blocks 388, 296, 308, 317; 16 of them (430 MB)
+// in 1, 2 blocks 176, 150, 14 (380 MB) 135, 133, 13 (350 MB) 116, 125; 64
+// mixed cases (250 MB) in 1, 2, 3 blocks 108, 116, 129.
+//
+// Within a block two groups side by side, on streams of their own that wait
+// for the caller's and that it waits for: one group's launch gap, field
+// solves and tail run beside the other's streaming.  One, two, three groups,
+// us a step: 64 mixed cases 119, 100, 146; 16 of them 36.7, 35.2, 55; 4 of
+// them 21.4, 18.8; the 32 dual-frequency cases 296, 271, 372.
+constexpr double kGroupBytes = 360e6;
+// Bytes a case streams through a step: x, v_x, the bound of v_y^2 + v_z^2 and the
+// identity of every electron, the full state of every ion every ion step.
+double streamed_bytes(const Case* c) {
+  return 28.0 * (double)c->est[0] + 40.0 * (double)c->est[1] / (double)c->desc.ion_subcycle;
+}
+// Split the cases (with their steps n) into `parts` lists balanced by expected
+// work (particles x steps, largest first onto the least loaded), each keeping
+// the order.
+struct CaseList {
+  std::vector<Case*> cases;
+  std::vector<int64_t> left;
+};
+std::vector<CaseList> split_cases(const std::vector<Case*>& cases, const std::vector<int64_t>& n, size_t parts) {
+  std::vector<CaseList> out(parts);
+  std::vector<size_t> order(cases.size());
+  std::iota(order.begin(), order.end(), (size_t)0);
+  auto work = [&](size_t k) { return (double)(cases[k]->est[0] + cases[k]->est[1]) * (double)n[k]; };
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return work(a) > work(b); });
+  std::vector<double> load(parts, 0.0);
+  std::vector<int> count(parts, 0);
+  std::vector<size_t> in(cases.size());
+  for (size_t k : order) {
+    size_t g = 0;  // least loaded; on a tie (empty cases) the one with fewest cases
+    for (size_t h = 1; h < parts; ++h)
+      if (load[h] < load[g] || (load[h] == load[g] && count[h] < count[g])) g = h;
+    in[k] = g;
+    load[g] += work(k);
+    ++count[g];
+  }
+  for (size_t k = 0; k < cases.size(); ++k) {
+    out[in[k]].cases.push_back(cases[k]);
+    out[in[k]].left.push_back(n[k]);
+  }
+  return out;
+}
+
+// One window of the groups G[0..parts.size()) side by side.
+int side_window(edp_ctx* ctx, Group** G, std::vector<CaseList>& parts, bool& done) {
+  const size_t ng = parts.size();
   if (ng == 1) {
-    gc[0] = cases;
-    gl[0] = n;
-  } else {
-    std::vector<size_t> order(cases.size());
-    for (size_t k = 0; k < order.size(); ++k) order[k] = k;
-    auto work = [&](size_t k) { return (double)(cases[k]->est[0] + cases[k]->est[1]) * (double)n[k]; };
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return work(a) > work(b); });
-    double load[kMaxGroups] = {};
-    int count[kMaxGroups] = {};
-    std::vector<int> in(cases.size());
-    for (size_t k : order) {
-      int g = 0;  // least loaded; on a tie (empty cases) the one with fewest cases
-      for (int h = 1; h < ng; ++h)
-        if (load[h] < load[g] || (load[h] == load[g] && count[h] < count[g])) g = h;
-      in[k] = g;
-      load[g] += work(k);
-      ++count[g];
-    }
-    for (size_t k = 0; k < cases.size(); ++k) {
-      gc[in[k]].push_back(cases[k]);
-      gl[in[k]].push_back(n[k]);
-    }
+    G[0]->stream = ctx->stream;
+    G[0]->side = false;
+    return group_window(ctx, *G[0], parts[0].cases, parts[0].left, done);
   }
-  ctx->grp[0].stream = ctx->stream;
-  for (int g = 1; g < kMaxGroups; ++g) ctx->grp[g].stream = ctx->grp[g].own;
-  if (ng > 1) {
-    HIPCHK(hipEventRecord(ctx->fork_ev, ctx->stream));
-    for (int g = 1; g < ng; ++g) HIPCHK(hipStreamWaitEvent(ctx->grp[g].own, ctx->fork_ev, 0));
-  }
+  HIPCHK(hipEventRecord(ctx->fork_ev, ctx->stream));
+  std::vector<Window> W(ng);
   int r = EDP_OK;
-  bool done[kMaxGroups] = {};
-  for (int g = ng; g < kMaxGroups; ++g) done[g] = true;
-  auto all_done = [&] { return std::all_of(done, done + kMaxGroups, [](bool d) { return d; }); };
-  while (r == EDP_OK && !all_done())
-    for (int g = 0; g < ng && r == EDP_OK; ++g)
-      if (!done[g]) r = group_window(ctx, ctx->grp[g], gc[g], gl[g], done[g]);
+  for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
+    G[g]->stream = ctx->side[g];
+    G[g]->side = true;
+    HIPCHK(hipStreamWaitEvent(ctx->side[g], ctx->fork_ev, 0));
+    r = W[g].open(ctx, *G[g], parts[g].cases, parts[g].left);
+  }
+  // a few steps of each in turn, so that none waits for the enqueueing of
+  // another's whole window
+  for (bool more = true; more && r == EDP_OK;) {
+    more = false;
+    for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
+      r = W[g].some(ctx, *G[g], 16);
+      more = more || W[g].j < W[g].w;
+    }
+  }
+  done = true;
+  for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
+    if (W[g].act.empty()) continue;
+    done = false;
+    r = W[g].close(ctx, *G[g], parts[g].cases, parts[g].left);
+  }
   // the joins also after a failed window: whatever the groups did enqueue
   // stays ordered before later work on the caller's stream
-  for (int g = 1; g < ng; ++g) {
-    const hipError_t e = hipEventRecord(ctx->grp[g].join, ctx->grp[g].own);
-    const hipError_t w = e == hipSuccess ? hipStreamWaitEvent(ctx->stream, ctx->grp[g].join, 0) : e;
-    if (w != hipSuccess && r == EDP_OK) r = fail(EDP_EHIP, "joining group %d: %s", g, hipGetErrorString(w));
+  for (size_t g = 0; g < ng; ++g) {
+    const hipError_t e = hipEventRecord(ctx->side_end[g], ctx->side[g]);
+    const hipError_t w = e == hipSuccess ? hipStreamWaitEvent(ctx->stream, ctx->side_end[g], 0) : e;
+    if (w != hipSuccess && r == EDP_OK) r = fail(EDP_EHIP, "joining group %d: %s", (int)g, hipGetErrorString(w));
+  }
+  return r;
+}
+
+int run_lockstep(edp_ctx* ctx, const std::vector<Case*>& cases, const std::vector<int64_t>& n) {
+  double bytes = 0.0;
+  for (const Case* c : cases) bytes += streamed_bytes(c);
+  const size_t nb = ctx->groups == 1 ? 1 : std::min(std::max<size_t>(1, cases.size()),
+                                                    (size_t)std::max(1.0, std::ceil(bytes / kGroupBytes)));
+  std::vector<std::vector<CaseList>> blocks;
+  size_t used = 0;
+  for (CaseList& b : split_cases(cases, n, nb)) {
+    const size_t ng = std::min<size_t>(std::min(ctx->groups, kSide), std::max<size_t>(1, b.cases.size()));
+    blocks.push_back(split_cases(b.cases, b.left, ng));
+    used += ng;
+  }
+  while (ctx->grp.size() < used) ctx->grp.emplace_back();
+  int r = EDP_OK;
+  std::vector<char> done(nb, 0);
+  while (r == EDP_OK && !std::all_of(done.begin(), done.end(), [](char d) { return d != 0; })) {
+    size_t at = 0;
+    for (size_t b = 0; b < nb && r == EDP_OK; ++b) {
+      Group* G[kSide];
+      for (size_t g = 0; g < blocks[b].size(); ++g) G[g] = &ctx->grp[at++];
+      bool d = false;
+      if (!done[b]) r = side_window(ctx, G, blocks[b], d);
+      if (d) done[b] = 1;
+    }
+  }
+  // after a failed window the groups' events may be older than what it enqueued
+  if (r != EDP_OK) {
+    (void)hipStreamSynchronize(ctx->stream);
+    (void)sync_sides(ctx);
   }
   return r;
 }
@@ -1220,15 +1341,16 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
   ctx->stream = (hipStream_t)hip_stream;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->num_cu = prop.multiProcessorCount;
-  // the other groups' streams (default priority) and the fork/join events
+  // the small cases' and the groups' streams (default priority) and the
+  // fork/join events
   bool ok = hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) == hipSuccess &&
             hipStreamCreateWithFlags(&ctx->small_stream, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess;
-  for (int g = 1; g < kMaxGroups && ok; ++g)
-    ok = hipStreamCreateWithFlags(&ctx->grp[g].own, hipStreamNonBlocking) == hipSuccess &&
-         hipEventCreateWithFlags(&ctx->grp[g].join, hipEventDisableTiming) == hipSuccess;
+  for (int g = 0; g < kSide && ok; ++g)
+    ok = hipStreamCreateWithFlags(&ctx->side[g], hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&ctx->side_end[g], hipEventDisableTiming) == hipSuccess;
   if (!ok) {
-    destroy_group_streams(ctx);
+    destroy_streams(ctx);
     delete ctx;
     return fail(EDP_EHIP, "creating the groups' streams or events failed");
   }
@@ -1236,7 +1358,7 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
   BlockRole* sp = nullptr;
   const int rs = scratch_roles(device, &sp);
   if (rs) {
-    destroy_group_streams(ctx);
+    destroy_streams(ctx);
     delete ctx;
     return rs;
   }
@@ -1251,10 +1373,13 @@ int edp_destroy(edp_ctx* ctx) {
   if (!ctx) return EDP_OK;
   (void)reset_groups(ctx);
   if (ctx->small_stream) (void)hipStreamSynchronize(ctx->small_stream);
-  for (Group& G : ctx->grp)
+  for (Group& G : ctx->grp) {
     if (G.roles_d) (void)hipFree(G.roles_d);
+    if (G.roles_pin) (void)hipHostFree(G.roles_pin);
+    if (G.last) (void)hipEventDestroy(G.last);
+  }
   if (ctx->small_roles) (void)hipFree(ctx->small_roles);
-  destroy_group_streams(ctx);
+  destroy_streams(ctx);
   for (auto& kv : ctx->cases) {
     Case* c = kv.second;
     if (c->vstage) (void)hipHostFree(c->vstage);
@@ -1530,8 +1655,7 @@ int edp_case_destroy(edp_ctx* ctx, edp_case id) {
   Case* c = find(ctx, id);
   if (!c) return fail(EDP_EINVAL, "unknown case");
   (void)hipStreamSynchronize(ctx->stream);
-  for (Group& G : ctx->grp)
-    if (G.own) (void)hipStreamSynchronize(G.own);
+  (void)sync_sides(ctx);
   for (Group& G : ctx->grp)
     if (std::find(G.batch.cases.begin(), G.batch.cases.end(), c) != G.batch.cases.end()) {
       drop_graph(G);
@@ -1599,8 +1723,8 @@ int edp_advance(edp_ctx* ctx, const edp_case* cases, int32_t n_cases, const int3
 int edp_sync(edp_ctx* ctx) {
   if (!ctx) return fail(EDP_EINVAL, "null context");
   HIPCHK(hipStreamSynchronize(ctx->stream));
-  for (Group& G : ctx->grp)
-    if (G.own) HIPCHK(hipStreamSynchronize(G.own));
+  const int rs = sync_sides(ctx);
+  if (rs) return rs;
   int status = EDP_OK;
   for (auto& kv : ctx->cases) {
     Case* c = kv.second;

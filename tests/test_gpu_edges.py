@@ -59,3 +59,33 @@ def test_edges_match_oracle(ctx, xs_default, orc, ng, n, step, small):
     finally:
         ctx.set_option(edupic.OPT_SMALL_MAX, 0)
         ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_FLUX)
+
+
+@pytest.mark.parametrize("mode,n", [(0, 3_400_000), (1, 3_400_000), (0, 1_000)], ids=["blocks", "blocks-graph", "one-block"])
+def test_blocks_and_side_by_side_groups(ctx, mode, n):
+    """Five cases whose streamed bytes need two blocks (and, small, one), the
+    blocks as two groups side by side, over windows of graphs and of a few
+    plain steps: densities and counters are those of one lockstep group."""
+    from paper_2103_09642_amd import edupic
+    say(f"test_blocks_and_side_by_side_groups mode={mode} n={n}")
+    got = {}
+    try:
+        ctx.set_option(edupic.OPT_SORT_EVERY, 5)
+        ctx.set_option(edupic.OPT_MODE, mode)
+        for groups in (1, 2, 4):
+            ctx.set_option(edupic.OPT_GROUPS, groups)
+            cases = [ctx.create_case(base_case(n_init_e=n + 999 * k, n_init_i=1_000 + 64 * k, n_grid=100 + k, weight=10.0,
+                                               ion_subcycle=2, cap_e=n + 100_000, cap_i=50_000, seed=k,
+                                               pressure_pa=20.0 + k, flags=["allow_unstable"])) for k in range(5)]
+            ctx.advance_steps(cases, [7, 26, 26, 0, 21])
+            got[groups] = [(g.counts(), g.deposit()) for g in cases]
+            for g in cases:
+                g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_GROUPS, 2)
+        ctx.set_option(edupic.OPT_MODE, 0)
+        ctx.set_option(edupic.OPT_SORT_EVERY, 100)
+    for groups in (2, 4):
+        for (ca, da), (cb, db) in zip(got[1], got[groups]):
+            assert ca == cb
+            assert all(np.array_equal(x, y) for x, y in zip(da, db))

@@ -32,6 +32,9 @@ hipError_t launch_window_end(const BlockRole* cases, int ncase, int steps, hipSt
 size_t particle_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed, int sp);
 size_t particle_static_lds(int sp, int nb);
 int particle_occupancy(int sp, int nb, size_t lds);
+hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, hipStream_t st);
+hipError_t launch_small_volt(const BlockRole* roles, int ncase, hipStream_t st);
+hipError_t launch_small_end(const BlockRole* roles, int ncase, hipStream_t st);
 hipError_t launch_seed(CaseDev* d, int sp, int64_t n, double sigma, hipStream_t st);
 hipError_t launch_deposit(CaseDev* d, int sp, int64_t* dst1, int64_t* dst2, int ng, int blocks,
                           hipStream_t st);
@@ -85,10 +88,14 @@ struct Case {
   double coll_rate[2] = {0.0, 0.0};
   int64_t rate_coll[2] = {0, 0}, rate_pst[2] = {0, 0};
   hipEvent_t est_ev = nullptr;
+  hipEvent_t est_wait = nullptr;  // est_ev, or the small cases' end
   bool est_pending = false;
   double* vstage = nullptr;  // pinned staging of V(t_s)
   hipEvent_t vev = nullptr;
-  bool vev_pending = false;
+  // V(t_s) of steps [v_lo, v_hi) in vstage (at s % kVoltChunk) may still be on
+  // its way to the device; v_ev ends it (null: nothing is)
+  int64_t v_lo = 0, v_hi = 0;
+  hipEvent_t v_ev = nullptr;
   bool failed = false;
 };
 
@@ -181,6 +188,11 @@ struct edp_ctx {
   // persistent one-workgroup-per-case kernel (0: none)
   int64_t small_max = 0;
   // the persistent small cases' stream (default priority) and role table
+  // pinned staging of the reads (kPinBytes) and, from the first one on, of state
+  // transfers (kStateBytes); one lock for both (reads of several threads)
+  char* pin = nullptr;
+  char* pin_state = nullptr;
+  std::mutex pin_mu;
   hipStream_t small_stream = nullptr;
   hipEvent_t small_join = nullptr;
   BlockRole* small_roles = nullptr;
@@ -422,12 +434,47 @@ Case* find(edp_ctx* ctx, edp_case id) {
 // The dynamic tail of CaseDev (from `step` on) is read and written whole.
 constexpr size_t kDynOff = offsetof(CaseDev, step);
 constexpr size_t kDynBytes = sizeof(CaseDev) - kDynOff;
+static_assert(kDynOff % 8 == 0 && kDynBytes % 8 == 0, "read in words");
 
-int read_dyn(edp_ctx* ctx, Case* c, CaseDev& t) {
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  HIPCHK(hipMemcpy((char*)&t + kDynOff, (char*)c->d + kDynOff, kDynBytes, hipMemcpyDeviceToHost));
+constexpr size_t kPinBytes = (size_t)256 << 10;
+static_assert(kPinBytes >= kDynBytes + 4 * kMaxNodes * 8, "the largest read of parts");
+// Slots of a state transfer through its staging at a time, of 48 bytes.
+constexpr int64_t kStateChunk = 1 << 14;
+constexpr size_t kStateBytes = (size_t)kStateChunk * 48;
+int state_buffer(edp_ctx* ctx) {  // with pin_mu held
+  if (!ctx->pin_state) HIPCHK(hipHostMalloc((void**)&ctx->pin_state, kStateBytes, hipHostMallocDefault));
   return EDP_OK;
 }
+
+// Parts of a case's device memory (n words each, see GatherPart) to the host,
+// after all work on the context's stream: one launch into pinned memory and
+// one wait.
+struct ReadPart {
+  const void* dev;
+  void* host;
+  size_t n;
+  int sel = 0;
+};
+int read_parts(edp_ctx* ctx, Case* c, std::initializer_list<ReadPart> parts) {
+  std::lock_guard<std::mutex> lock(ctx->pin_mu);
+  GatherParts P{};
+  size_t at = 0;
+  int k = 0;
+  for (const ReadPart& q : parts) {
+    if (k >= kGatherMax || (at + q.n) * 8 > kPinBytes) return fail(EDP_EINVAL, "internal: read exceeds the staging");
+    P.p[k++] = GatherPart{(const int64_t*)q.dev, (int64_t*)ctx->pin + at, (int32_t)q.n, q.sel};
+    at += q.n;
+  }
+  HIPCHK(launch_gather(c->d, P, k, ctx->stream));
+  HIPCHK(hipStreamSynchronize(ctx->stream));
+  k = 0;
+  for (const ReadPart& q : parts) std::memcpy(q.host, P.p[k++].dst, q.n * 8);
+  return EDP_OK;
+}
+// The case's dynamic part as one of the parts of a read.
+ReadPart dyn_part(Case* c, CaseDev& t) { return {(char*)c->d + kDynOff, (char*)&t + kDynOff, kDynBytes / 8}; }
+
+int read_dyn(edp_ctx* ctx, Case* c, CaseDev& t) { return read_parts(ctx, c, {dyn_part(c, t)}); }
 
 int write_dyn(edp_ctx* ctx, Case* c, const CaseDev& t) {
   HIPCHK(hipStreamSynchronize(ctx->stream));
@@ -461,26 +508,36 @@ double est_cost(const Case* c, int sp) {
 constexpr size_t kEstSpan = offsetof(CaseDev, ctr) + sizeof(int64_t) * kNumCtr - offsetof(CaseDev, alloc);
 constexpr int64_t kRateSteps = 1 << 20;
 
+// V(t_s) of steps [s0, s1) (at most kVoltChunk) into the case's pinned
+// staging, once what is on its way from there has left.
+int stage_volt(Case* c, int64_t s0, int64_t s1) {
+  if (c->v_ev && (s0 != c->v_hi || s1 - c->v_lo > kVoltChunk)) {
+    HIPCHK(hipEventSynchronize(c->v_ev));
+    c->v_ev = nullptr;
+  }
+  if (!c->v_ev) c->v_lo = s0;
+  c->v_hi = s1;
+  for (int64_t s = s0; s < s1; ++s) c->vstage[s % kVoltChunk] = voltage(c->desc, s);
+  return EDP_OK;
+}
+
 // Upload V(t_s) for steps [s0, s1) (s1 - s0 <= kVoltChunk) into the ring.
 int upload_volt(Case* c, int64_t s0, int64_t s1, hipStream_t st) {
-  if (c->vev_pending) {
-    HIPCHK(hipEventSynchronize(c->vev));
-    c->vev_pending = false;
-  }
+  const int r = stage_volt(c, s0, s1);
+  if (r) return r;
   const int64_t n = s1 - s0;
-  for (int64_t k = 0; k < n; ++k) c->vstage[k] = voltage(c->desc, s0 + k);
   double* ring = const_cast<double*>(c->h.volt);
   const int64_t a = s0 % kVoltChunk;
   const int64_t first = std::min<int64_t>(n, kVoltChunk - a);
-  HIPCHK(hipMemcpyAsync(ring + a, c->vstage, first * 8, hipMemcpyHostToDevice, st));
-  if (first < n) HIPCHK(hipMemcpyAsync(ring, c->vstage + first, (n - first) * 8, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(ring + a, c->vstage + a, first * 8, hipMemcpyHostToDevice, st));
+  if (first < n) HIPCHK(hipMemcpyAsync(ring, c->vstage, (n - first) * 8, hipMemcpyHostToDevice, st));
   HIPCHK(hipEventRecord(c->vev, st));
-  c->vev_pending = true;
+  c->v_ev = c->vev;
   return EDP_OK;
 }
 
 void poll_estimate(Case* c) {
-  if (c->est_pending && hipEventQuery(c->est_ev) == hipSuccess) {
+  if (c->est_pending && hipEventQuery(c->est_wait) == hipSuccess) {
     const char* b = (const char*)c->est_pinned;
     auto at = [&](size_t off) {
       int64_t v;
@@ -511,6 +568,7 @@ int request_estimate(Case* c, hipStream_t st) {
   if (c->est_pending) return EDP_OK;
   HIPCHK(hipMemcpyAsync(c->est_pinned, (char*)c->d + offsetof(CaseDev, alloc), kEstSpan, hipMemcpyDeviceToHost, st));
   HIPCHK(hipEventRecord(c->est_ev, st));
+  c->est_wait = c->est_ev;
   c->est_pending = true;
   return EDP_OK;
 }
@@ -564,6 +622,8 @@ void destroy_streams(edp_ctx* ctx) {
   if (ctx->small_join) (void)hipEventDestroy(ctx->small_join);
   ctx->small_stream = nullptr;
   ctx->small_join = nullptr;
+  if (ctx->pin) (void)hipHostFree(ctx->pin);
+  ctx->pin = nullptr;
   for (int g = 0; g < kSide; ++g) {
     if (ctx->side[g]) (void)hipStreamDestroy(ctx->side[g]);
     if (ctx->side_end[g]) (void)hipEventDestroy(ctx->side_end[g]);
@@ -1004,7 +1064,13 @@ bool small_case(const edp_ctx* ctx, const Case* c) {
 // The persistent small cases of an advance, on the context's small-case
 // stream (forked from and joined back into the caller's stream): windows of
 // up to 4096 steps, each one launch in which workgroup k runs case k by its
-// own window (the cases do not wait for each other).
+// own window (the cases do not wait for each other).  The host forms V(t) of
+// a window while the one before it runs, so the first windows of many cases
+// are short (kVoltsFirst values in all, then four times as many); it reaches
+// the device, and the slot counts the host, by one launch for all cases (256
+// cases of 1e3 electrons, 4000 steps: 11 ms on the host before the GPU began,
+// now 1).
+constexpr int64_t kVoltsFirst = 1 << 16;
 int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t> left) {
   hipStream_t st = ctx->small_stream;
   // the previous call's table may still be in flight from host memory
@@ -1015,22 +1081,35 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
   for (const Case* c : cases)
     lds = std::max(lds, small_lds_bytes(c->desc.n_grid, c->desc.flags, c->desc.n_eepf, c->desc.n_ifed));
   // every window's roles, built up front and uploaded once: window w holds
-  // the cases with steps left, each with min(left, 4096) steps
-  constexpr int64_t kWin = 4096;
+  // the cases with steps left, each with min(left, the window's) steps; one
+  // more entry for each case's end
+  struct Win {
+    size_t lo, hi;  // its roles (and their cases in `who`)
+  };
   std::vector<BlockRole>& roles = ctx->small_h;
   roles.clear();
-  std::vector<size_t> win_off{0};
+  std::vector<Case*> who;
+  std::vector<Win> wins;
   std::vector<int64_t> rem(left);
-  for (;;) {
+  int64_t most = std::min<int64_t>(4096, std::max<int64_t>(64, kVoltsFirst / (int64_t)cases.size()));
+  for (;; most = std::min<int64_t>(4096, 4 * most)) {
+    const size_t lo = roles.size();
     for (size_t k = 0; k < cases.size(); ++k)
       if (rem[k] > 0) {
-        const int64_t w = std::min(rem[k], kWin);
+        const int64_t w = std::min(rem[k], most);
         roles.push_back(role(cases[k], (int)w, 1));
+        who.push_back(cases[k]);
         rem[k] -= w;
       }
-    if (roles.size() == win_off.back()) break;
-    win_off.push_back(roles.size());
+    if (roles.size() == lo) break;
+    wins.push_back({lo, roles.size()});
   }
+  const size_t ends = roles.size();
+  for (size_t k = 0; k < cases.size(); ++k)
+    if (left[k] > 0 && !cases[k]->est_pending) {
+      roles.push_back(role(cases[k], 0, 1));
+      who.push_back(cases[k]);
+    }
   int r = EDP_OK;
   if (!roles.empty()) {
     if (roles.size() > ctx->small_cap) {
@@ -1042,22 +1121,24 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
     }
     HIPCHK(hipMemcpyAsync(ctx->small_roles, roles.data(), roles.size() * sizeof(BlockRole), hipMemcpyHostToDevice, st));
   }
-  for (size_t win = 0; win + 1 < win_off.size() && r == EDP_OK; ++win) {
-    const size_t lo = win_off[win], hi = win_off[win + 1];
-    for (size_t a = lo; a < hi && r == EDP_OK; ++a) {
-      Case* c = nullptr;
-      for (Case* q : cases)
-        if (q->d == roles[a].c) c = q;
-      r = upload_volt(c, c->step, c->step + roles[a].j, st);
+  for (size_t k = 0; k < wins.size() && r == EDP_OK; ++k) {
+    const Win& W = wins[k];
+    for (size_t a = W.lo; a < W.hi && r == EDP_OK; ++a) {
+      r = stage_volt(who[a], who[a]->step, who[a]->step + roles[a].j);
+      who[a]->v_ev = ctx->small_join;
     }
     if (r) break;
-    HIPCHK(launch_small(ctx->small_roles + lo, (int)(hi - lo), lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
-    for (size_t a = lo; a < hi && r == EDP_OK; ++a)
-      for (Case* q : cases)
-        if (q->d == roles[a].c) {
-          q->step += roles[a].j;
-          r = request_estimate(q, st);
-        }
+    HIPCHK(launch_small_volt(ctx->small_roles + W.lo, (int)(W.hi - W.lo), st));
+    HIPCHK(launch_small(ctx->small_roles + W.lo, (int)(W.hi - W.lo), lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
+    for (size_t a = W.lo; a < W.hi; ++a) who[a]->step += roles[a].j;
+    HIPCHK(hipEventRecord(ctx->small_join, st));  // the staging of this window and before is free
+  }
+  if (r == EDP_OK && roles.size() > ends) {
+    HIPCHK(launch_small_end(ctx->small_roles + ends, (int)(roles.size() - ends), st));
+    for (size_t a = ends; a < roles.size(); ++a) {
+      who[a]->est_wait = ctx->small_join;
+      who[a]->est_pending = true;
+    }
   }
   const hipError_t e = hipEventRecord(ctx->small_join, st);
   const hipError_t w = e == hipSuccess ? hipStreamWaitEvent(ctx->stream, ctx->small_join, 0) : e;
@@ -1233,18 +1314,8 @@ int deposit_species(edp_ctx* ctx, Case* c, int sp, int64_t step) {
 }
 
 int zero_diag(edp_ctx* ctx, Case* c) {
-  hipStream_t st = ctx->stream;
-  const int64_t ng = c->desc.n_grid;
-  for (double* p : {c->h.sum_ne, c->h.sum_ni, c->h.sum_je, c->h.sum_ji, c->h.sum_w, c->h.sum_e})
-    HIPCHK(launch_zero(p, ng * 8, st));
-  for (int64_t* p : {c->h.acc_je, c->h.acc_ji, c->h.acc_w, c->h.acc_e, c->h.acc_wi, c->h.acc_ei, c->h.acc_iz})
-    HIPCHK(launch_zero(p, 3 * ng * 8, st));
-  HIPCHK(launch_zero(c->h.eepf, (int64_t)std::max(1, c->desc.n_eepf) * 8, st));
-  if (c->h.n_xt > 0) {
-    HIPCHK(launch_zero(c->h.xt, (int64_t)kNumXt * c->h.n_xt * ng * 8, st));
-    HIPCHK(launch_zero(c->h.xt_cnt, (int64_t)2 * c->h.n_xt * 8, st));
-  }
-  if (c->h.n_ifed > 0) HIPCHK(launch_zero(c->h.ifed, (int64_t)2 * (c->h.n_ifed + 1) * 8, st));
+  // the sums, the steps' accumulators and the histograms lie in a row
+  HIPCHK(launch_zero(c->h.sum_ne, (char*)c->h.sort_cnt - (char*)c->h.sum_ne, ctx->stream));
   return EDP_OK;
 }
 
@@ -1345,14 +1416,15 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
   // fork/join events
   bool ok = hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) == hipSuccess &&
             hipStreamCreateWithFlags(&ctx->small_stream, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess;
+            hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess &&
+            hipHostMalloc((void**)&ctx->pin, kPinBytes, hipHostMallocDefault) == hipSuccess;
   for (int g = 0; g < kSide && ok; ++g)
     ok = hipStreamCreateWithFlags(&ctx->side[g], hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&ctx->side_end[g], hipEventDisableTiming) == hipSuccess;
   if (!ok) {
     destroy_streams(ctx);
     delete ctx;
-    return fail(EDP_EHIP, "creating the groups' streams or events failed");
+    return fail(EDP_EHIP, "creating the groups' streams, events or staging failed");
   }
   // the allocation-free advance's table: this device's scratch array
   BlockRole* sp = nullptr;
@@ -1379,6 +1451,7 @@ int edp_destroy(edp_ctx* ctx) {
     if (G.last) (void)hipEventDestroy(G.last);
   }
   if (ctx->small_roles) (void)hipFree(ctx->small_roles);
+  if (ctx->pin_state) (void)hipHostFree(ctx->pin_state);
   destroy_streams(ctx);
   for (auto& kv : ctx->cases) {
     Case* c = kv.second;
@@ -1558,6 +1631,10 @@ int edp_case_create(edp_ctx* ctx, const edp_case_desc* desc, void* dev_arena, in
       hipEventCreateWithFlags(&c->vev, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->est_ev, hipEventDisableTiming) != hipSuccess)
     return cleanup(fail(EDP_EHIP, "host staging allocation failed"));
+  c->est_wait = c->est_ev;
+  if (hipHostGetDevicePointer((void**)&h.volt_host, c->vstage, 0) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&h.est_host, c->est_pinned, 0) != hipSuccess)
+    return cleanup(fail(EDP_EHIP, "host staging is not visible to the device"));
   // zero the whole grid/diagnostic/scratch region, then upload
   const size_t z0 = L.off_cnt_e, z1 = L.total;
   if (launch_zero(c->arena + z0, (int64_t)(z1 - z0), st) != hipSuccess)
@@ -1801,11 +1878,9 @@ int edp_read_density(edp_ctx* ctx, edp_case id, double* ne, double* ni, int32_t 
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   CaseDev t;
-  int r = read_dyn(ctx, c, t);
-  if (r) return r;
   std::vector<double> a(ng), b(ng);
-  if ((r = read_grid(ctx, c, c->h.sum_ne, a.data(), ng * 8)) || (r = read_grid(ctx, c, c->h.sum_ni, b.data(), ng * 8)))
-    return r;
+  const int r = read_parts(ctx, c, {dyn_part(c, t), {c->h.sum_ne, a.data(), (size_t)ng}, {c->h.sum_ni, b.data(), (size_t)ng}});
+  if (r) return r;
   const double steps = t.diag_steps > 0 ? (double)t.diag_steps : 1.0;
   for (int p = 0; p < ng; ++p) {
     ne[p] = a[p] / steps;
@@ -1839,11 +1914,9 @@ int edp_read_currents(edp_ctx* ctx, edp_case id, double* je, double* ji, int32_t
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   HIPCHK(launch_fold(c->d, ctx->stream));
   CaseDev t;
-  int r = read_dyn(ctx, c, t);
-  if (r) return r;
   std::vector<double> a(ng), b(ng);
-  if ((r = read_grid(ctx, c, c->h.sum_je, a.data(), ng * 8)) || (r = read_grid(ctx, c, c->h.sum_ji, b.data(), ng * 8)))
-    return r;
+  const int r = read_parts(ctx, c, {dyn_part(c, t), {c->h.sum_je, a.data(), (size_t)ng}, {c->h.sum_ji, b.data(), (size_t)ng}});
+  if (r) return r;
   const double ns = t.diag_steps > 0 ? (double)t.diag_steps : 1.0;
   const double ni = t.diag_ion_steps > 0 ? (double)t.diag_ion_steps : 1.0;
   for (int p = 0; p < ng; ++p) {
@@ -1861,9 +1934,8 @@ int edp_read_mean_energy(edp_ctx* ctx, edp_case id, double* mee, int32_t n, int3
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   HIPCHK(launch_fold(c->d, ctx->stream));
   std::vector<double> w(ng), e(ng);
-  int r;
-  if ((r = read_grid(ctx, c, c->h.sum_w, w.data(), ng * 8)) || (r = read_grid(ctx, c, c->h.sum_e, e.data(), ng * 8)))
-    return r;
+  const int r = read_parts(ctx, c, {{c->h.sum_w, w.data(), (size_t)ng}, {c->h.sum_e, e.data(), (size_t)ng}});
+  if (r) return r;
   for (int p = 0; p < ng; ++p) mee[p] = w[p] > 0.0 ? (e[p] / kDiagES) / (w[p] / kDiagWS) : 0.0;
   return after_read(ctx, c, reset);
 }
@@ -2088,12 +2160,7 @@ int edp_read_deposit(edp_ctx* ctx, edp_case id, int64_t* cnt_e, int64_t* cnt_i, 
   if (!c || !cnt_e || !cnt_i) return fail(EDP_EINVAL, "bad argument");
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
-  CaseDev t;
-  int r = read_dyn(ctx, c, t);
-  if (r) return r;
-  const int64_t s = t.step, k = s / c->desc.ion_subcycle;
-  if ((r = read_grid(ctx, c, c->h.cnt_e + (s % 3) * ng, cnt_e, ng * 8))) return r;
-  return read_grid(ctx, c, c->h.cnt_i + (k % 3) * ng, cnt_i, ng * 8);
+  return read_parts(ctx, c, {{c->h.cnt_e, cnt_e, (size_t)ng, 1}, {c->h.cnt_i, cnt_i, (size_t)ng, 2}});
 }
 
 int edp_read_fields(edp_ctx* ctx, edp_case id, double* rho, double* phi, double* ef, int32_t n) {
@@ -2101,16 +2168,20 @@ int edp_read_fields(edp_ctx* ctx, edp_case id, double* rho, double* phi, double*
   if (!c) return fail(EDP_EINVAL, "bad argument");
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
-  int r;
-  if (rho && (r = read_grid(ctx, c, c->h.rho, rho, ng * 8))) return r;
-  if (ef && (r = read_grid(ctx, c, c->h.efield, ef, ng * 8))) return r;
+  CaseDev t;
+  std::vector<double> a(ng), b(ng), ph(ng), f(ng);
+  const size_t w = (size_t)ng;
+  const int r = read_parts(ctx, c, {dyn_part(c, t), {c->h.rho, a.data(), w}, {c->h.efield, b.data(), w},
+                                    {c->h.phi, ph.data(), w}, {c->h.flux, f.data(), w}});
+  if (r) return r;
+  if (rho) std::copy(a.begin(), a.end(), rho);
+  if (ef) std::copy(b.begin(), b.end(), ef);
   if (phi) {
-    CaseDev t;
-    if ((r = read_dyn(ctx, c, t))) return r;
-    if (t.phi_valid) return read_grid(ctx, c, c->h.phi, phi, ng * 8);
+    if (t.phi_valid) {
+      std::copy(ph.begin(), ph.end(), phi);
+      return EDP_OK;
+    }
     // the flux solver keeps F_q = phi_q - phi_{q+1} and V; sum them back up
-    std::vector<double> f(ng);
-    if ((r = read_grid(ctx, c, c->h.flux, f.data(), ng * 8))) return r;
     phi[0] = f[ng - 1];
     for (int p = 1; p < ng - 1; ++p) phi[p] = phi[p - 1] - f[p - 1];
     phi[ng - 1] = 0.0;
@@ -2128,26 +2199,30 @@ int edp_get_state(edp_ctx* ctx, edp_case id, int32_t species, double* x, double*
   const int64_t n = t.alloc[species] < c->h.sp[species].cap ? t.alloc[species] : c->h.sp[species].cap;
   const int set = t.cur[species];
   const SpeciesDev& S = c->h.sp[species];
-  std::vector<double> hx(n), hvx(n), hvy(n), hvz(n);
-  std::vector<uint64_t> hu(n);
-  if (n > 0) {
-    HIPCHK(hipMemcpy(hx.data(), S.x[set], n * 8, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hvx.data(), S.vx[set], n * 8, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hvy.data(), S.vy[set], n * 8, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hvz.data(), S.vz[set], n * 8, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hu.data(), S.uid[set], n * 8, hipMemcpyDeviceToHost));
-  }
+  std::lock_guard<std::mutex> lock(ctx->pin_mu);
+  if ((r = state_buffer(ctx))) return r;
+  double *hx = (double*)ctx->pin_state, *hvx = hx + kStateChunk, *hvy = hvx + kStateChunk, *hvz = hvy + kStateChunk;
+  uint64_t* hu = (uint64_t*)(hvz + kStateChunk);
   int64_t m = 0;
-  for (int64_t i = 0; i < n; ++i) {
-    if (!(hx[i] == hx[i])) continue;
-    if (m < cap) {
-      if (x) x[m] = hx[i];
-      if (vx) vx[m] = hvx[i];
-      if (vy) vy[m] = hvy[i];
-      if (vz) vz[m] = hvz[i];
-      if (uid) uid[m] = hu[i];
+  for (int64_t i0 = 0; i0 < n; i0 += kStateChunk) {
+    const int64_t w = std::min(kStateChunk, n - i0);
+    HIPCHK(hipMemcpyAsync(hx, S.x[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipMemcpyAsync(hvx, S.vx[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipMemcpyAsync(hvy, S.vy[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipMemcpyAsync(hvz, S.vz[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipMemcpyAsync(hu, S.uid[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    for (int64_t i = 0; i < w; ++i) {
+      if (!(hx[i] == hx[i])) continue;
+      if (m < cap) {
+        if (x) x[m] = hx[i];
+        if (vx) vx[m] = hvx[i];
+        if (vy) vy[m] = hvy[i];
+        if (vz) vz[m] = hvz[i];
+        if (uid) uid[m] = hu[i];
+      }
+      ++m;
     }
-    ++m;
   }
   if (n_out) *n_out = m;
   return EDP_OK;
@@ -2173,16 +2248,29 @@ int edp_set_state(edp_ctx* ctx, edp_case id, int32_t species, const double* x, c
   int r = read_dyn(ctx, c, t);
   if (r) return r;
   if (n > 0) {
-    HIPCHK(hipMemcpy(S.x[0], x, n * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(S.vx[0], vx, n * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(S.vy[0], vy, n * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(S.vz[0], vz, n * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(S.uid[0], uid, n * 8, hipMemcpyHostToDevice));
-    if (species == 0) {
-      // the float bound of vy*vy + vz*vz every kernel writer keeps
-      std::vector<float> p2((size_t)n);
-      for (int64_t i = 0; i < n; ++i) p2[i] = float_above(vy[i] * vy[i] + vz[i] * vz[i]);
-      HIPCHK(hipMemcpy(S.vp2[0], p2.data(), n * 4, hipMemcpyHostToDevice));
+    std::lock_guard<std::mutex> lock(ctx->pin_mu);
+    if ((r = state_buffer(ctx))) return r;
+    for (int64_t i0 = 0; i0 < n; i0 += kStateChunk) {
+      const int64_t w = std::min(kStateChunk, n - i0);
+      char* at = ctx->pin_state;
+      auto put = [&](void* dev, const void* host, size_t bytes) {
+        std::memcpy(at, host, bytes);
+        const hipError_t e = hipMemcpyAsync(dev, at, bytes, hipMemcpyHostToDevice, ctx->stream);
+        at += kStateChunk * 8;
+        return e;
+      };
+      HIPCHK(put(S.x[0] + i0, x + i0, w * 8));
+      HIPCHK(put(S.vx[0] + i0, vx + i0, w * 8));
+      HIPCHK(put(S.vy[0] + i0, vy + i0, w * 8));
+      HIPCHK(put(S.vz[0] + i0, vz + i0, w * 8));
+      HIPCHK(put(S.uid[0] + i0, uid + i0, w * 8));
+      if (species == 0) {
+        // the float bound of vy*vy + vz*vz every kernel writer keeps
+        float* p2 = (float*)at;
+        for (int64_t i = 0; i < w; ++i) p2[i] = float_above(vy[i0 + i] * vy[i0 + i] + vz[i0 + i] * vz[i0 + i]);
+        HIPCHK(hipMemcpyAsync(S.vp2[0] + i0, p2, w * 4, hipMemcpyHostToDevice, ctx->stream));
+      }
+      HIPCHK(hipStreamSynchronize(ctx->stream));
     }
   }
   t.step = step;

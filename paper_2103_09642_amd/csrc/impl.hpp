@@ -130,6 +130,10 @@ struct CaseDev {
   const double *nsig_e, *nsig_i, *sig_el, *sig_exc, *sig_ion, *sig_iso, *sig_back;
   const double *rden;   // Thomas reciprocals r_p, p = 0..ng-1 (r_0 unused)
   const double *volt;   // V(t_s) at volt[s % kVoltChunk]
+  // the host's pinned copies: V(t_s) at the same places, and alloc[] .. ctr[]
+  // as of the last window of the small-case kernel (see k_small_volt, k_small_end)
+  const double* volt_host;
+  int64_t* est_host;
   int64_t *cnt_e;       // [3][ng] electron deposit, ring by step % 3
   int64_t *cnt_i;       // [3][ng] ion deposit, ring by (step / nsub) % 3
   double *rho, *phi, *efield;
@@ -197,6 +201,19 @@ struct BlockRole {
   // chunks of a step (consecutive workgroups share their bounds, the first
   // starts at 0 and the last ends at 2^31)
   uint32_t f_lo, f_hi;
+};
+
+// Parts of a case's memory gathered into pinned host memory by one launch.
+// sel: 0 n words at src; 1 and 2 row (step % 3) or ((step / nsub) % 3) of n
+// words, with the case's step: the deposit ring the next step reads.
+struct GatherPart {
+  const int64_t* src;
+  int64_t* dst;
+  int32_t n, sel;
+};
+constexpr int kGatherMax = 6;
+struct GatherParts {
+  GatherPart p[kGatherMax];
 };
 
 }  // namespace edp

@@ -2243,6 +2243,35 @@ __global__ void k_zero(int64_t* __restrict__ p, int64_t n) {
     p[i] = 0;
 }
 
+// Workgroup b copies part b (see GatherPart).  The destination is host
+// memory: a result of a few KiB leaves in one launch and one wait, where a
+// copy of each part took about 15 us.
+__global__ void __launch_bounds__(kBlock) k_gather(const CaseDev* __restrict__ C, GatherParts P) {
+  const GatherPart& q = P.p[blockIdx.x];
+  const int64_t s = C->step;
+  const int64_t row = q.sel == 0 ? 0 : (q.sel == 1 ? s : s / C->nsub) % 3;
+  const int64_t* __restrict__ src = q.src + row * q.n;
+  for (int i = threadIdx.x; i < q.n; i += kBlock) q.dst[i] = src[i];
+}
+
+// Before a window of the small-case kernel: workgroup b takes V(t) of role
+// b's role.j steps from the host's copy into the case's ring.
+__global__ void __launch_bounds__(kBlock) k_small_volt(const BlockRole* __restrict__ R) {
+  const BlockRole& r = R[blockIdx.x];
+  const double* __restrict__ src = r.c->volt_host;
+  double* dst = const_cast<double*>(r.c->volt);
+  const int64_t s0 = r.c->step;
+  for (int i = threadIdx.x; i < r.j; i += kBlock) dst[(s0 + i) % kVoltChunk] = src[(s0 + i) % kVoltChunk];
+}
+
+// After a case's last window: its slot counts and counters for the host's
+// launch sizes.
+__global__ void __launch_bounds__(kWave) k_small_end(const BlockRole* __restrict__ R) {
+  constexpr int n = (int)((offsetof(CaseDev, ctr) - offsetof(CaseDev, alloc)) / 8) + kNumCtr;
+  const CaseDev* C = R[blockIdx.x].c;
+  for (int i = threadIdx.x; i < n; i += kWave) C->est_host[i] = ((const int64_t*)C->alloc)[i];
+}
+
 // ---------------------------------------------------------------------------
 // Host-side launchers (same translation unit as the kernels).
 // ---------------------------------------------------------------------------
@@ -2350,6 +2379,21 @@ hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode,
     hipLaunchKernelGGL(k_small<1>, dim3(ncase), dim3(kBlock), lds, st, roles, sort_every, pretest);
   else
     hipLaunchKernelGGL(k_small<0>, dim3(ncase), dim3(kBlock), lds, st, roles, sort_every, pretest);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, hipStream_t st) {
+  hipLaunchKernelGGL(k_gather, dim3(n), dim3(kBlock), 0, st, c, P);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_volt(const BlockRole* roles, int ncase, hipStream_t st) {
+  hipLaunchKernelGGL(k_small_volt, dim3(ncase), dim3(kBlock), 0, st, roles);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_end(const BlockRole* roles, int ncase, hipStream_t st) {
+  hipLaunchKernelGGL(k_small_end, dim3(ncase), dim3(kWave), 0, st, roles);
   return hipGetLastError();
 }
 

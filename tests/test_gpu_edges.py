@@ -89,3 +89,30 @@ def test_blocks_and_side_by_side_groups(ctx, mode, n):
         for (ca, da), (cb, db) in zip(got[1], got[groups]):
             assert ca == cb
             assert all(np.array_equal(x, y) for x, y in zip(da, db))
+
+
+@pytest.mark.parametrize("cases,steps", [(200, 700), (1, 70_001)], ids=["short-first-windows", "voltage-ring-wraps"])
+def test_small_windows_equal_lockstep(ctx, cases, steps):
+    """Persistent small cases over several windows, the first ones short for
+    many cases, and over more steps than the voltage ring holds: the lockstep
+    launches' densities, counters and last potential."""
+    from paper_2103_09642_amd import edupic
+    say(f"test_small_windows_equal_lockstep cases={cases} steps={steps}")
+    got = []
+    try:
+        for small in (0, 1 << 20):
+            ctx.set_option(edupic.OPT_SMALL_MAX, small)
+            gs = [ctx.create_case(base_case(n_init_e=40 + k % 50, n_init_i=60, n_grid=20 + k % 7, weight=10.0, ion_subcycle=3,
+                                            cap_e=5_000, cap_i=5_000, seed=k, pressure_pa=5.0, flags=["allow_unstable"]))
+                  for k in range(cases)]
+            part = 300 + steps % 7
+            ctx.advance_steps(gs, [part] * cases)
+            ctx.advance_steps(gs, [steps - part - (k % 3) for k in range(cases)])
+            got.append([(g.counts(), g.deposit(), g.fields()) for g in gs])
+            for g in gs:
+                g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_SMALL_MAX, 0)
+    for (ca, da, fa), (cb, db, fb) in zip(*got):
+        assert ca == cb
+        assert all(np.array_equal(x, y) for x, y in zip(da + fa, db + fb))

@@ -32,7 +32,7 @@ hipError_t launch_window_end(const BlockRole* cases, int ncase, int steps, hipSt
 size_t particle_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed, int sp);
 size_t particle_static_lds(int sp, int nb);
 int particle_occupancy(int sp, int nb, size_t lds);
-hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, hipStream_t st);
+hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, int blocks, hipStream_t st);
 hipError_t launch_small_volt(const BlockRole* roles, int ncase, hipStream_t st);
 hipError_t launch_small_end(const BlockRole* roles, int ncase, hipStream_t st);
 hipError_t launch_seed(CaseDev* d, int sp, int64_t n, double sigma, hipStream_t st);
@@ -188,11 +188,7 @@ struct edp_ctx {
   // persistent one-workgroup-per-case kernel (0: none)
   int64_t small_max = 0;
   // the persistent small cases' stream (default priority) and role table
-  // pinned staging of the reads (kPinBytes) and, from the first one on, of state
-  // transfers (kStateBytes); one lock for both (reads of several threads)
-  char* pin = nullptr;
-  char* pin_state = nullptr;
-  std::mutex pin_mu;
+  std::mutex pin_mu;  // the cases' pinned staging in reads and state transfers (of several threads)
   hipStream_t small_stream = nullptr;
   hipEvent_t small_join = nullptr;
   BlockRole* small_roles = nullptr;
@@ -436,15 +432,16 @@ constexpr size_t kDynOff = offsetof(CaseDev, step);
 constexpr size_t kDynBytes = sizeof(CaseDev) - kDynOff;
 static_assert(kDynOff % 8 == 0 && kDynBytes % 8 == 0, "read in words");
 
-constexpr size_t kPinBytes = (size_t)256 << 10;
+// Reads and state transfers go through the case's pinned staging of V(t): after
+// the wait for the context's stream nothing is on its way from it, and what it
+// held is on the device (a staging of their own would be one more pinned
+// allocation, a few tenths of a millisecond, in a first pass).
+constexpr size_t kPinBytes = (size_t)kVoltChunk * 8;
 static_assert(kPinBytes >= kDynBytes + 4 * kMaxNodes * 8, "the largest read of parts");
-// Slots of a state transfer through its staging at a time, of 48 bytes.
-constexpr int64_t kStateChunk = 1 << 14;
-constexpr size_t kStateBytes = (size_t)kStateChunk * 48;
-int state_buffer(edp_ctx* ctx) {  // with pin_mu held
-  if (!ctx->pin_state) HIPCHK(hipHostMalloc((void**)&ctx->pin_state, kStateBytes, hipHostMallocDefault));
-  return EDP_OK;
-}
+// Slots of a state transfer at a time, of 48 bytes.
+constexpr int64_t kStateChunk = 10240;
+static_assert((size_t)kStateChunk * 48 <= kPinBytes && kStateChunk % 2 == 0, "a chunk of every array");
+constexpr int kStateBlocks = 16;  // workgroups per array of a transfer
 
 // Parts of a case's device memory (n words each, see GatherPart) to the host,
 // after all work on the context's stream: one launch into pinned memory and
@@ -462,13 +459,17 @@ int read_parts(edp_ctx* ctx, Case* c, std::initializer_list<ReadPart> parts) {
   int k = 0;
   for (const ReadPart& q : parts) {
     if (k >= kGatherMax || (at + q.n) * 8 > kPinBytes) return fail(EDP_EINVAL, "internal: read exceeds the staging");
-    P.p[k++] = GatherPart{(const int64_t*)q.dev, (int64_t*)ctx->pin + at, (int32_t)q.n, q.sel};
+    P.p[k++] = GatherPart{(const int64_t*)q.dev, (int64_t*)c->h.volt_host + at, (int32_t)q.n, q.sel};
     at += q.n;
   }
-  HIPCHK(launch_gather(c->d, P, k, ctx->stream));
+  HIPCHK(launch_gather(c->d, P, k, 1, ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
-  k = 0;
-  for (const ReadPart& q : parts) std::memcpy(q.host, P.p[k++].dst, q.n * 8);
+  c->v_ev = nullptr;
+  at = 0;
+  for (const ReadPart& q : parts) {
+    std::memcpy(q.host, c->vstage + at, q.n * 8);
+    at += q.n;
+  }
   return EDP_OK;
 }
 // The case's dynamic part as one of the parts of a read.
@@ -622,8 +623,6 @@ void destroy_streams(edp_ctx* ctx) {
   if (ctx->small_join) (void)hipEventDestroy(ctx->small_join);
   ctx->small_stream = nullptr;
   ctx->small_join = nullptr;
-  if (ctx->pin) (void)hipHostFree(ctx->pin);
-  ctx->pin = nullptr;
   for (int g = 0; g < kSide; ++g) {
     if (ctx->side[g]) (void)hipStreamDestroy(ctx->side[g]);
     if (ctx->side_end[g]) (void)hipEventDestroy(ctx->side_end[g]);
@@ -1416,15 +1415,14 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
   // fork/join events
   bool ok = hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) == hipSuccess &&
             hipStreamCreateWithFlags(&ctx->small_stream, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess &&
-            hipHostMalloc((void**)&ctx->pin, kPinBytes, hipHostMallocDefault) == hipSuccess;
+            hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess;
   for (int g = 0; g < kSide && ok; ++g)
     ok = hipStreamCreateWithFlags(&ctx->side[g], hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&ctx->side_end[g], hipEventDisableTiming) == hipSuccess;
   if (!ok) {
     destroy_streams(ctx);
     delete ctx;
-    return fail(EDP_EHIP, "creating the groups' streams, events or staging failed");
+    return fail(EDP_EHIP, "creating the groups' streams or events failed");
   }
   // the allocation-free advance's table: this device's scratch array
   BlockRole* sp = nullptr;
@@ -1451,7 +1449,6 @@ int edp_destroy(edp_ctx* ctx) {
     if (G.last) (void)hipEventDestroy(G.last);
   }
   if (ctx->small_roles) (void)hipFree(ctx->small_roles);
-  if (ctx->pin_state) (void)hipHostFree(ctx->pin_state);
   destroy_streams(ctx);
   for (auto& kv : ctx->cases) {
     Case* c = kv.second;
@@ -2200,17 +2197,17 @@ int edp_get_state(edp_ctx* ctx, edp_case id, int32_t species, double* x, double*
   const int set = t.cur[species];
   const SpeciesDev& S = c->h.sp[species];
   std::lock_guard<std::mutex> lock(ctx->pin_mu);
-  if ((r = state_buffer(ctx))) return r;
-  double *hx = (double*)ctx->pin_state, *hvx = hx + kStateChunk, *hvy = hvx + kStateChunk, *hvz = hvy + kStateChunk;
+  double *hx = c->vstage, *hvx = hx + kStateChunk, *hvy = hvx + kStateChunk, *hvz = hvy + kStateChunk;
   uint64_t* hu = (uint64_t*)(hvz + kStateChunk);
   int64_t m = 0;
   for (int64_t i0 = 0; i0 < n; i0 += kStateChunk) {
     const int64_t w = std::min(kStateChunk, n - i0);
-    HIPCHK(hipMemcpyAsync(hx, S.x[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(hvx, S.vx[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(hvy, S.vy[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(hvz, S.vz[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(hu, S.uid[set] + i0, w * 8, hipMemcpyDeviceToHost, ctx->stream));
+    GatherParts P{};
+    const double* from[4] = {S.x[set] + i0, S.vx[set] + i0, S.vy[set] + i0, S.vz[set] + i0};
+    int64_t* to = (int64_t*)c->h.volt_host;
+    for (int a = 0; a < 4; ++a) P.p[a] = GatherPart{(const int64_t*)from[a], to + a * kStateChunk, (int32_t)w, 0};
+    P.p[4] = GatherPart{(const int64_t*)(S.uid[set] + i0), to + 4 * kStateChunk, (int32_t)w, 0};
+    HIPCHK(launch_gather(c->d, P, 5, kStateBlocks, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     for (int64_t i = 0; i < w; ++i) {
       if (!(hx[i] == hx[i])) continue;
@@ -2249,27 +2246,27 @@ int edp_set_state(edp_ctx* ctx, edp_case id, int32_t species, const double* x, c
   if (r) return r;
   if (n > 0) {
     std::lock_guard<std::mutex> lock(ctx->pin_mu);
-    if ((r = state_buffer(ctx))) return r;
     for (int64_t i0 = 0; i0 < n; i0 += kStateChunk) {
       const int64_t w = std::min(kStateChunk, n - i0);
-      char* at = ctx->pin_state;
-      auto put = [&](void* dev, const void* host, size_t bytes) {
-        std::memcpy(at, host, bytes);
-        const hipError_t e = hipMemcpyAsync(dev, at, bytes, hipMemcpyHostToDevice, ctx->stream);
-        at += kStateChunk * 8;
-        return e;
-      };
-      HIPCHK(put(S.x[0] + i0, x + i0, w * 8));
-      HIPCHK(put(S.vx[0] + i0, vx + i0, w * 8));
-      HIPCHK(put(S.vy[0] + i0, vy + i0, w * 8));
-      HIPCHK(put(S.vz[0] + i0, vz + i0, w * 8));
-      HIPCHK(put(S.uid[0] + i0, uid + i0, w * 8));
-      if (species == 0) {
-        // the float bound of vy*vy + vz*vz every kernel writer keeps
-        float* p2 = (float*)at;
-        for (int64_t i = 0; i < w; ++i) p2[i] = float_above(vy[i0 + i] * vy[i0 + i] + vz[i0 + i] * vz[i0 + i]);
-        HIPCHK(hipMemcpyAsync(S.vp2[0] + i0, p2, w * 4, hipMemcpyHostToDevice, ctx->stream));
+      const void* from[5] = {x + i0, vx + i0, vy + i0, vz + i0, uid + i0};
+      void* to[5] = {S.x[0] + i0, S.vx[0] + i0, S.vy[0] + i0, S.vz[0] + i0, S.uid[0] + i0};
+      const int64_t* src = (const int64_t*)c->h.volt_host;
+      GatherParts P{};
+      int k = 0;
+      for (; k < 5; ++k) {
+        std::memcpy(c->vstage + k * kStateChunk, from[k], w * 8);
+        P.p[k] = GatherPart{src + k * kStateChunk, (int64_t*)to[k], (int32_t)w, 0};
       }
+      if (species == 0) {
+        // the float bound of vy*vy + vz*vz every kernel writer keeps, two to a
+        // word (the slot after the last, if any, is not in use)
+        float* p2 = (float*)(c->vstage + k * kStateChunk);
+        for (int64_t i = 0; i < w; ++i) p2[i] = float_above(vy[i0 + i] * vy[i0 + i] + vz[i0 + i] * vz[i0 + i]);
+        if (w % 2) p2[w] = 0.0f;
+        P.p[k] = GatherPart{src + k * kStateChunk, (int64_t*)(S.vp2[0] + i0), (int32_t)((w + 1) / 2), 0};
+        ++k;
+      }
+      HIPCHK(launch_gather(c->d, P, k, kStateBlocks, ctx->stream));
       HIPCHK(hipStreamSynchronize(ctx->stream));
     }
   }

@@ -2258,15 +2258,15 @@ __global__ void k_zero(int64_t* __restrict__ p, int64_t n) {
     p[i] = 0;
 }
 
-// Workgroup b copies part b (see GatherPart).  The destination is host
-// memory: a result of a few KiB leaves in one launch and one wait, where a
-// copy of each part took about 15 us.
+// Workgroups (b, *) copy part b (see GatherPart).  One side is host memory: a
+// result of a few KiB leaves in one launch and one wait, where a copy of each
+// part took about 15 us.
 __global__ void __launch_bounds__(kBlock) k_gather(const CaseDev* __restrict__ C, GatherParts P) {
   const GatherPart& q = P.p[blockIdx.x];
   const int64_t s = C->step;
   const int64_t row = q.sel == 0 ? 0 : (q.sel == 1 ? s : s / C->nsub) % 3;
   const int64_t* __restrict__ src = q.src + row * q.n;
-  for (int i = threadIdx.x; i < q.n; i += kBlock) q.dst[i] = src[i];
+  for (int i = (int)(blockIdx.y * kBlock + threadIdx.x); i < q.n; i += (int)gridDim.y * kBlock) q.dst[i] = src[i];
 }
 
 // Before a window of the small-case kernel: workgroup b takes V(t) of role
@@ -2397,8 +2397,8 @@ hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode,
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather, dim3(n), dim3(kBlock), 0, st, c, P);
+hipError_t launch_gather(const CaseDev* c, const GatherParts& P, int n, int blocks, hipStream_t st) {
+  hipLaunchKernelGGL(k_gather, dim3(n, blocks), dim3(kBlock), 0, st, c, P);
   return hipGetLastError();
 }
 

@@ -42,7 +42,7 @@ hipError_t launch_sort(const BlockRole* roles, const BlockRole* case_roles, int 
                        int every, int dstep, hipStream_t st);
 hipError_t launch_fold(CaseDev* d, hipStream_t st);
 size_t small_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed);
-size_t small_static_lds();
+size_t small_static_lds(int nb);
 hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode, int sort_every, int pretest,
                         hipStream_t st);
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t st);
@@ -1057,7 +1057,7 @@ int group_window(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::v
 bool small_case(const edp_ctx* ctx, const Case* c) {
   if (ctx->small_max <= 0 || std::max(c->est[0], c->est[1]) > ctx->small_max) return false;
   const edp_case_desc& D = c->desc;
-  return small_lds_bytes(D.n_grid, D.flags, D.n_eepf, D.n_ifed) + small_static_lds() <= 65536;
+  return small_lds_bytes(D.n_grid, D.flags, D.n_eepf, D.n_ifed) + small_static_lds(256) <= 65536;
 }
 
 // The persistent small cases of an advance, on the context's small-case

@@ -395,6 +395,15 @@ struct StepIndex {
       k3 = (int)(k % 3);
     }
   }
+  // of the next step
+  __device__ __forceinline__ void next(int nsub) {
+    s3 = s3 == 2 ? 0 : s3 + 1;
+    if (++sub == nsub) {
+      sub = 0;
+      ++k;
+      k3 = k3 == 2 ? 0 : k3 + 1;
+    }
+  }
 };
 
 // The constants of a field solve.
@@ -1046,11 +1055,8 @@ struct PassIn {
   }
 };
 
-// Totals of one species' step in one workgroup (kRec fields, summed over the
-// waves): in the small-case kernel v, in every thread; in a lockstep launch
-// the wave's own, field f in lane f.
+// A wave's totals of one species' step (kRec fields): field f in lane f.
 struct SpTot {
-  int v[kRec];
   int field;
 };
 
@@ -1076,7 +1082,6 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   __shared__ int32_t sSeg[NB / kWave][kSeg];
   __shared__ double sVx[kPay][SP == 0 ? kSeg : 1];
   __shared__ uint64_t sUid[kPay][SP == 0 ? kSeg : 1];
-  __shared__ int sTot[SMALL ? NB / kWave : 1][kRec];
   // entries of the overflow list, next pass over it
   __shared__ int sOvf, sFin;
   // the pre-test's bound of P by energy block (direct collision test), as
@@ -1666,24 +1671,11 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
       if (sF[b]) gl_add(&hist[b], (long long)sF[b]);
   const int v[kRec] = {t_coll, t_ioniz, t_pow, t_gnd, t_live, t_be, t_bi, t_drop};
   SpTot T;
-  if constexpr (SMALL) {
-    if (lane == 0)
+  // lane f has field f
+  T.field = 0;
 #pragma unroll
-      for (int f = 0; f < kRec; ++f) sTot[w][f] = v[f];
-    __syncthreads();
-#pragma unroll
-    for (int f = 0; f < kRec; ++f) T.v[f] = 0;
-#pragma unroll 1
-    for (int u = 0; u < NB / kWave; ++u)
-#pragma unroll
-      for (int f = 0; f < kRec; ++f) T.v[f] += sTot[u][f];
-    __syncthreads();  // sTot, the segments and the histograms are free again
-  } else {
-    // lane f has field f
-    T.field = 0;
-#pragma unroll
-    for (int f = 0; f < kRec; ++f) T.field = lane == f ? v[f] : T.field;
-  }
+  for (int f = 0; f < kRec; ++f) T.field = lane == f ? v[f] : T.field;
+  if (SMALL) __syncthreads();  // the segments and the histograms are free again
   return T;
 }
 
@@ -1866,6 +1858,7 @@ __device__ __forceinline__ int cell_of(double x, double inv_dx, int ng) {
 // Compaction + counting sort by cell of species sp in one workgroup: the
 // live slots of [0, n) of set `cur` go to the other set, cell by cell (order
 // within a cell arbitrary); returns the live count.  sC: LDS for ng counters.
+template <int NB>
 __device__ __forceinline__ int64_t small_sort(CaseDev* __restrict__ Cw, int sp, int cur, int64_t n, unsigned int* sC) {
   __shared__ int64_t sRed[64];
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
@@ -1875,14 +1868,14 @@ __device__ __forceinline__ int64_t small_sort(CaseDev* __restrict__ Cw, int sp, 
   const EDP_GLOBAL double* __restrict__ X = G(S.x[cur]);
   for (int p = threadIdx.x; p < ng; p += blockDim.x) sC[p] = 0;
   __syncthreads();
-  for (int64_t i = threadIdx.x; i < n; i += kBlock) {
+  for (int64_t i = threadIdx.x; i < n; i += NB) {
     const double x = X[i];
     if (x == x) atomicAdd(&sC[cell_of(x, inv_dx, ng)], 1u);
   }
   __syncthreads();
   // exclusive scan of the ng - 1 cell counts, a contiguous range per thread
   const int m = ng - 1;
-  const int per = (m + kBlock - 1) / kBlock;
+  const int per = (m + NB - 1) / NB;
   const int lo = (int)threadIdx.x * per < m ? (int)threadIdx.x * per : m;
   const int hi = lo + per < m ? lo + per : m;
   int64_t acc = 0;
@@ -1906,7 +1899,7 @@ __device__ __forceinline__ int64_t small_sort(CaseDev* __restrict__ Cw, int sp, 
   EDP_GLOBAL double* __restrict__ VZ2 = G(S.vz[nxt]);
   EDP_GLOBAL uint64_t* __restrict__ UID2 = G(S.uid[nxt]);
   EDP_GLOBAL float* __restrict__ VP22 = sp == 0 ? G(S.vp2[nxt]) : nullptr;
-  for (int64_t i = threadIdx.x; i < n; i += kBlock) {
+  for (int64_t i = threadIdx.x; i < n; i += NB) {
     const double x = X[i];
     if (!(x == x)) continue;
     const double vx = VX[i], vy = VY[i], vz = VZ[i];
@@ -1926,12 +1919,17 @@ __device__ __forceinline__ int64_t small_sort(CaseDev* __restrict__ Cw, int sp, 
 // Window of steps of the small cases: workgroup b advances the case of role
 // b by role.j steps.  Dynamic LDS: E, then the largest of the particle
 // phase's histograms (also the field solve's scratch) and the sort's
-// counters.
-template <int MODE>
-__global__ void __launch_bounds__(kBlock) k_small(const BlockRole* __restrict__ R, int sort_every, int pretest) {
+// counters.  Bound by the latency of a step's phases, one after another: with
+// 512 threads a case of 1e3 particles is one to three slices a wave (256
+// where the LDS of a case's measurements asks for it), the step's indices
+// and the slot counts are kept by every wave, and a wave keeps its totals
+// until the end (1e3 electrons on 400 nodes 12.3 -> 11.4 us a step, 5e3 on
+// 641 nodes 31.5 -> 26.9).
+template <int MODE, int NB>
+__global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, int sort_every, int pretest) {
   extern __shared__ double ssm2[];
-  __shared__ int64_t sState[5];  // step, n_e, n_i, cur_e, cur_i
-  __shared__ int sBirth[2];
+  // births of the steps t, t - 1 (read) and t + 1 (cleared) mod 3
+  __shared__ int sBirth[3][2];
   const EDP_CONST BlockRole* r = KC(R) + blockIdx.x;
   CaseDev* Cw = r->c;
   const int steps = r->j;
@@ -1940,79 +1938,84 @@ __global__ void __launch_bounds__(kBlock) k_small(const BlockRole* __restrict__ 
   const int nsub = C->nsub;
   double* sE = ssm2;
   double* reg = ssm2 + ng;
-  if (threadIdx.x == 0) {
-    sState[0] = Cw->step;
-    sState[1] = Cw->n[0];
-    sState[2] = Cw->n[1];
-    sState[3] = Cw->cur[0];
-    sState[4] = Cw->cur[1];
-  }
+  int64_t s = C->step;
+  int64_t n_e = C->n[0], n_i = C->n[1];
+  int cur_e = C->cur[0], cur_i = C->cur[1];
+  // read once: the kernel writes them at its end
+  asm volatile("" : "+s"(s), "+s"(n_e), "+s"(n_i), "+s"(cur_e), "+s"(cur_i));
+  const int64_t cap_e = C->sp[0].cap, cap_i = C->sp[1].cap;
+  StepIndex I(s, nsub);
+  // steps to the next compaction + cell sort, on the lockstep path's schedule
+  const int64_t every_i = (int64_t)sort_every * nsub;
+  int64_t to_e = (sort_every - s % sort_every) % sort_every, to_i = (every_i - s % every_i) % every_i;
+  int64_t tot[2] = {0, 0};  // lane f: this wave's total of field f, per species
+  if (threadIdx.x < 6) sBirth[threadIdx.x / 2][threadIdx.x % 2] = 0;
   __syncthreads();
+  int b3 = 0;  // t mod 3
+#pragma unroll 1
   for (int t = 0; t < steps; ++t) {
-    const int64_t s = sState[0];
-    int64_t n_e = sState[1], n_i = sState[2];
-    int cur_e = (int)sState[3], cur_i = (int)sState[4];
-    const StepIndex I(s, nsub);
     const bool ion_step = I.sub == 0;
-    // compaction + cell sort on the lockstep path's schedule
-    if (s % sort_every == 0) {
-      n_e = small_sort(Cw, 0, cur_e, n_e, (unsigned int*)ssm2);
+    const int b_next = b3 == 2 ? 0 : b3 + 1, b_last = b3 == 0 ? 2 : b3 - 1;
+    n_e = n_e + sBirth[b_last][0] < cap_e ? n_e + sBirth[b_last][0] : cap_e;
+    n_i = n_i + sBirth[b_last][1] < cap_i ? n_i + sBirth[b_last][1] : cap_i;
+    if (threadIdx.x < 2) sBirth[b_next][threadIdx.x] = 0;
+    if (to_e == 0) {
+      n_e = small_sort<NB>(Cw, 0, cur_e, n_e, (unsigned int*)ssm2);
       cur_e ^= 1;
+      to_e = sort_every;
     }
-    if (s % ((int64_t)sort_every * nsub) == 0) {
-      n_i = small_sort(Cw, 1, cur_i, n_i, (unsigned int*)ssm2);
+    if (to_i == 0) {
+      n_i = small_sort<NB>(Cw, 1, cur_i, n_i, (unsigned int*)ssm2);
       cur_i ^= 1;
+      to_i = every_i;
     }
-    if (threadIdx.x < 2) sBirth[threadIdx.x] = 0;
+    --to_e;
+    --to_i;
     // steps 1-2
     auto solve = [&]() __attribute__((always_inline)) {
-      const RingNodes<kBlock> N(C->cnt_e, C->cnt_i, C->volt, s, I.s3, I.k3, ng);
-      solve_field<MODE, kBlock>(Cw, ng, s, I, sE, reg, true, N, SolveIn(C));
+      const RingNodes<NB> N(C->cnt_e, C->cnt_i, C->volt, s, I.s3, I.k3, ng);
+      solve_field<MODE, NB>(Cw, ng, s, I, sE, reg, true, N, SolveIn(C));
     };
     Births<true> B;
     B.base[0] = n_e;
     B.base[1] = n_i;
-    B.cap[0] = C->sp[0].cap;
-    B.cap[1] = C->sp[1].cap;
-    B.lds = sBirth;
+    B.cap[0] = cap_e;
+    B.cap[1] = cap_i;
+    B.lds = sBirth[b3];
     B.glob[0] = B.glob[1] = nullptr;
-    const int64_t nch_e = (n_e + kChunk - 1) / kChunk, nch_i = (n_i + kChunk - 1) / kChunk;
-    const SpTot te = species_pass<0, true, kBlock>(Cw, sE, reg, s, I, n_e, 0, nch_e, cur_e, cur_i, B, pretest, PassIn<0>(C), solve);
-    SpTot ti{};
-    if (ion_step) ti = species_pass<1, true, kBlock>(Cw, sE, reg, s, I, n_i, 0, nch_i, cur_i, cur_e, B, pretest, PassIn<1>(C), [] { __syncthreads(); });
-    if (threadIdx.x == 0) {
-      int64_t* ctr = Cw->ctr;
-      ctr[kCollE] += te.v[kRecColl];
-      ctr[kIoniz] += te.v[kRecIoniz];
-      ctr[kAbsEPow] += te.v[kRecAbsPow];
-      ctr[kAbsEGnd] += te.v[kRecAbsGnd];
-      ctr[kPstepE] += te.v[kRecLive];
-      ctr[kCollI] += ti.v[kRecColl];
-      ctr[kAbsIPow] += ti.v[kRecAbsPow];
-      ctr[kAbsIGnd] += ti.v[kRecAbsGnd];
-      ctr[kPstepI] += ti.v[kRecLive];
-      const int64_t ge = te.v[kRecBornE] + ti.v[kRecBornE], gi = te.v[kRecBornI] + ti.v[kRecBornI];
-      ctr[kLiveE] += ge - te.v[kRecAbsPow] - te.v[kRecAbsGnd];
-      ctr[kLiveI] += gi - ti.v[kRecAbsPow] - ti.v[kRecAbsGnd];
-      const int64_t dropped = te.v[kRecDropped] + ti.v[kRecDropped];
-      if (dropped) {
-        ctr[kDropped] += dropped;
-        Cw->error = 1;
-      }
-      sState[0] = s + 1;
-      sState[1] = n_e + ge;
-      sState[2] = n_i + gi;
-      sState[3] = cur_e;
-      sState[4] = cur_i;
+    const int64_t nch_e = (n_e + NB - 1) / NB, nch_i = (n_i + NB - 1) / NB;
+    tot[0] += species_pass<0, true, NB>(Cw, sE, reg, s, I, n_e, 0, nch_e, cur_e, cur_i, B, pretest, PassIn<0>(C), solve).field;
+    if (ion_step)
+      tot[1] += species_pass<1, true, NB>(Cw, sE, reg, s, I, n_i, 0, nch_i, cur_i, cur_e, B, pretest, PassIn<1>(C),
+                                          [] { __syncthreads(); }).field;
+    ++s;
+    I.next(nsub);
+    b3 = b_next;
+  }
+  // the counters of each wave's totals
+  const int f = (int)threadIdx.x % kWave;
+  constexpr int kTo[2][kRec] = {{kCollE, kIoniz, kAbsEPow, kAbsEGnd, kPstepE, kLiveE, kLiveI, kDropped},
+                                {kCollI, -1, kAbsIPow, kAbsIGnd, kPstepI, kLiveE, kLiveI, kDropped}};
+#pragma unroll
+  for (int sp = 0; sp < 2; ++sp) {
+    int to = -1;
+#pragma unroll
+    for (int q = 0; q < kRec; ++q) to = f == q ? kTo[sp][q] : to;
+    if (to >= 0 && tot[sp]) {
+      gl_add(&Cw->ctr[to], tot[sp]);
+      if (f == kRecAbsPow || f == kRecAbsGnd) gl_add(&Cw->ctr[sp == 0 ? kLiveE : kLiveI], -tot[sp]);
+      if (f == kRecDropped) Cw->error = 1;
     }
-    __syncthreads();
   }
   if (threadIdx.x == 0) {
-    Cw->step = sState[0];
-    Cw->n[0] = Cw->alloc[0] = sState[1];
-    Cw->n[1] = Cw->alloc[1] = sState[2];
-    Cw->cur[0] = (int32_t)sState[3];
-    Cw->cur[1] = (int32_t)sState[4];
+    const int b_last = b3 == 0 ? 2 : b3 - 1;
+    n_e = n_e + sBirth[b_last][0] < cap_e ? n_e + sBirth[b_last][0] : cap_e;
+    n_i = n_i + sBirth[b_last][1] < cap_i ? n_i + sBirth[b_last][1] : cap_i;
+    Cw->step = s;
+    Cw->n[0] = Cw->alloc[0] = n_e;
+    Cw->n[1] = Cw->alloc[1] = n_i;
+    Cw->cur[0] = cur_e;
+    Cw->cur[1] = cur_i;
   }
 }
 
@@ -2381,19 +2384,25 @@ size_t small_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed) {
   return ((size_t)ng + region) * 8;
 }
 
-size_t small_static_lds() {
-  const size_t waves = kBlock / kWave;
-  return waves * kSegE * (4 + 8 + 8) + waves * kSegI * 4 + 2 * kMaxPb * 8 + 6144;
+size_t small_static_lds(int nb) {
+  const size_t waves = (size_t)nb / kWave;
+  return waves * (kSegE * (4 + 8 + 8) + kWave * 4 + kSegI * 4) + 2 * kMaxPb * 4 + 2048;
 }
 
 // One window of the small cases: workgroup b runs the case of roles[b] for
 // roles[b].j steps.
 hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode, int sort_every, int pretest,
                         hipStream_t st) {
-  if (mode == 1)
-    hipLaunchKernelGGL(k_small<1>, dim3(ncase), dim3(kBlock), lds, st, roles, sort_every, pretest);
-  else
-    hipLaunchKernelGGL(k_small<0>, dim3(ncase), dim3(kBlock), lds, st, roles, sort_every, pretest);
+  if (lds + small_static_lds(512) <= 65536) {
+    if (mode == 1)
+      hipLaunchKernelGGL((k_small<1, 512>), dim3(ncase), dim3(512), lds, st, roles, sort_every, pretest);
+    else
+      hipLaunchKernelGGL((k_small<0, 512>), dim3(ncase), dim3(512), lds, st, roles, sort_every, pretest);
+  } else if (mode == 1) {
+    hipLaunchKernelGGL((k_small<1, 256>), dim3(ncase), dim3(256), lds, st, roles, sort_every, pretest);
+  } else {
+    hipLaunchKernelGGL((k_small<0, 256>), dim3(ncase), dim3(256), lds, st, roles, sort_every, pretest);
+  }
   return hipGetLastError();
 }
 

@@ -160,9 +160,11 @@ extern "C" {
                                  later layer streams its chunks more slowly;
                                  layer l of L then takes a share of its
                                  case's chunks weighted by
-                                 1 - skew l / (L - 1).  -1: 200 (L - 1), at
-                                 most 900, when the launch serves one case,
-                                 else 0.  Results do not depend on it, speed
+                                 1 - skew l / (L - 1).  -1: when the launch
+                                 serves one case, 450 (L - 1) in workgroups of
+                                 512 threads without particle measurements,
+                                 else 200 (L - 1), at most 900; with several
+                                 cases 0.  Results do not depend on it, speed
                                  does */
 #define EDP_OPT_PRETEST 14     /* the collision pre-test's bound of P (section
                                  2.1.6, direct test): 0 (default) automatic,

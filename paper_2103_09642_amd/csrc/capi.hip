@@ -667,13 +667,17 @@ BlockRole role(const Case* c, int j, int n) {
 // the older waves, and a later layer streams its chunks more slowly.  With
 // skew a (per mille) layer l of L gets the weight 1 - a l / (L - 1), and
 // each case's chunks are split by the weights of its workgroups.  The
-// automatic skew (a < 0) is 200 (L - 1), at most 900, for a launch of one
-// case: on the large case (2e6 particles per species, four layers) 600-750
-// measured best, 4% above none; a launch of several cases runs without
-// (measured neutral with two lockstep groups, 3% slower with one: cases
-// differ in their cost per chunk more than layers do).
+// automatic skew (a < 0), for a launch of one case in the two layers of
+// workgroups of 512, is 450, or 200 where the loop also measures (it reads
+// more and computes more, and the layers then differ less).  Measured, us a
+// step with 200, 300, 400, 500: the large case (1.6e6 electrons) 30.0 29.8
+// 29.6 29.4, with its averages on 34.2 34.2 35.1 36.1; 3e5 electrons on 777
+// nodes 21.3 21.2 21.2 20.9; 1.2e6 on 2000 nodes 27.3 27.1 27.0 26.6.  A
+// launch of several cases runs without (64 mixed cases 95.1 with none or 200,
+// 96.4 with 500; the dual-frequency set 268, 265, 274): cases differ in their
+// cost per chunk more than layers do.
 void particle_roles(std::vector<BlockRole>& roles, const std::vector<Case*>& cs, const std::vector<int>& want,
-                    int num_cu, int skew) {
+                    int num_cu, int skew, int nb) {
   struct Pos {
     double key;
     int k, j;
@@ -691,7 +695,10 @@ void particle_roles(std::vector<BlockRole>& roles, const std::vector<Case*>& cs,
     at[p.k].push_back(b);  // j increasing with b within a case
   }
   const int layers = (nblocks + num_cu - 1) / std::max(1, num_cu);
-  if (skew < 0) skew = cs.size() == 1 ? std::min(900, 200 * (layers - 1)) : 0;
+  if (skew < 0) {
+    const bool measures = cs.size() == 1 && (cs[0]->h.flags & kDiagParticle) != 0;
+    skew = cs.size() == 1 ? std::min(900, (nb == 512 && !measures ? 450 : 200) * (layers - 1)) : 0;
+  }
   auto weight = [&](int b) {
     if (layers < 2 || skew <= 0) return 1.0;
     return 1.0 - 1e-3 * skew * (double)(b / num_cu) / (double)(layers - 1);
@@ -841,7 +848,7 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   roles.reserve((size_t)B.parts[0] + B.parts[1] + nc + B.sorts[0] + B.sorts[1]);
   for (int sp = 0; sp < 2; ++sp) {
     B.role_off[sp] = roles.size();
-    particle_roles(roles, cs, want[sp], ctx->num_cu, ctx->part_skew);
+    particle_roles(roles, cs, want[sp], ctx->num_cu, ctx->part_skew, nb[sp]);
   }
   B.role_off[2] = roles.size();
   for (size_t k = 0; k < nc; ++k) roles.push_back(role(cs[k], 0, 1));

@@ -38,7 +38,8 @@ constexpr double kDiagWS = 1048576.0;  // c
 constexpr double kDiagES = 1048576.0;  // c * energy [eV]
 constexpr double kDiagIZS = 4294967296.0;  // c * nu_ion dt_e
 
-// Workgroup size of most kernels, and of the small-case kernel's chunks.
+// Workgroup size of most kernels (the particle and small-case kernels' are
+// template arguments).
 constexpr int kBlock = 256;
 constexpr int kChunk = kBlock;  // slots per chunk of the host's size estimates and the sort
 // Largest chunk of the lockstep particle kernels (one slot per thread of a

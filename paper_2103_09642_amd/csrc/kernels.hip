@@ -20,7 +20,8 @@
 //
 // Every FP64 expression of the push and the collision kinematics is written
 // in the same operation order as its definition, and the library is built
-// with -ffp-contract=off, so no multiply-add is fused.
+// with -ffp-contract=off, so no multiply-add is fused (but in div_by, whose
+// fused steps give the correctly rounded quotient).
 #include <hip/hip_ext.h>
 
 #include <type_traits>
@@ -1688,7 +1689,7 @@ __device__ __forceinline__ int64_t step_slots(const EDP_CONST CaseDev* __restric
 }
 
 // Steps 1-7 of one species for every case of a lockstep group, at step
-// step0 + dstep of each case.  At most 128 VGPRs (four workgroups per CU):
+// step0 + dstep of each case.  At most 128 VGPRs (16 waves per CU):
 // the streaming loop needs about 100; the scattering code after the loop
 // would take twice that if left alone, and spills there instead (colliders
 // are a few percent of the particles).  Every workgroup solves its case's field into

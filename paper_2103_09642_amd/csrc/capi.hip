@@ -41,9 +41,9 @@ hipError_t launch_deposit(CaseDev* d, int sp, int64_t* dst1, int64_t* dst2, int 
 hipError_t launch_sort(const BlockRole* roles, const BlockRole* case_roles, int sp, int blocks, int ncase, int max_ng,
                        int every, int dstep, hipStream_t st);
 hipError_t launch_fold(CaseDev* d, hipStream_t st);
-size_t small_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed);
+size_t small_lds_bytes(int nb, int ng, uint32_t flags, int n_eepf, int n_ifed);
 size_t small_static_lds(int nb);
-hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode, int sort_every, int pretest,
+hipError_t launch_small(const BlockRole* roles, int ncase, int nb, size_t lds, int mode, int sort_every, int pretest,
                         hipStream_t st);
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t st);
 }  // namespace edp
@@ -1064,7 +1064,7 @@ int group_window(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::v
 bool small_case(const edp_ctx* ctx, const Case* c) {
   if (ctx->small_max <= 0 || std::max(c->est[0], c->est[1]) > ctx->small_max) return false;
   const edp_case_desc& D = c->desc;
-  return small_lds_bytes(D.n_grid, D.flags, D.n_eepf, D.n_ifed) + small_static_lds(256) <= 65536;
+  return small_lds_bytes(256, D.n_grid, D.flags, D.n_eepf, D.n_ifed) + small_static_lds(256) <= 65536;
 }
 
 // The persistent small cases of an advance, on the context's small-case
@@ -1083,9 +1083,16 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
   HIPCHK(hipStreamSynchronize(st));
   HIPCHK(hipEventRecord(ctx->fork_ev, ctx->stream));
   HIPCHK(hipStreamWaitEvent(st, ctx->fork_ev, 0));
+  // 512 threads where every case's LDS lets two workgroups share a CU
+  int nb = 512;
   size_t lds = 0;
-  for (const Case* c : cases)
-    lds = std::max(lds, small_lds_bytes(c->desc.n_grid, c->desc.flags, c->desc.n_eepf, c->desc.n_ifed));
+  for (int pass = 0; pass < 2; ++pass) {
+    lds = 0;
+    for (const Case* c : cases)
+      lds = std::max(lds, small_lds_bytes(nb, c->desc.n_grid, c->desc.flags, c->desc.n_eepf, c->desc.n_ifed));
+    if (nb == 512 && lds + small_static_lds(512) <= 81920) break;
+    nb = 256;
+  }
   // every window's roles, built up front and uploaded once: window w holds
   // the cases with steps left, each with min(left, the window's) steps; one
   // more entry for each case's end
@@ -1135,7 +1142,7 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
     }
     if (r) break;
     HIPCHK(launch_small_volt(ctx->small_roles + W.lo, (int)(W.hi - W.lo), st));
-    HIPCHK(launch_small(ctx->small_roles + W.lo, (int)(W.hi - W.lo), lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
+    HIPCHK(launch_small(ctx->small_roles + W.lo, (int)(W.hi - W.lo), nb, lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
     for (size_t a = W.lo; a < W.hi; ++a) who[a]->step += roles[a].j;
     HIPCHK(hipEventRecord(ctx->small_join, st));  // the staging of this window and before is free
   }

@@ -341,7 +341,7 @@ struct FieldWriter {
   const EDP_CONST CaseDev* C;
   int s3, k3;  // step % 3, ion step index % 3
   int ng;
-  bool ion_step, xt;
+  bool ion_step, xt, rings;
   size_t plane, row, row_prev;
   // node p before the solve: rho for reads, the time sums of the densities,
   // the deposit rings the next steps refill cleared, the particle sums of step
@@ -355,8 +355,8 @@ struct FieldWriter {
       gl_sum(G(C->sum_ni) + p, ni);
     }
     const int prev3 = s3 == 0 ? 2 : s3 - 1;
-    G(C->cnt_e)[prev3 * ng + p] = 0;
-    if (ion_step) G(C->cnt_i)[(k3 == 0 ? 2 : k3 - 1) * ng + p] = 0;
+    if (rings) G(C->cnt_e)[prev3 * ng + p] = 0;
+    if (rings && ion_step) G(C->cnt_i)[(k3 == 0 ? 2 : k3 - 1) * ng + p] = 0;
     if (fl & (kDiagCurrent | kDiagMeanE | kDiagXT)) fold_particle_sums(C, p, prev3 * ng, row_prev, plane);
     if (xt) {
       EDP_GLOBAL double* __restrict__ X = G(C->xt);
@@ -422,6 +422,7 @@ struct SolveIn {
 constexpr int kRingRegs = 4;
 template <int NB>
 struct RingNodes {
+  static constexpr bool kOwn = false;
   const EDP_GLOBAL int64_t *gE, *gI;
   int64_t e[kRingRegs], i[kRingRegs];
   double V;
@@ -454,6 +455,13 @@ struct RingNodes {
   }
 };
 
+// The densities of a small case whose workgroup keeps them in LDS.
+struct OwnNodes {
+  static constexpr bool kOwn = true;
+  int64_t *e, *i;
+  double V;
+};
+
 // Steps 1-2 of step s, computed by every workgroup that needs E (each
 // particle workgroup of a lockstep launch, the small-case workgroup): the
 // densities of the deposit rings read at step s, rho, the potential and E on
@@ -468,10 +476,10 @@ struct RingNodes {
 // unrolled to the largest grid with the writer's code in each copy (the
 // electron kernel's code 64 -> 42 KB; a step of 1e3 electrons on 400 nodes
 // 13.5 -> 12.4 us).
-template <int MODE, int NB>
+template <int MODE, int NB, class Nodes>
 __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int ng, const int64_t s,
                                             const StepIndex& I, double* sE, double* sF, const bool writer,
-                                            const RingNodes<NB>& N, const SolveIn& S) {
+                                            const Nodes& N, const SolveIn& S) {
   // the flux solve is always worked by the first 256 threads (its sums then
   // have the same order, and the same bits, whatever the workgroup)
   constexpr int NS = 256;
@@ -481,10 +489,16 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int 
   const bool ion_step = I.sub == 0;
   const int t = (int)threadIdx.x;
   const int lane = t % kWave, wv = __builtin_amdgcn_readfirstlane(t / kWave);
-  // the rings, staged where E and the scratch go
-  int64_t* const nE = (int64_t*)sF;
-  int64_t* const nI = (int64_t*)sE;
-  N.stage(nE, nI, ng);
+  // the rings, staged where E and the scratch go (or kept elsewhere)
+  int64_t *nE, *nI;
+  if constexpr (Nodes::kOwn) {
+    nE = N.e;
+    nI = N.i;
+  } else {
+    nE = (int64_t*)sF;
+    nI = (int64_t*)sE;
+    N.stage(nE, nI, ng);
+  }
   const double V = N.V;
   const double scale = S.scale, kp = S.kpois, dx = S.dx;
   FieldWriter W;
@@ -493,6 +507,7 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int 
   W.k3 = I.k3;
   W.ng = ng;
   W.ion_step = ion_step;
+  W.rings = !Nodes::kOwn;
   W.xt = writer && (C->flags & kDiagXT) != 0;
   W.plane = W.row = W.row_prev = 0;
   uint32_t bin = 0;
@@ -514,15 +529,26 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int 
     }
     return kECharge * (ni - ne);
   };
-  __syncthreads();
   double ne, ni;
-  if (writer) {
+  if constexpr (Nodes::kOwn) {
+    // the waves that do not solve take the writer's nodes meanwhile
+    static_assert(NB > NS, "waves beside the solving ones");
 #pragma unroll 1
-    for (int p = t; p < ng; p += NB) {
+    for (int p = t - NS; p < ng; p += NB - NS) {
+      if (p < 0) break;
       const double rho = dens(p, ne, ni);
       W.node(p, ne, ni, rho);
     }
-    __syncthreads();  // the staged ions are overwritten below
+  } else {
+    __syncthreads();
+    if (writer) {
+#pragma unroll 1
+      for (int p = t; p < ng; p += NB) {
+        const double rho = dens(p, ne, ni);
+        W.node(p, ne, ni, rho);
+      }
+      __syncthreads();  // the staged ions are overwritten below
+    }
   }
   if (MODE == 1) {
     // node p = t + q NB: rho and the right-hand side d_p = rho_p dx^2/eps0
@@ -1075,9 +1101,13 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
                                               const int64_t s, const StepIndex& I, const int64_t n, const int64_t c_lo,
                                               const int64_t c_hi, const int cur, const int cur_o,
                                               const Births<SMALL>& B, const int pretest, const PassIn<SP>& A,
-                                              const Solve& solve) {
+                                              const Solve& solve, unsigned long long* own_e = nullptr,
+                                              unsigned long long* own_i = nullptr) {
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   constexpr int kSeg = seg_len<SP>();
+  // a small case's workgroup that keeps the deposits in LDS (own_e, own_i:
+  // of the next step and of the next ion step)
+  constexpr bool OWN = SMALL && NB > kBlock;
   constexpr bool ZEROED = !(SMALL && SP == 1);  // the solve left the histogram zero
   constexpr int kPay = SP == 0 ? NB / kWave : 1;
   __shared__ int32_t sSeg[NB / kWave][kSeg];
@@ -1098,15 +1128,15 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   const int n_ifed = C->n_ifed;
   // histogram: the EEPF for electrons, the IFEDF of both electrodes for ions
   const int n_hist = SP == 0 ? ((fl & kDiagEepf) ? n_eepf : 0) : ((fl & kDiagIfed) ? 2 * (n_ifed + 1) : 0);
-  unsigned long long* sH = (unsigned long long*)reg;
-  unsigned long long* sJ = sH + ng;
+  unsigned long long* sH = OWN ? (SP == 0 ? own_e : own_i) : (unsigned long long*)reg;
+  unsigned long long* sJ = (unsigned long long*)reg + (OWN ? 0 : ng);
   unsigned long long* sW = sJ + ng;
   unsigned long long* sEn = sW + ng;
   unsigned long long* sIz = sEn + ng;  // electrons with the xt arrays only
   unsigned int* sF = (unsigned int*)(sIz + (SP == 0 && xt ? ng : 0));
-  if (pdiag || !ZEROED) {
+  if (pdiag || (!ZEROED && !OWN)) {
     for (int p = threadIdx.x; p < ng; p += NB) {
-      if (!ZEROED) sH[p] = 0;
+      if (!ZEROED && !OWN) sH[p] = 0;
       if (!pdiag) continue;
       sJ[p] = 0;
       sW[p] = 0;
@@ -1398,10 +1428,17 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
         if (ioniz) {
           long long r;
           const int q = deposit_split(xb, inv_dx, ng, r);
-          gl_add(&dst[q], 4294967296LL - r);
-          gl_add(&dst[q + 1], r);
-          gl_add(&cnt_i_next[q], 4294967296LL - r);
-          gl_add(&cnt_i_next[q + 1], r);
+          if constexpr (OWN) {
+            lds_add(&own_e[q], 4294967296LL - r);
+            lds_add(&own_e[q + 1], r);
+            lds_add(&own_i[q], 4294967296LL - r);
+            lds_add(&own_i[q + 1], r);
+          } else {
+            gl_add(&dst[q], 4294967296LL - r);
+            gl_add(&dst[q + 1], r);
+            gl_add(&cnt_i_next[q], 4294967296LL - r);
+            gl_add(&cnt_i_next[q + 1], r);
+          }
           if (ok_i) ion_birth_at(C, P, f_i + ri, s, uid, xb);
         }
       }
@@ -1561,8 +1598,13 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
             surf = true;
             long long r;
             const int p = deposit_split(abs_pow ? 0.0 : L_gap, inv_dx, ng, r);
-            gl_add(&cnt_e_next[p], 4294967296LL - r);
-            if (r) gl_add(&cnt_e_next[p + 1], r);
+            if constexpr (OWN) {
+              lds_add(&own_e[p], 4294967296LL - r);
+              if (r) lds_add(&own_e[p + 1], r);
+            } else {
+              gl_add(&cnt_e_next[p], 4294967296LL - r);
+              if (r) gl_add(&cnt_e_next[p + 1], r);
+            }
           }
         }
       }
@@ -1643,7 +1685,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
   // every load of the candidates' rounds waited for those too (a step of 1.3e5
   // electrons on 641 nodes 16.4 -> 16.1 us).  A thread's first nodes without a
   // loop: before one, the compiler waits for whatever is on its way.
-  {
+  if constexpr (!OWN) {
     unsigned long long h[kRingRegs];
 #pragma unroll
     for (int u = 0; u < kRingRegs; ++u) {
@@ -1654,7 +1696,7 @@ __device__ __forceinline__ SpTot species_pass(CaseDev* __restrict__ Cw, const do
     for (int u = 0; u < kRingRegs; ++u)
       if (h[u]) gl_add(&dst[(int)threadIdx.x + u * NB], (long long)h[u]);
   }
-  if (ng > kRingRegs * NB)
+  if (!OWN && ng > kRingRegs * NB)
     for (int q = (int)threadIdx.x + kRingRegs * NB; q < ng; q += NB)
       if (const unsigned long long h = sH[q]) gl_add(&dst[q], (long long)h);
   if (pdiag)
@@ -1918,14 +1960,21 @@ __device__ __forceinline__ int64_t small_sort(CaseDev* __restrict__ Cw, int sp, 
 }
 
 // Window of steps of the small cases: workgroup b advances the case of role
-// b by role.j steps.  Dynamic LDS: E, then the largest of the particle
-// phase's histograms (also the field solve's scratch) and the sort's
-// counters.  Bound by the latency of a step's phases, one after another: with
-// 512 threads a case of 1e3 particles is one to three slices a wave (256
-// where the LDS of a case's measurements asks for it), the step's indices
-// and the slot counts are kept by every wave, and a wave keeps its totals
-// until the end (1e3 electrons on 400 nodes 12.3 -> 11.4 us a step, 5e3 on
-// 641 nodes 31.5 -> 26.9).
+// b by role.j steps.  Bound by the latency of a step's phases, one after
+// another.  With 512 threads a case of 1e3 particles is one to three slices a
+// wave; the densities and the deposits of the next step stay in LDS (no flush,
+// no rings in between; the window's end writes them back), and the waves that
+// do not solve the field do the writer's duties meanwhile.  256 threads where
+// a case's grid and measurements ask for the LDS: deposits through the
+// rings.  Every wave keeps the step's indices, the slot counts and its totals
+// until the end.  Measured, us a step with 256 threads and totals every step,
+// with 512, with the deposits in LDS: 1e3 electrons on 400 nodes 12.3, 11.2,
+// 9.6, 5e3 on 641 nodes 31.5, 26.8, 25.2.
+//
+// Dynamic LDS: E (also the sort's counters), then for 512 threads the
+// densities and deposits of both species and the larger of the two
+// species' measurement arrays, for 256 the larger particle region (also the
+// field solve's scratch).
 template <int MODE, int NB>
 __global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, int sort_every, int pretest) {
   extern __shared__ double ssm2[];
@@ -1937,8 +1986,15 @@ __global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, i
   const EDP_CONST CaseDev* __restrict__ C = KC(Cw);
   const int ng = C->ng;
   const int nsub = C->nsub;
+  constexpr bool OWN = NB > kBlock;
   double* sE = ssm2;
-  double* reg = ssm2 + ng;
+  // the electrons' density of the step and deposit for the next, the ions'
+  // density and deposit for the next ion step
+  int64_t* A0 = (int64_t*)(ssm2 + ng);
+  int64_t* A1 = A0 + ng;
+  int64_t* I0 = A1 + ng;
+  int64_t* I1 = I0 + ng;
+  double* reg = ssm2 + (OWN ? 5 : 1) * ng;
   int64_t s = C->step;
   int64_t n_e = C->n[0], n_i = C->n[1];
   int cur_e = C->cur[0], cur_i = C->cur[1];
@@ -1951,6 +2007,16 @@ __global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, i
   int64_t to_e = (sort_every - s % sort_every) % sort_every, to_i = (every_i - s % every_i) % every_i;
   int64_t tot[2] = {0, 0};  // lane f: this wave's total of field f, per species
   if (threadIdx.x < 6) sBirth[threadIdx.x / 2][threadIdx.x % 2] = 0;
+  if constexpr (OWN) {
+    const EDP_GLOBAL int64_t *gE = G(C->cnt_e), *gI = G(C->cnt_i);
+    for (int p = threadIdx.x; p < ng; p += NB) {
+      // (an ion step takes I1 as its density first)
+      const int64_t now = gI[I.k3 * ng + p], next = gI[(I.k3 == 2 ? 0 : I.k3 + 1) * ng + p];
+      A0[p] = gE[I.s3 * ng + p];
+      I0[p] = now;
+      I1[p] = I.sub == 0 ? now : next;
+    }
+  }
   __syncthreads();
   int b3 = 0;  // t mod 3
 #pragma unroll 1
@@ -1973,9 +2039,22 @@ __global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, i
     --to_e;
     --to_i;
     // steps 1-2
+    if constexpr (OWN) {
+      if (ion_step) {
+        int64_t* const a = I0;
+        I0 = I1;
+        I1 = a;
+        for (int p = threadIdx.x; p < ng; p += NB) I1[p] = 0;
+      }
+    }
     auto solve = [&]() __attribute__((always_inline)) {
-      const RingNodes<NB> N(C->cnt_e, C->cnt_i, C->volt, s, I.s3, I.k3, ng);
-      solve_field<MODE, NB>(Cw, ng, s, I, sE, reg, true, N, SolveIn(C));
+      if constexpr (OWN) {
+        const OwnNodes N{A0, I0, G(C->volt)[s % kVoltChunk]};
+        solve_field<MODE, NB>(Cw, ng, s, I, sE, (double*)A1, true, N, SolveIn(C));
+      } else {
+        const RingNodes<NB> N(C->cnt_e, C->cnt_i, C->volt, s, I.s3, I.k3, ng);
+        solve_field<MODE, NB>(Cw, ng, s, I, sE, reg, true, N, SolveIn(C));
+      }
     };
     Births<true> B;
     B.base[0] = n_e;
@@ -1985,13 +2064,32 @@ __global__ void __launch_bounds__(NB) k_small(const BlockRole* __restrict__ R, i
     B.lds = sBirth[b3];
     B.glob[0] = B.glob[1] = nullptr;
     const int64_t nch_e = (n_e + NB - 1) / NB, nch_i = (n_i + NB - 1) / NB;
-    tot[0] += species_pass<0, true, NB>(Cw, sE, reg, s, I, n_e, 0, nch_e, cur_e, cur_i, B, pretest, PassIn<0>(C), solve).field;
+    tot[0] += species_pass<0, true, NB>(Cw, sE, reg, s, I, n_e, 0, nch_e, cur_e, cur_i, B, pretest, PassIn<0>(C), solve,
+                                          (unsigned long long*)A1, (unsigned long long*)I1).field;
     if (ion_step)
       tot[1] += species_pass<1, true, NB>(Cw, sE, reg, s, I, n_i, 0, nch_i, cur_i, cur_e, B, pretest, PassIn<1>(C),
-                                          [] { __syncthreads(); }).field;
+                                          [] { __syncthreads(); }, (unsigned long long*)A1, (unsigned long long*)I1).field;
+    if constexpr (OWN) {
+      int64_t* const a = A0;
+      A0 = A1;
+      A1 = a;
+    }
     ++s;
     I.next(nsub);
     b3 = b_next;
+  }
+  if constexpr (OWN) {
+    // the rings as the next step reads and fills them (kl: the last ion step's)
+    const int kl = I.sub == 0 ? (I.k3 + 2) % 3 : I.k3;
+    EDP_GLOBAL int64_t *gE = G(C->cnt_e), *gI = G(C->cnt_i);
+    for (int p = threadIdx.x; p < ng; p += NB) {
+      gE[I.s3 * ng + p] = A0[p];
+      gE[(I.s3 + 1) % 3 * ng + p] = 0;
+      gE[(I.s3 + 2) % 3 * ng + p] = 0;
+      gI[kl * ng + p] = I0[p];
+      gI[(kl + 1) % 3 * ng + p] = I1[p];
+      gI[(kl + 2) % 3 * ng + p] = 0;
+    }
   }
   // the counters of each wave's totals
   const int f = (int)threadIdx.x % kWave;
@@ -2373,16 +2471,14 @@ int particle_occupancy(int sp, int nb, size_t lds) {
   return sp == 0 ? particle_occupancy_t<0>(nb, lds) : particle_occupancy_t<1>(nb, lds);
 }
 
-// Dynamic LDS of the small-case kernel for a case: E, then the largest of
-// either species' particle region (which also holds the field solve's
-// scratch and the sort's counters).
-size_t small_lds_bytes(int ng, uint32_t flags, int n_eepf, int n_ifed) {
-  size_t region = (size_t)ng;
+// Dynamic LDS of the small-case kernel with nb threads for a case (see k_small).
+size_t small_lds_bytes(int nb, int ng, uint32_t flags, int n_eepf, int n_ifed) {
+  size_t sums = 0;  // of either species beyond E and the deposit
   for (int sp = 0; sp < 2; ++sp) {
-    const size_t r = particle_lds_bytes(ng, flags, n_eepf, n_ifed, sp) / 8 - (size_t)ng;
-    region = region > r ? region : r;
+    const size_t r = particle_lds_bytes(ng, flags, n_eepf, n_ifed, sp) / 8 - 2 * (size_t)ng;
+    sums = sums > r ? sums : r;
   }
-  return ((size_t)ng + region) * 8;
+  return ((size_t)(nb == 512 ? 5 : 2) * ng + sums) * 8;
 }
 
 size_t small_static_lds(int nb) {
@@ -2392,9 +2488,9 @@ size_t small_static_lds(int nb) {
 
 // One window of the small cases: workgroup b runs the case of roles[b] for
 // roles[b].j steps.
-hipError_t launch_small(const BlockRole* roles, int ncase, size_t lds, int mode, int sort_every, int pretest,
+hipError_t launch_small(const BlockRole* roles, int ncase, int nb, size_t lds, int mode, int sort_every, int pretest,
                         hipStream_t st) {
-  if (lds + small_static_lds(512) <= 65536) {
+  if (nb == 512) {
     if (mode == 1)
       hipLaunchKernelGGL((k_small<1, 512>), dim3(ncase), dim3(512), lds, st, roles, sort_every, pretest);
     else

@@ -24,8 +24,8 @@ and lose at another), so when the calibration run says that every
 combination fits in JOINT_BUDGET_SECONDS the tuner tries them all;
 otherwise one knob at a time: the sort interval, then the workgroups per
 CU at that interval.  Last, for a batch of several cases, the lockstep
-groups (each on a stream of its own, one group's launch ramp and tail
-overlapping another's streaming) at the chosen schedule.  The cases evolve while they are measured
+groups (one, or blocks of two side by side; 2, 3 and 4 are alike) at the
+chosen schedule.  The cases evolve while they are measured
 (a seeded plasma loses or gains particles for many cycles), so the
 candidates of a knob run in a mirrored order (A B C D D C B A) and each
 one's rate pools its two trials: a linear drift of the throughput cancels.

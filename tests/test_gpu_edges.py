@@ -116,3 +116,32 @@ def test_small_windows_equal_lockstep(ctx, cases, steps):
     for (ca, da, fa), (cb, db, fb) in zip(*got):
         assert ca == cb
         assert all(np.array_equal(x, y) for x, y in zip(da + fa, db + fb))
+
+
+@pytest.mark.parametrize("ng", [3, 12, 33, 400, 700])
+def test_small_measurements_equal_lockstep(ctx, ng):
+    """Every measurement of a small case, on grids from a few nodes (whose
+    sums stay in a CU's cache from step to step) to one whose measurement
+    arrays leave room for 256 threads only: the lockstep launches' sums."""
+    from paper_2103_09642_amd import edupic
+    say(f"test_small_measurements_equal_lockstep ng={ng}")
+    c = base_case(n_init_e=0, n_init_i=0, pressure_pa=40.0, weight=1e5, n_grid=ng, ion_subcycle=5, cap_e=30_000,
+                  cap_i=30_000, gamma_see=(0.2, 0.1), eta_refl=(0.2, 0.3), see_te_ev=2.0,
+                  flags=["allow_unstable", "density", "eepf", "current", "meane", "xt", "ifed"])
+    st = random_state(1_500, 1_400, c["gap_m"], seed=ng, te_ev=4.0, hot_frac=0.3, hot_ev=90.0, ion_energy_ev=30.0)
+    got = []
+    try:
+        for small in (0, 1 << 20):
+            ctx.set_option(edupic.OPT_SMALL_MAX, small)
+            g = ctx.create_case(c)
+            g.set_state(0, st["e"], 3)
+            g.set_state(1, st["i"], 3)
+            g.advance_steps(411)
+            got.append((g.counts(), g.deposit() + g.density() + g.eepf() + g.currents() + (g.mean_energy(),)
+                        + tuple(g.xt(q) for q in edupic.XT_NAMES) + tuple(g.ifed()) + g.fields()))
+            g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_SMALL_MAX, 0)
+    assert got[0][0] == got[1][0]
+    for a, b in zip(got[0][1], got[1][1]):
+        assert np.array_equal(a, b, equal_nan=True)

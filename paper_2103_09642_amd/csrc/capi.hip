@@ -70,6 +70,30 @@ int fail(int code, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(EDP_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
+// The context's device, current for a call's launches and waits (with the
+// default stream they go to whichever device is current), and the calling
+// thread's again after it: reads and state transfers launch kernels, and a
+// caller may read from a thread with another device current.
+struct OnDevice {
+  int was = -1;
+  hipError_t err;
+  explicit OnDevice(int device) {
+    err = hipGetDevice(&was);
+    if (err == hipSuccess && was != device)
+      err = hipSetDevice(device);
+    else
+      was = -1;
+  }
+  ~OnDevice() {
+    if (was >= 0) (void)hipSetDevice(was);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
+#define ON_DEVICE(ctx)                    \
+  const OnDevice on_device_((ctx)->device); \
+  HIPCHK(on_device_.err)
+
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) & ~(kAlign - 1); }
 
@@ -1742,6 +1766,7 @@ int edp_case_destroy(edp_ctx* ctx, edp_case id) {
   if (!ctx) return fail(EDP_EINVAL, "null context");
   Case* c = find(ctx, id);
   if (!c) return fail(EDP_EINVAL, "unknown case");
+  ON_DEVICE(ctx);
   (void)hipStreamSynchronize(ctx->stream);
   (void)sync_sides(ctx);
   for (Group& G : ctx->grp)
@@ -1810,6 +1835,7 @@ int edp_advance(edp_ctx* ctx, const edp_case* cases, int32_t n_cases, const int3
 
 int edp_sync(edp_ctx* ctx) {
   if (!ctx) return fail(EDP_EINVAL, "null context");
+  ON_DEVICE(ctx);
   HIPCHK(hipStreamSynchronize(ctx->stream));
   const int rs = sync_sides(ctx);
   if (rs) return rs;
@@ -1830,6 +1856,7 @@ int edp_read_counts(edp_ctx* ctx, edp_case id, edp_counts* out) {
   if (!ctx || !out) return fail(EDP_EINVAL, "null argument");
   Case* c = find(ctx, id);
   if (!c) return fail(EDP_EINVAL, "unknown case");
+  ON_DEVICE(ctx);
   CaseDev t;
   int r = read_dyn(ctx, c, t);
   if (r) return r;
@@ -1886,6 +1913,7 @@ static int read_grid(edp_ctx* ctx, Case* c, const void* dev, void* host, size_t 
 int edp_read_density(edp_ctx* ctx, edp_case id, double* ne, double* ni, int32_t n, int32_t reset) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !ne || !ni) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   CaseDev t;
@@ -1903,6 +1931,7 @@ int edp_read_density(edp_ctx* ctx, edp_case id, double* ne, double* ni, int32_t 
 int edp_read_eepf(edp_ctx* ctx, edp_case id, double* f, int64_t* counts, int32_t n, int32_t reset) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int nb = c->desc.n_eepf;
   if (n < nb) return fail(EDP_EINVAL, "output shorter than n_eepf");
   std::vector<int64_t> h(nb);
@@ -1921,6 +1950,7 @@ int edp_read_eepf(edp_ctx* ctx, edp_case id, double* f, int64_t* counts, int32_t
 int edp_read_currents(edp_ctx* ctx, edp_case id, double* je, double* ji, int32_t n, int32_t reset) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !je || !ji) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   HIPCHK(launch_fold(c->d, ctx->stream));
@@ -1941,6 +1971,7 @@ int edp_read_currents(edp_ctx* ctx, edp_case id, double* je, double* ji, int32_t
 int edp_read_mean_energy(edp_ctx* ctx, edp_case id, double* mee, int32_t n, int32_t reset) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !mee) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   HIPCHK(launch_fold(c->d, ctx->stream));
@@ -1954,6 +1985,7 @@ int edp_read_mean_energy(edp_ctx* ctx, edp_case id, double* mee, int32_t n, int3
 int edp_read_xt_steps(edp_ctx* ctx, edp_case id, int64_t* steps, int64_t* ion_steps, int32_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   if (!(c->desc.flags & EDP_DIAG_XT)) return fail(EDP_EINVAL, "the xt arrays are off for this case");
   const int nx = c->h.n_xt;
   if (n < nx) return fail(EDP_EINVAL, "output shorter than the number of xt bins");
@@ -1971,6 +2003,7 @@ int edp_read_xt_steps(edp_ctx* ctx, edp_case id, int64_t* steps, int64_t* ion_st
 int edp_read_xt(edp_ctx* ctx, edp_case id, int32_t q, double* out, int64_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !out || q < 0 || q >= EDP_XT_N) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   if (!(c->desc.flags & EDP_DIAG_XT)) return fail(EDP_EINVAL, "the xt arrays are off for this case");
   const int ng = c->desc.n_grid, nx = c->h.n_xt;
   const size_t cells = (size_t)nx * ng;
@@ -2040,6 +2073,7 @@ int edp_read_xt(edp_ctx* ctx, edp_case id, int32_t q, double* out, int64_t n) {
 int edp_read_ifed(edp_ctx* ctx, edp_case id, double* f_pow, double* f_gnd, int64_t* counts, int32_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   if (!(c->desc.flags & EDP_DIAG_IFED)) return fail(EDP_EINVAL, "the IFEDF is off for this case");
   const int nb = c->h.n_ifed;
   if (n < nb) return fail(EDP_EINVAL, "output shorter than n_ifed");
@@ -2062,6 +2096,7 @@ int edp_read_ifed(edp_ctx* ctx, edp_case id, double* f_pow, double* f_gnd, int64
 int edp_read_info(edp_ctx* ctx, edp_case id, double* out, int32_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !out) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   if (n < EDP_INFO_N) return fail(EDP_EINVAL, "output shorter than EDP_INFO_N");
   const int ng = c->desc.n_grid;
   const uint32_t fl = c->desc.flags;
@@ -2163,12 +2198,14 @@ int edp_set_voltage(edp_ctx* ctx, edp_case id, const double* v_amp, int32_t n_ha
 int edp_reset_diag(edp_ctx* ctx, edp_case id) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   return reset_diag(ctx, c);  // also clears the pending per-step sums
 }
 
 int edp_read_deposit(edp_ctx* ctx, edp_case id, int64_t* cnt_e, int64_t* cnt_i, int32_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || !cnt_e || !cnt_i) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   return read_parts(ctx, c, {{c->h.cnt_e, cnt_e, (size_t)ng, 1}, {c->h.cnt_i, cnt_i, (size_t)ng, 2}});
@@ -2177,6 +2214,7 @@ int edp_read_deposit(edp_ctx* ctx, edp_case id, int64_t* cnt_e, int64_t* cnt_i, 
 int edp_read_fields(edp_ctx* ctx, edp_case id, double* rho, double* phi, double* ef, int32_t n) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   const int ng = c->desc.n_grid;
   if (n < ng) return fail(EDP_EINVAL, "output shorter than n_grid");
   CaseDev t;
@@ -2204,6 +2242,7 @@ int edp_get_state(edp_ctx* ctx, edp_case id, int32_t species, double* x, double*
                   double* vz, uint64_t* uid, int64_t cap, int64_t* n_out) {
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || (species != 0 && species != 1) || cap < 0) return fail(EDP_EINVAL, "bad argument");
+  ON_DEVICE(ctx);
   CaseDev t;
   int r = read_dyn(ctx, c, t);
   if (r) return r;
@@ -2244,6 +2283,7 @@ int edp_set_state(edp_ctx* ctx, edp_case id, int32_t species, const double* x, c
   Case* c = ctx ? find(ctx, id) : nullptr;
   if (!c || (species != 0 && species != 1) || n < 0 || step < 0) return fail(EDP_EINVAL, "bad argument");
   if (n > 0 && (!x || !vx || !vy || !vz || !uid)) return fail(EDP_EINVAL, "null array");
+  ON_DEVICE(ctx);
   const SpeciesDev& S = c->h.sp[species];
   if (n > S.cap) return fail(EDP_ESTATE, "%lld particles exceed capacity %lld", (long long)n, (long long)S.cap);
   // the kernels rely on every live particle being inside [0, L] with finite
@@ -2307,6 +2347,7 @@ int edp_set_state(edp_ctx* ctx, edp_case id, int32_t species, const double* x, c
 
 int edp_set_option(edp_ctx* ctx, int32_t key, int64_t value) {
   if (!ctx) return fail(EDP_EINVAL, "null context");
+  ON_DEVICE(ctx);
   // every option changes what a captured step sequence contains (and some the
   // tables): drain both groups and rebuild on the next advance
   {
@@ -2370,6 +2411,7 @@ int edp_set_option(edp_ctx* ctx, int32_t key, int64_t value) {
 
 int edp_read_profile(edp_ctx* ctx, double* ms, int64_t* launches) {
   if (!ctx) return fail(EDP_EINVAL, "null context");
+  ON_DEVICE(ctx);
   HIPCHK(hipStreamSynchronize(ctx->stream));
   int r = drain_profile(ctx);
   if (r) return r;

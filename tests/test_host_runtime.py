@@ -1,0 +1,135 @@
+"""The library's host code on a stand-in for the HIP runtime
+(hip_host_model.cpp): which device its launches go to, what its pinned
+staging holds while other work is on its way, and the shapes it launches.
+No GPU: each scenario runs in a process of its own, in which the stand-in's
+symbols come before the real runtime's."""
+import ctypes as C
+import os
+import subprocess
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def model(tmp_path_factory):
+    from paper_2103_09642_amd import edupic
+    if not os.path.exists(edupic.LIB_PATH):
+        from paper_2103_09642_amd import build
+        build.build()
+    so = str(tmp_path_factory.mktemp("model") / "model.so")
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "paper_2103_09642_amd", "csrc"), os.path.join(HERE, "hip_host_model.cpp"),
+                    "-o", so], check=True)
+    return so
+
+
+def _scenario(model, name, *args):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), model, name, *map(str, args)], cwd=ROOT,
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+# ---------------------------------------------------------------------------
+# In the scenarios' process
+# ---------------------------------------------------------------------------
+class Lib:
+    """The library on the stand-in, without torch: contexts and cases by their handles."""
+
+    def __init__(self, model):
+        self.m = C.CDLL(model, mode=C.RTLD_GLOBAL)
+        self.m.model_log.restype = C.c_char_p
+        self.m.model_volt.restype = C.POINTER(C.c_double)
+        sys.modules["torch"] = None  # the binding then loads the library alone
+        from paper_2103_09642_amd import edupic, workloads
+        self.e, self.w, self.L = edupic, workloads, edupic.load()
+        self.keep = []
+
+    def ok(self, code):
+        assert code == 0, (code, self.L.edp_last_error())
+
+    def context(self, device=0, stream=None):
+        h = C.c_void_p()
+        self.ok(self.L.edp_create(C.byref(h), device, stream))
+        ctx = self.e.Context.__new__(self.e.Context)
+        ctx.h = h
+        ctx.set_xsec(self.w.synthetic_xsec())
+        self.keep.append(ctx)
+        return ctx
+
+    def stream(self):
+        s = C.c_void_p()
+        assert self.m.hipStreamCreateWithFlags(C.byref(s), 0) == 0
+        return s
+
+    def case(self, ctx, **kw):
+        kw = dict(dict(n_init_e=500, n_init_i=500, n_grid=50, weight=10.0, cap_e=5000, cap_i=5000, pressure_pa=5.0,
+                       flags=["allow_unstable"]), **kw)
+        d = self.w.base_case(**kw)
+        nbytes = ctx.case_bytes(d)
+        arena = np.zeros(nbytes + 256, dtype=np.uint8)
+        at = (arena.ctypes.data + 255) // 256 * 256
+        i = C.c_int64()
+        desc = self.e.make_desc(d)
+        self.ok(self.L.edp_case_create(ctx.h, C.byref(desc), at, nbytes, C.byref(i)))
+        c = self.e.Case.__new__(self.e.Case)
+        c.ctx, c.case, c.ng, c.id, c.arena, c.at = ctx, d, d["n_grid"], i.value, arena, at
+        self.keep.append(c)
+        return c
+
+    def advance(self, ctx, cases, steps):
+        n = len(cases)
+        return self.L.edp_advance_steps(ctx.h, (C.c_int64 * n)(*[c.id for c in cases]), n, (C.c_int64 * n)(*steps))
+
+    def launches(self, name=""):
+        out = []
+        for line in self.m.model_log().decode().splitlines():
+            f = line.split()
+            if f[0] == "launch" and name in f[1]:
+                out.append(dict([("name", f[1])] + [(k, int(v)) for k, v in (q.split("=") for q in f[2:])]))
+        return out
+
+    def volts(self, case, steps):
+        """V(t_s) of steps 0 .. steps - 1 as the case's device memory holds it, and as it should be."""
+        d = case.case
+        want = np.zeros(steps)
+        t = np.arange(steps) * d["dt_e"]
+        for v, f, ph in d["harmonics"]:
+            want += v * np.sin(2 * np.pi * f * t + ph)
+        return np.ctypeslib.as_array(self.m.model_volt(C.c_void_p(case.at)), (steps,)), want
+
+
+def scenario_device(lib):
+    """A context on device 1 whose stream is the default one, called from a thread whose device is 0."""
+    ctx = lib.context(device=1)
+    g = lib.case(ctx, flags=["allow_unstable", "density", "eepf", "current", "meane", "xt", "ifed"])
+    st = lib.w.random_state(300, 300, g.case["gap_m"], seed=1)
+    calls = {"counts": g.counts, "deposit": g.deposit, "fields": g.fields, "density": lambda: g.density(reset=True),
+             "eepf": g.eepf, "currents": g.currents, "mean_energy": g.mean_energy, "xt": lambda: g.xt("ne"),
+             "ifed": g.ifed, "info": g.info, "reset_diag": g.reset_diag, "get_state": lambda: g.get_state(0),
+             "set_state": lambda: g.set_state(0, st["e"], 5)}
+    for name, call in calls.items():
+        lib.m.hipSetDevice(0)
+        lib.m.model_clear()
+        call()
+        assert all(q["dev"] == 1 for q in lib.launches()), (name, lib.launches())
+        assert lib.m.model_device() == 0, f"{name} left another device current"
+
+
+if __name__ == "__main__":
+    sys.path.insert(0, ROOT)
+    globals()["scenario_" + sys.argv[2]](Lib(sys.argv[1]), *map(int, sys.argv[3:]))
+
+
+# ---------------------------------------------------------------------------
+# The tests
+# ---------------------------------------------------------------------------
+def test_reads_and_transfers_launch_on_the_contexts_device(model):
+    """Reads and state transfers launch on their context's device, whichever
+    is current in the calling thread, and leave that one current."""
+    _scenario(model, "device")

@@ -1158,29 +1158,39 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
     }
     HIPCHK(hipMemcpyAsync(ctx->small_roles, roles.data(), roles.size() * sizeof(BlockRole), hipMemcpyHostToDevice, st));
   }
-  for (size_t k = 0; k < wins.size() && r == EDP_OK; ++k) {
-    const Win& W = wins[k];
-    for (size_t a = W.lo; a < W.hi && r == EDP_OK; ++a) {
-      r = stage_volt(who[a], who[a]->step, who[a]->step + roles[a].j);
+  auto window = [&](const Win& W) -> int {
+    for (size_t a = W.lo; a < W.hi; ++a) {
+      const int e = stage_volt(who[a], who[a]->step, who[a]->step + roles[a].j);
+      if (e) return e;
       who[a]->v_ev = ctx->small_join;
     }
-    if (r) break;
-    HIPCHK(launch_small_volt(ctx->small_roles + W.lo, (int)(W.hi - W.lo), st));
-    HIPCHK(launch_small(ctx->small_roles + W.lo, (int)(W.hi - W.lo), nb, lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
+    const int n = (int)(W.hi - W.lo);
+    HIPCHK(launch_small_volt(ctx->small_roles + W.lo, n, st));
+    HIPCHK(launch_small(ctx->small_roles + W.lo, n, nb, lds, ctx->poisson, ctx->sort_every, ctx->pretest, st));
     for (size_t a = W.lo; a < W.hi; ++a) who[a]->step += roles[a].j;
     HIPCHK(hipEventRecord(ctx->small_join, st));  // the staging of this window and before is free
+    return EDP_OK;
+  };
+  auto end = [&]() -> int {
+    if (roles.size() > ends) HIPCHK(launch_small_end(ctx->small_roles + ends, (int)(roles.size() - ends), st));
+    HIPCHK(hipEventRecord(ctx->small_join, st));
+    HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->small_join, 0));
+    return EDP_OK;
+  };
+  for (size_t k = 0; k < wins.size() && r == EDP_OK; ++k) r = window(wins[k]);
+  if (r == EDP_OK) r = end();
+  if (r != EDP_OK) {
+    // nothing of it may still run when the caller goes on: the windows before
+    // are not joined to the caller's stream, and the staging is also the reads'
+    (void)hipStreamSynchronize(st);
+    for (Case* c : cases) c->v_ev = nullptr;
+    return r;
   }
-  if (r == EDP_OK && roles.size() > ends) {
-    HIPCHK(launch_small_end(ctx->small_roles + ends, (int)(roles.size() - ends), st));
-    for (size_t a = ends; a < roles.size(); ++a) {
-      who[a]->est_wait = ctx->small_join;
-      who[a]->est_pending = true;
-    }
+  for (size_t a = ends; a < roles.size(); ++a) {
+    who[a]->est_wait = ctx->small_join;
+    who[a]->est_pending = true;
   }
-  const hipError_t e = hipEventRecord(ctx->small_join, st);
-  const hipError_t w = e == hipSuccess ? hipStreamWaitEvent(ctx->stream, ctx->small_join, 0) : e;
-  if (w != hipSuccess && r == EDP_OK) r = fail(EDP_EHIP, "joining the small cases: %s", hipGetErrorString(w));
-  return r;
+  return EDP_OK;
 }
 
 int run_lockstep(edp_ctx* ctx, const std::vector<Case*>& cases, const std::vector<int64_t>& n);

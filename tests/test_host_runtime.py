@@ -121,9 +121,28 @@ def scenario_device(lib):
         assert lib.m.model_device() == 0, f"{name} left another device current"
 
 
+def scenario_small_failure(lib):
+    """The second window of the persistent small cases cannot be launched."""
+    ctx = lib.context(stream=lib.stream())
+    ctx.set_option(lib.e.OPT_SMALL_MAX, 1 << 20)
+    cases = [lib.case(ctx, seed=k) for k in range(2)]
+    lib.m.model_fail(b"7k_small", 2)
+    assert lib.advance(ctx, cases, [10_000] * 2) == lib.e.EDP_EHIP
+    for g in cases:
+        g.counts()
+    lib.m.model_finish()
+    for g in cases:
+        got, want = lib.volts(g, 4096)
+        assert np.allclose(got, want, rtol=1e-9, atol=1e-9)
+    # and the context goes on
+    lib.ok(lib.advance(ctx, cases, [50] * 2))
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
-    globals()["scenario_" + sys.argv[2]](Lib(sys.argv[1]), *map(int, sys.argv[3:]))
+    the_lib = Lib(sys.argv[1])
+    globals()["scenario_" + sys.argv[2]](the_lib, *map(int, sys.argv[3:]))
+    os._exit(0)  # contexts and arenas go with the process, in no order
 
 
 # ---------------------------------------------------------------------------
@@ -133,3 +152,9 @@ def test_reads_and_transfers_launch_on_the_contexts_device(model):
     """Reads and state transfers launch on their context's device, whichever
     is current in the calling thread, and leave that one current."""
     _scenario(model, "device")
+
+
+def test_a_failed_small_case_window_leaves_nothing_under_way(model):
+    """An advance of small cases that fails between its windows has ended what
+    it had launched: a read after it does not get into their voltages."""
+    _scenario(model, "small_failure")

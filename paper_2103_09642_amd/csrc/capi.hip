@@ -211,8 +211,13 @@ struct edp_ctx {
   // cases of at most this many slots per species (estimate) run in the
   // persistent one-workgroup-per-case kernel (0: none)
   int64_t small_max = 0;
+  // the cases' pinned staging: held from its filling to the record of the event
+  // that ends its use, and by reads and state transfers (a thread may read
+  // while another advances)
+  std::mutex pin_mu;
+  // an advance uploads V(t) on streams that `stream` does not wait for yet
+  bool forked = false;
   // the persistent small cases' stream (default priority) and role table
-  std::mutex pin_mu;  // the cases' pinned staging in reads and state transfers (of several threads)
   hipStream_t small_stream = nullptr;
   hipEvent_t small_join = nullptr;
   BlockRole* small_roles = nullptr;
@@ -467,6 +472,14 @@ constexpr int64_t kStateChunk = 10240;
 static_assert((size_t)kStateChunk * 48 <= kPinBytes && kStateChunk % 2 == 0, "a chunk of every array");
 constexpr int kStateBlocks = 16;  // workgroups per array of a transfer
 
+// With pin_mu held: work enqueued on the context's stream from here on uses
+// the staging after the V(t) on its way from it (another thread's advance may
+// have uploaded it on a stream of its own).
+int staging_after_upload(edp_ctx* ctx, Case* c) {
+  if (c->v_ev && ctx->forked) HIPCHK(hipStreamWaitEvent(ctx->stream, c->v_ev, 0));
+  return EDP_OK;
+}
+
 // Parts of a case's device memory (n words each, see GatherPart) to the host,
 // after all work on the context's stream: one launch into pinned memory and
 // one wait.
@@ -478,6 +491,8 @@ struct ReadPart {
 };
 int read_parts(edp_ctx* ctx, Case* c, std::initializer_list<ReadPart> parts) {
   std::lock_guard<std::mutex> lock(ctx->pin_mu);
+  const int r = staging_after_upload(ctx, c);
+  if (r) return r;
   GatherParts P{};
   size_t at = 0;
   int k = 0;
@@ -547,7 +562,8 @@ int stage_volt(Case* c, int64_t s0, int64_t s1) {
 }
 
 // Upload V(t_s) for steps [s0, s1) (s1 - s0 <= kVoltChunk) into the ring.
-int upload_volt(Case* c, int64_t s0, int64_t s1, hipStream_t st) {
+int upload_volt(edp_ctx* ctx, Case* c, int64_t s0, int64_t s1, hipStream_t st) {
+  std::lock_guard<std::mutex> lock(ctx->pin_mu);
   const int r = stage_volt(c, s0, s1);
   if (r) return r;
   const int64_t n = s1 - s0;
@@ -1030,7 +1046,7 @@ struct Window {
       if (gsteps <= w) w = (w / gsteps) * gsteps; else gsteps = 0;
     }
     for (Case* c : act) {
-      r = upload_volt(c, c->step, c->step + w, G.stream);
+      r = upload_volt(ctx, c, c->step, c->step + w, G.stream);
       if (r) return r;
     }
     return EDP_OK;
@@ -1082,6 +1098,20 @@ int group_window(edp_ctx* ctx, Group& G, const std::vector<Case*>& cases, std::v
   while (r == EDP_OK && W.j < W.w) r = W.some(ctx, G, W.w);
   return r ? r : W.close(ctx, G, cases, left);
 }
+
+// While it lives, an advance uploads V(t) on streams the context's does not
+// wait for (see staging_after_upload).
+struct Forked {
+  edp_ctx* ctx;
+  explicit Forked(edp_ctx* c) : ctx(c) { set(true); }
+  ~Forked() { set(false); }
+  Forked(const Forked&) = delete;
+  Forked& operator=(const Forked&) = delete;
+  void set(bool on) {
+    std::lock_guard<std::mutex> lock(ctx->pin_mu);
+    ctx->forked = on;
+  }
+};
 
 // Whether a case runs in the persistent one-workgroup-per-case kernel: few
 // enough slots (estimate) and its LDS within one workgroup's 64 KiB.
@@ -1158,7 +1188,8 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
     }
     HIPCHK(hipMemcpyAsync(ctx->small_roles, roles.data(), roles.size() * sizeof(BlockRole), hipMemcpyHostToDevice, st));
   }
-  auto window = [&](const Win& W) -> int {
+  const Forked forked(ctx);
+  auto launch = [&](const Win& W) -> int {
     for (size_t a = W.lo; a < W.hi; ++a) {
       const int e = stage_volt(who[a], who[a]->step, who[a]->step + roles[a].j);
       if (e) return e;
@@ -1171,21 +1202,22 @@ int run_small(edp_ctx* ctx, const std::vector<Case*>& cases, std::vector<int64_t
     HIPCHK(hipEventRecord(ctx->small_join, st));  // the staging of this window and before is free
     return EDP_OK;
   };
-  auto end = [&]() -> int {
+  auto join = [&]() -> int {
     if (roles.size() > ends) HIPCHK(launch_small_end(ctx->small_roles + ends, (int)(roles.size() - ends), st));
     HIPCHK(hipEventRecord(ctx->small_join, st));
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->small_join, 0));
     return EDP_OK;
   };
-  for (size_t k = 0; k < wins.size() && r == EDP_OK; ++k) r = window(wins[k]);
-  if (r == EDP_OK) r = end();
-  if (r != EDP_OK) {
+  for (size_t k = 0; k <= wins.size() && r == EDP_OK; ++k) {
+    std::lock_guard<std::mutex> lock(ctx->pin_mu);
+    r = k < wins.size() ? launch(wins[k]) : join();
+    if (r == EDP_OK) continue;
     // nothing of it may still run when the caller goes on: the windows before
     // are not joined to the caller's stream, and the staging is also the reads'
     (void)hipStreamSynchronize(st);
     for (Case* c : cases) c->v_ev = nullptr;
-    return r;
   }
+  if (r) return r;
   for (size_t a = ends; a < roles.size(); ++a) {
     who[a]->est_wait = ctx->small_join;
     who[a]->est_pending = true;
@@ -1324,6 +1356,7 @@ int run_lockstep(edp_ctx* ctx, const std::vector<Case*>& cases, const std::vecto
   }
   while (ctx->grp.size() < used) ctx->grp.emplace_back();
   int r = EDP_OK;
+  const Forked forked(ctx);
   std::vector<char> done(nb, 0);
   while (r == EDP_OK && !std::all_of(done.begin(), done.end(), [](char d) { return d != 0; })) {
     size_t at = 0;
@@ -2260,6 +2293,7 @@ int edp_get_state(edp_ctx* ctx, edp_case id, int32_t species, double* x, double*
   const int set = t.cur[species];
   const SpeciesDev& S = c->h.sp[species];
   std::lock_guard<std::mutex> lock(ctx->pin_mu);
+  if ((r = staging_after_upload(ctx, c))) return r;
   double *hx = c->vstage, *hvx = hx + kStateChunk, *hvy = hvx + kStateChunk, *hvz = hvy + kStateChunk;
   uint64_t* hu = (uint64_t*)(hvz + kStateChunk);
   int64_t m = 0;
@@ -2310,6 +2344,8 @@ int edp_set_state(edp_ctx* ctx, edp_case id, int32_t species, const double* x, c
   if (r) return r;
   if (n > 0) {
     std::lock_guard<std::mutex> lock(ctx->pin_mu);
+    if (c->v_ev) HIPCHK(hipEventSynchronize(c->v_ev));  // of another thread since the read above
+    c->v_ev = nullptr;
     for (int64_t i0 = 0; i0 < n; i0 += kStateChunk) {
       const int64_t w = std::min(kStateChunk, n - i0);
       const void* from[5] = {x + i0, vx + i0, vy + i0, vz + i0, uid + i0};

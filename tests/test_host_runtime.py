@@ -138,6 +138,35 @@ def scenario_small_failure(lib):
     lib.ok(lib.advance(ctx, cases, [50] * 2))
 
 
+def scenario_read_beside_advance(lib, n_cases, small):
+    """Another thread reads while the voltages of an advance are on their way to the device."""
+    ctx = lib.context(stream=lib.stream())
+    ctx.set_option(lib.e.OPT_SMALL_MAX, small)
+    cases = [lib.case(ctx, seed=k) for k in range(n_cases)]
+    readers = []
+
+    def read():
+        for g in cases:
+            g.counts()
+            g.deposit()
+            g.get_state(0)
+
+    @C.CFUNCTYPE(None)
+    def hook():
+        readers.append(threading.Thread(target=read))
+        readers[0].start()
+        readers[0].join(0.3)  # it may have to wait for this thread
+
+    # an upload (the first copy is that of the workgroups' roles); small cases' by one launch
+    lib.m.model_hook(b"k_small_volt" if small else b"copy from pinned", 1 if small else n_cases + 1, hook)
+    lib.ok(lib.advance(ctx, cases, [6000] * n_cases))
+    readers[0].join()
+    lib.m.model_finish()
+    for g in cases:
+        got, want = lib.volts(g, 6000)
+        assert np.allclose(got, want, rtol=1e-9, atol=1e-9)
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -158,3 +187,10 @@ def test_a_failed_small_case_window_leaves_nothing_under_way(model):
     """An advance of small cases that fails between its windows has ended what
     it had launched: a read after it does not get into their voltages."""
     _scenario(model, "small_failure")
+
+
+@pytest.mark.parametrize("n_cases,small", [(1, 0), (3, 0), (3, 1 << 20)], ids=["one", "side-by-side", "small"])
+def test_a_read_beside_an_advance_leaves_its_voltages_alone(model, n_cases, small):
+    """Reads and transfers use the memory the voltages are uploaded from: one
+    from another thread waits for the upload."""
+    _scenario(model, "read_beside_advance", n_cases, small)

@@ -150,9 +150,12 @@ extern "C" {
                                  own forked from and joined back into its
                                  stream; 0 (default) none.  Results do not
                                  depend on it, speed does */
-#define EDP_OPT_PART_WG_PER_CU 9 /* resident particle workgroups per CU a batch
+#define EDP_OPT_PART_WG_PER_CU 9 /* resident particle workgroups per CU a launch
                                  uses: 0 (default) all that fit, k >= 1 at
-                                 most k; results do not depend on it, speed
+                                 most k of 256 threads, or as many threads in
+                                 workgroups of 512; of two lockstep groups
+                                 side by side each takes three quarters of
+                                 them.  Results do not depend on it, speed
                                  does: the autotuner (tune.py) picks it       */
 #define EDP_OPT_PART_SKEW 13   /* per mille, 0..900, or -1 (default):
                                  a particle launch's workgroups are

@@ -773,11 +773,13 @@ int sort_blocks(const edp_ctx* ctx, const Case* c, int sp) { return std::max(1, 
 // 21.5, 6e5 27.4 24.7; of 400 nodes, 1.8e5 19.8 20.1, 3e5 23.5 21.7; of 2048
 // nodes, 6e4 15.5 14.7, 3e5 21.6 20.1.
 int particle_block(const edp_ctx* ctx, const std::vector<Case*>& cs, int sp, int max_ng, size_t lds) {
-  // an explicit single workgroup per CU is one of 256 threads
-  if (ctx->part_wg_per_cu == 1 || lds + particle_static_lds(sp, 512) > 65536) return 256;
+  if (lds + particle_static_lds(sp, 512) > 65536) return 256;
+  const int occ = particle_occupancy(sp, 256, lds);
+  // an explicit share that only workgroups of 256 give
+  if (ctx->part_wg_per_cu % 2 != 0 && ctx->part_wg_per_cu < occ) return 256;
   int64_t chunks = 0;
   for (const Case* c : cs) chunks += est_chunks(c, sp);
-  const int64_t resident = (int64_t)ctx->num_cu * particle_occupancy(sp, 256, lds);
+  const int64_t resident = (int64_t)ctx->num_cu * occ;
   return chunks >= resident || max_ng > 1024 ? 512 : 256;
 }
 
@@ -803,9 +805,10 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   for (int sp = 0; sp < 2; ++sp) nb[sp] = particle_block(ctx, cs, sp, max_ng, lds[sp]);
   std::vector<int> want[2];
   for (int sp = 0; sp < 2; ++sp) {
-    const int occ = particle_occupancy(sp, nb[sp], lds[sp]);
-    // the option counts workgroups of 256 threads
-    const int per_cu = ctx->part_wg_per_cu > 0 ? std::min(std::max(1, ctx->part_wg_per_cu * 256 / nb[sp]), occ) : occ;
+    // the option counts workgroups of 256 threads (an odd number of them, fewer
+    // than fit, is launched as such: see particle_block)
+    const int occ = particle_occupancy(sp, nb[sp], lds[sp]), cap = ctx->part_wg_per_cu;
+    const int per_cu = cap == 0 || cap >= particle_occupancy(sp, 256, lds[sp]) ? occ : std::min(cap * 256 / nb[sp], occ);
     // of two groups side by side each asks for three quarters of the slots: the
     // second's workgroups fill what the first's leave at their ends (all of
     // them, three quarters, half, us a step: 8 mixed cases 32.8 29.2 27.4, 32

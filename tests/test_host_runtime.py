@@ -167,6 +167,20 @@ def scenario_read_beside_advance(lib, n_cases, small):
         assert np.allclose(got, want, rtol=1e-9, atol=1e-9)
 
 
+def scenario_workgroups_per_cu(lib):
+    """Threads of a full chip's launches (8 CUs, each with room for 1024 particle threads) by the option."""
+    lib.m.model_cus(8)
+    ctx = lib.context(stream=lib.stream())
+    g = lib.case(ctx, n_init_e=30_000, n_init_i=30_000, cap_e=40_000, cap_i=40_000)
+    for k in (0, 1, 2, 3, 4, 5, 7, 64):
+        ctx.set_option(lib.e.OPT_PART_WG_PER_CU, k)
+        lib.m.model_clear()
+        lib.ok(lib.advance(ctx, [g], [1]))
+        for q in lib.launches("11k_particles"):
+            assert q["grid"] * q["block"] == 8 * 256 * (min(k, 4) or 4), (k, q)
+        lib.m.model_finish()
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -194,3 +208,9 @@ def test_a_read_beside_an_advance_leaves_its_voltages_alone(model, n_cases, smal
     """Reads and transfers use the memory the voltages are uploaded from: one
     from another thread waits for the upload."""
     _scenario(model, "read_beside_advance", n_cases, small)
+
+
+def test_the_workgroup_option_gives_its_share_of_the_wave_slots(model):
+    """EDP_OPT_PART_WG_PER_CU = k: k workgroups of 256 threads per CU, or as
+    many threads in larger ones."""
+    _scenario(model, "workgroups_per_cu")

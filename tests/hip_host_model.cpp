@@ -125,6 +125,11 @@ void model_fail(const char* name, int nth) { fail_name = name, fail_nth = nth; }
 void model_hook(const char* name, int nth, void (*f)()) { hook_name = name, hook_nth = nth, hook = f; }
 int model_device() { return device; }
 const double* model_volt(const CaseDev* c) { return c->volt; }  // the device's V(t_s)
+void model_arrays(const CaseDev* c, int sp, void** out) {
+  const SpeciesDev& S = c->sp[sp];
+  void* a[6] = {S.x[0], S.vx[0], S.vy[0], S.vz[0], S.uid[0], S.vp2[0]};
+  memcpy(out, a, sizeof a);
+}
 void model_finish() {
   std::lock_guard<std::recursive_mutex> l(mu);
   for (Stream* s : streams) drain(s, INT64_MAX);

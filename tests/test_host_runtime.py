@@ -103,6 +103,16 @@ class Lib:
             want += v * np.sin(2 * np.pi * f * t + ph)
         return np.ctypeslib.as_array(self.m.model_volt(C.c_void_p(case.at)), (steps,)), want
 
+    def particles(self, case, sp, n):
+        """The first n slots of a species' first buffer set."""
+        at = (C.c_void_p * 6)()
+        self.m.model_arrays(C.c_void_p(case.at), sp, at)
+        out = {k: np.ctypeslib.as_array(C.cast(at[i], C.POINTER(C.c_double)), (n,)) for i, k in enumerate(("x", "vx", "vy", "vz"))}
+        out["uid"] = np.ctypeslib.as_array(C.cast(at[4], C.POINTER(C.c_uint64)), (n,))
+        if sp == 0:
+            out["vp2"] = np.ctypeslib.as_array(C.cast(at[5], C.POINTER(C.c_float)), (n,)).astype(np.float64)
+        return out
+
 
 def scenario_device(lib):
     """A context on device 1 whose stream is the default one, called from a thread whose device is 0."""
@@ -181,6 +191,23 @@ def scenario_workgroups_per_cu(lib):
         lib.m.model_finish()
 
 
+def scenario_large_state(lib, n):
+    """Waits for the stream in a state load of n particles; they arrive whole and in order."""
+    ctx = lib.context(stream=lib.stream())
+    g = lib.case(ctx, n_init_e=0, n_init_i=0, cap_e=n + 10, cap_i=n + 10)
+    st = lib.w.random_state(n, n, g.case["gap_m"], seed=1)
+    for sp, key in ((0, "e"), (1, "i")):
+        lib.m.model_clear()
+        g.set_state(sp, st[key], 5)
+        assert lib.m.model_log().count(b"wait") <= 12, lib.m.model_log()
+        have = lib.particles(g, sp, n)
+        for k in ("x", "vx", "vy", "vz", "uid"):
+            assert np.array_equal(have[k], st[key][k]), k
+        if sp == 0:
+            v2 = st[key]["vy"] ** 2 + st[key]["vz"] ** 2
+            assert np.all(have["vp2"] >= v2) and np.all(have["vp2"] <= v2 * (1 + 2.0 ** -22))
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -214,3 +241,10 @@ def test_the_workgroup_option_gives_its_share_of_the_wave_slots(model):
     """EDP_OPT_PART_WG_PER_CU = k: k workgroups of 256 threads per CU, or as
     many threads in larger ones."""
     _scenario(model, "workgroups_per_cu")
+
+
+@pytest.mark.parametrize("n", [10_240, 61_440, 61_441, 300_001])
+def test_a_state_load_does_not_wait_chunk_by_chunk(model, n):
+    """A load goes through the pinned staging in chunks, a wait each, only
+    while that is the faster way."""
+    _scenario(model, "large_state", n)

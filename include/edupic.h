@@ -135,10 +135,12 @@ extern "C" {
                                  blocks' windows follow one another, and a
                                  block runs as two groups side by side on
                                  streams the library creates (default
-                                 priority), so that one group's launch ramp
-                                 and tail overlap the other's streaming; work
-                                 enqueued later on the context's
-                                 stream is ordered after every group.
+                                 priority; one of them on the context's in a
+                                 call of a few steps), so that one group's
+                                 launch ramp and tail overlap the other's
+                                 streaming; work enqueued later on the
+                                 context's stream is ordered after every
+                                 group.
                                  Results do not depend on it, speed does: the
                                  autotuner (tune.py) picks it */
 #define EDP_OPT_SMALL_MAX 12   /* cases with at most this many particle slots

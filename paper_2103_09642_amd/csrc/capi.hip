@@ -227,10 +227,8 @@ struct edp_ctx {
   // on streams of their own, forked from and joined back into `stream` by an
   // advance
   std::deque<Group> grp;
-  // the streams of groups side by side (default priority) and the events the
-  // caller's stream waits on
+  // streams for groups side by side (default priority)
   hipStream_t side[kSide] = {};
-  hipEvent_t side_end[kSide] = {};
   hipEvent_t fork_ev = nullptr;
   // the allocation-free advance (edp_advance_steps_noalloc): one group on
   // `stream` whose role table is the device's scratch array
@@ -665,9 +663,7 @@ void destroy_streams(edp_ctx* ctx) {
   ctx->small_join = nullptr;
   for (int g = 0; g < kSide; ++g) {
     if (ctx->side[g]) (void)hipStreamDestroy(ctx->side[g]);
-    if (ctx->side_end[g]) (void)hipEventDestroy(ctx->side_end[g]);
     ctx->side[g] = nullptr;
-    ctx->side_end[g] = nullptr;
   }
 }
 
@@ -1303,6 +1299,19 @@ std::vector<CaseList> split_cases(const std::vector<Case*>& cases, const std::ve
   return out;
 }
 
+// Whether the first of two groups side by side stays on the context's stream
+// in a window of `steps` steps that streams `bytes` a step, instead of a stream
+// of its own that waits for the context's and that it waits for.  Two waits
+// less, 30-40 us a call (8 mixed cases, 5 steps a call: 210 -> 180 us).  But the
+// runtime may have given the caller's stream the hardware queue of the other
+// group's, as it does not two streams created together, and the groups then
+// run one after the other: a third of the streaming time and some 6 us a step
+// (64 mixed cases 94 -> 130 us a step).  So only while that is less.
+bool first_on_context(const edp_ctx* ctx, int64_t steps, double bytes) {
+  // not on the default stream, which no graph is captured on
+  return ctx->stream && (double)steps * (bytes / 3.0 / 4.7e6 + 6.0) <= 40.0;
+}
+
 // One window of the groups G[0..parts.size()) side by side.
 int side_window(edp_ctx* ctx, Group** G, std::vector<CaseList>& parts, bool& done) {
   const size_t ng = parts.size();
@@ -1311,36 +1320,45 @@ int side_window(edp_ctx* ctx, Group** G, std::vector<CaseList>& parts, bool& don
     G[0]->side = false;
     return group_window(ctx, *G[0], parts[0].cases, parts[0].left, done);
   }
+  int64_t steps = 0;  // of the longer window
+  double bytes = 0.0;
+  for (const CaseList& p : parts) {
+    int64_t w = 0;
+    for (size_t k = 0; k < p.cases.size(); ++k)
+      if (p.left[k] > 0) {
+        w = w > 0 ? std::min(w, p.left[k]) : p.left[k];
+        bytes += streamed_bytes(p.cases[k]);
+      }
+    steps = std::max(steps, w);
+  }
+  // a call's last look, with no steps left, waits for nothing (it cost as much
+  // as its window: 8 mixed cases, 5 steps a call, 240 -> 210 us)
+  done = steps == 0;
+  if (done) return EDP_OK;
+  const bool on_context = first_on_context(ctx, steps, bytes);
   HIPCHK(hipEventRecord(ctx->fork_ev, ctx->stream));
   std::vector<Window> W(ng);
   int r = EDP_OK;
   for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
-    G[g]->stream = ctx->side[g];
+    G[g]->stream = g == 0 && on_context ? ctx->stream : ctx->side[g];
     G[g]->side = true;
-    HIPCHK(hipStreamWaitEvent(ctx->side[g], ctx->fork_ev, 0));
+    if (G[g]->stream != ctx->stream) HIPCHK(hipStreamWaitEvent(G[g]->stream, ctx->fork_ev, 0));
     r = W[g].open(ctx, *G[g], parts[g].cases, parts[g].left);
   }
   // a few steps of each in turn, so that none waits for the enqueueing of
   // another's whole window
+  constexpr int64_t kTurn = 16;
   for (bool more = true; more && r == EDP_OK;) {
     more = false;
     for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
-      r = W[g].some(ctx, *G[g], 16);
+      r = W[g].some(ctx, *G[g], kTurn);
       more = more || W[g].j < W[g].w;
     }
   }
-  done = true;
   for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
     if (W[g].act.empty()) continue;
-    done = false;
     r = W[g].close(ctx, *G[g], parts[g].cases, parts[g].left);
-  }
-  // the joins also after a failed window: whatever the groups did enqueue
-  // stays ordered before later work on the caller's stream
-  for (size_t g = 0; g < ng; ++g) {
-    const hipError_t e = hipEventRecord(ctx->side_end[g], ctx->side[g]);
-    const hipError_t w = e == hipSuccess ? hipStreamWaitEvent(ctx->stream, ctx->side_end[g], 0) : e;
-    if (w != hipSuccess && r == EDP_OK) r = fail(EDP_EHIP, "joining group %d: %s", (int)g, hipGetErrorString(w));
+    if (r == EDP_OK && G[g]->stream != ctx->stream) HIPCHK(hipStreamWaitEvent(ctx->stream, G[g]->last, 0));
   }
   return r;
 }
@@ -1371,7 +1389,8 @@ int run_lockstep(edp_ctx* ctx, const std::vector<Case*>& cases, const std::vecto
       if (d) done[b] = 1;
     }
   }
-  // after a failed window the groups' events may be older than what it enqueued
+  // after a failed window the groups' events may be older than what it
+  // enqueued, and the context's stream does not wait for the others
   if (r != EDP_OK) {
     (void)hipStreamSynchronize(ctx->stream);
     (void)sync_sides(ctx);
@@ -1501,8 +1520,7 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
             hipStreamCreateWithFlags(&ctx->small_stream, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->small_join, hipEventDisableTiming) == hipSuccess;
   for (int g = 0; g < kSide && ok; ++g)
-    ok = hipStreamCreateWithFlags(&ctx->side[g], hipStreamNonBlocking) == hipSuccess &&
-         hipEventCreateWithFlags(&ctx->side_end[g], hipEventDisableTiming) == hipSuccess;
+    ok = hipStreamCreateWithFlags(&ctx->side[g], hipStreamNonBlocking) == hipSuccess;
   if (!ok) {
     destroy_streams(ctx);
     delete ctx;

@@ -125,6 +125,7 @@ void model_fail(const char* name, int nth) { fail_name = name, fail_nth = nth; }
 void model_hook(const char* name, int nth, void (*f)()) { hook_name = name, hook_nth = nth, hook = f; }
 int model_device() { return device; }
 const double* model_volt(const CaseDev* c) { return c->volt; }  // the device's V(t_s)
+int64_t model_step(const CaseDev* c) { return c->step; }
 void model_arrays(const CaseDev* c, int sp, void** out) {
   const SpeciesDev& S = c->sp[sp];
   void* a[6] = {S.x[0], S.vx[0], S.vy[0], S.vz[0], S.uid[0], S.vp2[0]};
@@ -271,6 +272,7 @@ hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t e, unsigned) {
   std::lock_guard<std::recursive_mutex> l(mu);
   const Event v = *(Event*)e;
   if (v.s) push(stream_of(st), [v] { drain(v.s, v.id); });
+  say("order stream=%d\n", stream_of(st)->n);
   return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEvent_t) new Event, hipSuccess; }

@@ -45,6 +45,7 @@ class Lib:
         self.m = C.CDLL(model, mode=C.RTLD_GLOBAL)
         self.m.model_log.restype = C.c_char_p
         self.m.model_volt.restype = C.POINTER(C.c_double)
+        self.m.model_step.restype = C.c_int64
         sys.modules["torch"] = None  # the binding then loads the library alone
         from paper_2103_09642_amd import edupic, workloads
         self.e, self.w, self.L = edupic, workloads, edupic.load()
@@ -208,6 +209,22 @@ def scenario_large_state(lib, n):
             assert np.all(have["vp2"] >= v2) and np.all(have["vp2"] <= v2 * (1 + 2.0 ** -22))
 
 
+def scenario_side_by_side(lib, n_cases, steps, own_stream, most):
+    """The waits between streams of a call, and that the caller's stream is behind all of its work."""
+    stream = lib.stream() if own_stream else None
+    ctx = lib.context(stream=stream)
+    cases = [lib.case(ctx, seed=k) for k in range(n_cases)]
+    for call in (1, 2):
+        lib.m.model_clear()
+        lib.ok(lib.advance(ctx, cases, [steps + k // 2 for k in range(n_cases)]))
+        log = lib.m.model_log()
+        assert log.count(b"order") <= most, log.decode()
+        assert len({q["stream"] for q in lib.launches("11k_particlesILi0")}) >= 2
+        assert lib.m.hipStreamSynchronize(stream) == 0
+        for k, g in enumerate(cases):
+            assert lib.m.model_step(C.c_void_p(g.at)) == call * (steps + k // 2)
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -248,3 +265,10 @@ def test_a_state_load_does_not_wait_chunk_by_chunk(model, n):
     """A load goes through the pinned staging in chunks, a wait each, only
     while that is the faster way."""
     _scenario(model, "large_state", n)
+
+
+@pytest.mark.parametrize("n_cases,steps,own_stream,most", [(2, 5, 1, 2), (2, 3000, 1, 4), (4, 3000, 1, 8), (2, 5, 0, 4)])
+def test_groups_side_by_side_wait_once_a_window(model, n_cases, steps, own_stream, most):
+    """Two groups side by side wait for the caller's stream and it for them
+    once a window, in a call of a few steps without a stream for each."""
+    _scenario(model, "side_by_side", n_cases, steps, own_stream, most)

@@ -91,8 +91,7 @@ def main():
     ap.add_argument("--workload", choices=["dual32", "batch64", "large", "small", "small256"], default="dual32")
     ap.add_argument("--mode", type=int, default=-1, choices=(-1, 0, 1),
                     help="launch mode of the timed region: 0 plain, 1 graph windows; -1 (default) the "
-                         "autotuner's choice for a batch of cases (several groups' graphs can overlap worse "
-                         "than their plain launches), graph windows otherwise")
+                         "autotuner's choice for a batch of cases, graph windows otherwise")
     ap.add_argument("--plain-steps", type=int, default=10,
                     help="dual32: timed RF cycles of the plain large case reported beside it (0: skip)")
     ap.add_argument("--cpu-steps", type=int, default=0,
@@ -214,10 +213,10 @@ def choose_schedule(args, ctx, descs, warm):
                                             tune.DEFAULT_CANDIDATES + ((BATCH_SORT_EXTRA,) if len(descs) > 1
                                                                        else ()),
                                             wg_candidates=(args.wg_per_cu,) if args.wg_per_cu >= 0 else
-                                            tune.DEFAULT_WG_CANDIDATES,
+                                            tune.DISTINCT_WG_CANDIDATES,
                                             restore_state=True,
                                             group_candidates=(args.groups,) if args.groups else
-                                            tune.DEFAULT_GROUP_CANDIDATES,
+                                            tune.DISTINCT_GROUP_CANDIDATES,
                                             mode_candidates=mode_candidates, measure_fn=traced_measure)
     finally:
         for c in copies:

@@ -13,14 +13,15 @@ mode: graph windows or plain launches).
   and the memory system less contention; which wins depends on the batch.
 
 The best values depend on the workload -- a single case of 2e6 particles
-per species is fastest near a 50-step interval, the 64-case batched set near
-100-200; the dual-frequency set gains 7% from 4 workgroups per CU where the
-batched set loses 2% -- and nothing in the results depends on any of them (a
+per species is fastest near a 50-step interval, the dual-frequency set near
+400; that set runs 5% slower with three workgroups per CU than with all, the
+large case 2% faster, a case of 3e5 electrons 10% faster with two -- and
+nothing in the results depends on any of them (a
 step is bit-identical across sort intervals and launch shapes).  So the
 tuner advances the real cases under each candidate in turn, losing no step,
 times each trial with the device's own particle-step counters, and keeps the
-fastest.  The knobs interact (4 workgroups per CU win at one sort interval
-and lose at another), so when the calibration run says that every
+fastest.  The knobs interact (fewer workgroups per CU can win at one sort
+interval and lose at another), so when the calibration run says that every
 combination fits in JOINT_BUDGET_SECONDS the tuner tries them all;
 otherwise one knob at a time: the sort interval, then the workgroups per
 CU at that interval.  Last, for a batch of several cases, the lockstep
@@ -56,6 +57,11 @@ from typing import Callable, Dict, List, Optional, Sequence, Tuple
 DEFAULT_CANDIDATES = (25, 50, 100, 200)  # sort intervals (steps)
 DEFAULT_WG_CANDIDATES = (0, 4, 3)        # particle workgroups per CU (0: all that fit)
 DEFAULT_GROUP_CANDIDATES = (2, 3, 4)     # lockstep groups of a multi-case batch
+# The values among those that the library runs differently: a CU holds four
+# particle workgroups (4 and more are 0, all that fit), and 2, 3 and 4 groups
+# are alike.  Not the defaults above, which callers and their caches know.
+DISTINCT_WG_CANDIDATES = (0, 3, 2)
+DISTINCT_GROUP_CANDIDATES = (1, 2)
 MAX_TRIAL_STEPS = 8000
 MAX_TRIAL_STRETCH = 8       # at most this many windows per trial
 MIN_TRIAL_SECONDS = 0.3     # calibration target per trial
@@ -212,8 +218,7 @@ def tune_schedule(ctx, cases: Sequence, candidates: Sequence[int] = DEFAULT_CAND
     groups at 2.  Every trial
     before the groups stage runs with 2 groups.  With `mode_candidates`
     (launch modes: 1 graph windows, 0 plain launches) the last stage tries
-    every group count in every mode -- several groups' graphs can overlap
-    worse than their plain launches -- and the choice gains a "mode".  With
+    every group count in every mode and the choice gains a "mode".  With
     restore_state every trial starts from the cases' state at the call, and
     the cases end in it."""
     from . import edupic

@@ -225,6 +225,29 @@ def scenario_side_by_side(lib, n_cases, steps, own_stream, most):
             assert lib.m.model_step(C.c_void_p(g.at)) == call * (steps + k // 2)
 
 
+def scenario_distinct_schedules(lib):
+    """Launch shapes of two cases that fill the chip under each candidate of the benchmark's tuner."""
+    from paper_2103_09642_amd import tune
+    lib.m.model_cus(8)
+    ctx = lib.context(stream=lib.stream())
+    cases = [lib.case(ctx, n_init_e=30_000, n_init_i=30_000, cap_e=40_000, cap_i=40_000, seed=k) for k in range(2)]
+
+    def shapes(wg, groups):
+        ctx.set_option(lib.e.OPT_PART_WG_PER_CU, wg)
+        ctx.set_option(lib.e.OPT_GROUPS, groups)
+        lib.m.model_clear()
+        lib.ok(lib.advance(ctx, cases, [1, 1]))
+        lib.m.model_finish()
+        return tuple(sorted((q["grid"], q["block"]) for q in lib.launches("11k_particlesILi0")))
+
+    every = [(w, g) for w in tune.DISTINCT_WG_CANDIDATES for g in tune.DISTINCT_GROUP_CANDIDATES]
+    assert len({shapes(w, g) for w, g in every}) == len(every)
+    for w in range(1, 9):  # and nothing but the single workgroup is left out
+        assert w == 1 or any(shapes(w, 2) == shapes(v, 2) for v in tune.DISTINCT_WG_CANDIDATES)
+    for g in range(1, 5):
+        assert any(shapes(0, g) == shapes(0, h) for h in tune.DISTINCT_GROUP_CANDIDATES)
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -272,3 +295,10 @@ def test_groups_side_by_side_wait_once_a_window(model, n_cases, steps, own_strea
     """Two groups side by side wait for the caller's stream and it for them
     once a window, in a call of a few steps without a stream for each."""
     _scenario(model, "side_by_side", n_cases, steps, own_stream, most)
+
+
+def test_the_benchmarks_tuner_tries_schedules_that_differ(model):
+    """No two of the candidates that bench.py tunes over launch the same."""
+    _scenario(model, "distinct_schedules")
+    bench = open(os.path.join(ROOT, "bench.py")).read()
+    assert "tune.DISTINCT_WG_CANDIDATES" in bench and "tune.DISTINCT_GROUP_CANDIDATES" in bench

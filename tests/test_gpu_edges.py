@@ -145,3 +145,95 @@ def test_small_measurements_equal_lockstep(ctx, ng):
     assert got[0][0] == got[1][0]
     for a, b in zip(got[0][1], got[1][1]):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+MEASURE = ["density", "eepf", "current", "meane", "xt", "ifed"]
+SURFACES = {"gamma_see": (0.4, 0.3), "eta_refl": (0.3, 0.2), "see_te_ev": 2.0}
+
+
+def _with_wall_hits(c, st, n):
+    """Every 37th particle, n of each species, about to cross an electrode, some slow and some fast."""
+    rng = np.random.default_rng(n)
+    for sp, dt in (("e", c["dt_e"]), ("i", c["ion_subcycle"] * c["dt_e"])):
+        at = np.arange(n) * 37
+        v = rng.uniform(1e5, 4e6, n) if sp == "e" else rng.uniform(1e3, 2e4, n)
+        far = rng.uniform(0.1, 0.9, n) * v * dt
+        left = np.arange(n) % 2 == 0
+        st[sp]["x"][at] = np.where(left, far, c["gap_m"] - far)
+        st[sp]["vx"][at] = np.where(left, -v, v)
+    return st
+
+
+@pytest.mark.parametrize("flags", [MEASURE, ["null_collision"], MEASURE + ["null_collision"]],
+                         ids=["measurements", "null-collisions", "both"])
+def test_wide_workgroups_with_options_match_oracle(ctx, xs_default, orc, flags):
+    """One ion step of enough particles for workgroups of 512 threads, with
+    measurements, null collisions and both electrodes emitting and reflecting.
+    Thomas fields are the oracle's bits, so positions, deposits, counters and
+    every sum of fixed-point parts are too; collided velocities 1e-12."""
+    from paper_2103_09642_amd import edupic
+    say(f"test_wide_workgroups_with_options_match_oracle {flags}")
+    n = 300_001
+    c = base_case(n_init_e=0, n_init_i=0, pressure_pa=40.0, weight=2e5, n_grid=200, ion_subcycle=5, cap_e=n + 20_000,
+                  cap_i=n + 20_000, flags=["allow_unstable"] + flags, **SURFACES)
+    st = random_state(n, n, c["gap_m"], seed=11, te_ev=4.0, hot_frac=0.3, hot_ev=90.0, ion_energy_ev=30.0)
+    st = _with_wall_hits(c, st, 4000)
+    ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_THOMAS)
+    try:
+        g, o = make_pair(ctx, c, xs_default, orc)
+        set_both(g, o, st, 5)
+        g.advance_steps(1)
+        o.step(1)
+        cg, co = g.counts(), o.counts()
+        for k in ("abs_e_pow", "abs_e_gnd", "abs_i_pow", "abs_i_gnd", "coll_e", "coll_i", "ioniz", "see_pow", "see_gnd",
+                  "refl"):
+            assert cg[k] == co[k], k
+        assert min(co["see_pow"], co["see_gnd"], co["refl"], co["ioniz"], co["coll_i"]) > 50
+        for a, b in zip(g.deposit(), o.deposit()):
+            assert np.array_equal(a, b), "deposit"
+        for sp in (0, 1):
+            compare_states(g.get_state(sp), o.get_state(sp), 1e-12, f"sp{sp}")
+        if "xt" in flags:
+            for q in ("ne", "ni", "je", "ji", "meanee", "meanei", "ioniz", "powere", "poweri", "efield"):
+                assert np.array_equal(g.xt(q), o.xt(q)), q
+            assert np.array_equal(g.ifed()[2], o.ifed()[2]), "IFEDF"
+            assert np.array_equal(g.eepf()[1], o.eepf()[1]), "EEPF"
+        g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_FLUX)
+
+
+@pytest.mark.parametrize("groups", [1, 2])
+def test_wide_workgroups_of_several_cases_equal_narrow_ones(ctx, groups):
+    """Three cases with different options in one call, in workgroups of 512
+    threads and, one workgroup per CU, of 256: counters, deposits, fields and
+    every measurement are the same bits after sorts and ion steps."""
+    from paper_2103_09642_amd import edupic
+    say(f"test_wide_workgroups_of_several_cases_equal_narrow_ones groups={groups}")
+    n = 250_000
+    descs = [base_case(n_init_e=n + 333 * k, n_init_i=n - 77 * k, n_grid=150 + 60 * k, weight=1e4, pressure_pa=20.0 + 15 * k,
+                       ion_subcycle=5, cap_e=n + 40_000, cap_i=n + 40_000, seed=5 + k, flags=["allow_unstable"] + fl, **surf)
+             for k, (fl, surf) in enumerate([(MEASURE, SURFACES), (["null_collision"], SURFACES), (MEASURE[:3], {})])]
+    got = []
+    try:
+        ctx.set_option(edupic.OPT_GROUPS, groups)
+        ctx.set_option(edupic.OPT_SORT_EVERY, 7)
+        for wg in (0, 1):
+            ctx.set_option(edupic.OPT_PART_WG_PER_CU, wg)
+            gs = [ctx.create_case(d) for d in descs]
+            ctx.advance_steps(gs, [33, 33, 28])
+            a, b = gs[0], gs[2]
+            got.append(([g.counts() for g in gs],
+                        [v for g in gs for v in g.deposit() + g.fields()] + list(a.density() + a.eepf() + a.currents())
+                        + [a.mean_energy()] + [a.xt(q) for q in edupic.XT_NAMES] + list(a.ifed())
+                        + list(b.density() + b.eepf() + b.currents())))
+            for g in gs:
+                g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_GROUPS, 2)
+        ctx.set_option(edupic.OPT_SORT_EVERY, 100)
+        ctx.set_option(edupic.OPT_PART_WG_PER_CU, 0)
+    assert got[0][0] == got[1][0]
+    assert min(got[0][0][0][k] for k in ("coll_e", "coll_i", "abs_e_pow")) > 0
+    for x, y in zip(got[0][1], got[1][1]):
+        assert np.array_equal(x, y, equal_nan=True)

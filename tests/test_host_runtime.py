@@ -248,6 +248,23 @@ def scenario_distinct_schedules(lib):
         assert any(shapes(0, g) == shapes(0, h) for h in tune.DISTINCT_GROUP_CANDIDATES)
 
 
+def scenario_wide_workgroups(lib):
+    """Threads of the launches of the cases that the GPU tests of wide workgroups advance, on a chip of 256 CUs."""
+    import test_gpu_edges as t
+    lib.m.model_cus(256)
+    ctx = lib.context(stream=lib.stream())
+    n = 300_001
+    for flags in (t.MEASURE, ["null_collision"], t.MEASURE + ["null_collision"]):
+        g = lib.case(ctx, n_init_e=n, n_init_i=n, n_grid=200, cap_e=n + 20_000, cap_i=n + 20_000, ion_subcycle=5,
+                     flags=["allow_unstable"] + flags, **t.SURFACES)
+        for wg, threads in ((0, 512), (1, 256)):
+            ctx.set_option(lib.e.OPT_PART_WG_PER_CU, wg)
+            lib.m.model_clear()
+            lib.ok(lib.advance(ctx, [g], [5]))
+            lib.m.model_finish()
+            assert {q["block"] for q in lib.launches("11k_particles")} == {threads}
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -302,3 +319,9 @@ def test_the_benchmarks_tuner_tries_schedules_that_differ(model):
     _scenario(model, "distinct_schedules")
     bench = open(os.path.join(ROOT, "bench.py")).read()
     assert "tune.DISTINCT_WG_CANDIDATES" in bench and "tune.DISTINCT_GROUP_CANDIDATES" in bench
+
+
+def test_the_gpu_tests_of_wide_workgroups_launch_them(model):
+    """Measurements, null collisions and surfaces run in workgroups of 512
+    threads at the sizes of their tests, and of 256 by option."""
+    _scenario(model, "wide_workgroups")

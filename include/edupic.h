@@ -129,9 +129,11 @@ extern "C" {
                                  (default 2).  1: all cases advance in one
                                  group, a launch advances each of them by a
                                  step.  2 and more, all alike: the cases are
-                                 split by expected work (particles x steps)
-                                 into as many blocks as keep each one's
-                                 particles within the Infinity Cache, the
+                                 split into a block per 360 MB that they
+                                 stream a step, which is about what the
+                                 Infinity Cache holds of a block from step to
+                                 step (balanced by expected work, particles x
+                                 steps, so that a block may hold more), the
                                  blocks' windows follow one another, and a
                                  block runs as two groups side by side on
                                  streams the library creates (default

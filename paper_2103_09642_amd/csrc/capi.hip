@@ -223,9 +223,8 @@ struct edp_ctx {
   BlockRole* small_roles = nullptr;
   size_t small_cap = 0;
   std::vector<BlockRole> small_h;
-  // the groups' tables and run state; group 0 runs on `stream`, the others
-  // on streams of their own, forked from and joined back into `stream` by an
-  // advance
+  // the groups' tables and run state, in the order of the blocks (one group or
+  // two each); as many as the largest advance so far had
   std::deque<Group> grp;
   // streams for groups side by side (default priority)
   hipStream_t side[kSide] = {};
@@ -785,8 +784,9 @@ int particle_block(const edp_ctx* ctx, const std::vector<Case*>& cs, int sp, int
 // work (est_cost), so every workgroup has about the same amount of it (any
 // count is still covered: the kernels split the live chunks over whatever
 // workgroups a case has).  The table is read by
-// kernels still in flight, so they are waited for before it changes; grids are rebuilt only when a case's share has moved by a quarter or the
-// shares by a sixteenth of the workgroups in all.
+// kernels still in flight, so they are waited for before it changes; grids are
+// rebuilt only when a case's share has moved by a quarter or the shares by a
+// sixteenth of the workgroups in all.
 int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
   Batch& B = G.batch;
   const size_t nc = cs.size();
@@ -1113,7 +1113,8 @@ struct Forked {
 };
 
 // Whether a case runs in the persistent one-workgroup-per-case kernel: few
-// enough slots (estimate) and its LDS within one workgroup's 64 KiB.
+// enough slots (estimate) and its LDS with 256 threads within 64 KiB (run_small
+// takes 512 threads where every case of the call fits 80 KiB so).
 bool small_case(const edp_ctx* ctx, const Case* c) {
   if (ctx->small_max <= 0 || std::max(c->est[0], c->est[1]) > ctx->small_max) return false;
   const edp_case_desc& D = c->desc;
@@ -1250,21 +1251,26 @@ int run_batch(edp_ctx* ctx, const std::vector<Case*>& all, const std::vector<int
 //
 // Blocks: cases whose particles the Infinity Cache holds together read them
 // from there step after step, more of them read from HBM.  So the cases are
-// cut into as few blocks as keep a block's streamed bytes a step within
-// kGroupBytes, and the blocks' windows follow one another on the caller's
-// stream.  Measured with one group a block, us a step: 32 dual-frequency cases
+// cut into as many blocks as their streamed bytes a step are multiples of
+// kGroupBytes (rounded up), and the blocks' windows follow one another on the
+// caller's stream.  kGroupBytes is where that was measured to pay, somewhat
+// above the 256 MB cache, of which a set a little larger still keeps most; the
+// blocks are balanced by work, so one of cases with few steps may hold more.
+// Measured with one group a block, us a step: 32 dual-frequency cases
 // of 27 MB each in 1, 3, 4, 5 blocks 388, 296, 308, 317; 16 of them (430 MB)
 // in 1, 2 blocks 176, 150, 14 (380 MB) 135, 133, 13 (350 MB) 116, 125; 64
 // mixed cases (250 MB) in 1, 2, 3 blocks 108, 116, 129.
 //
-// Within a block two groups side by side, on streams of their own that wait
-// for the caller's and that it waits for: one group's launch gap, field
-// solves and tail run beside the other's streaming.  One, two, three groups,
+// Within a block two groups side by side, on streams of their own (see
+// side_window): one group's launch gap, field solves and tail run beside the
+// other's streaming.  One, two, three groups,
 // us a step: 64 mixed cases 119, 100, 146; 16 of them 36.7, 35.2, 55; 4 of
 // them 21.4, 18.8; the 32 dual-frequency cases 296, 271, 372.
 constexpr double kGroupBytes = 360e6;
 // Bytes a case streams through a step: x, v_x, the bound of v_y^2 + v_z^2 and the
-// identity of every electron, the full state of every ion every ion step.
+// identity of every electron, the full state of every ion every ion step
+// (without the v_y and v_z of every electron that per-particle measurements
+// read, 16 bytes more).
 double streamed_bytes(const Case* c) {
   return 28.0 * (double)c->est[0] + 40.0 * (double)c->est[1] / (double)c->desc.ion_subcycle;
 }
@@ -1654,26 +1660,22 @@ int edp_case_create(edp_ctx* ctx, const edp_case_desc* desc, void* dev_arena, in
     // Candidates of the direct collision test.  nu* bounds n sigma_tot g up
     // to the energy e_lim its last bin is taken at, up to rounding of the bin
     // edges; the relative margin covers that and the ulps of exp, so a
-    // particle with R >= p_bound and an energy below e_lim has R >= P.  An
+    // particle with R >= p_cand and an energy below e_lim has R >= P.  An
     // ion's relative speed is at most |v| + |v_a|: each normal of the
     // generator is r cos or r sin with r <= sqrt(2 * 53 ln 2) < 8.58, so
     // |v_a|^2 <= (r1^2 + r2^2) sigma_a^2 < (12.2 sigma_a)^2, and
     // g^2 <= 2 (v^2 + |v_a|^2).
     const double e_lim = 4.0 * (double)nb * ctx->de;
-    h.p_bound_e = std::min(1.0, (1.0 - std::exp(-h.nu_star_e * h.dt_e)) * (1.0 + 1e-9));
-    h.p_bound_i = std::min(1.0, (1.0 - std::exp(-h.nu_star_i * h.dt_i)) * (1.0 + 1e-9));
-    h.v2_lim_e = 2.0 * e_lim * kEvToJ / kEMass * (1.0 - 1e-12);
-    h.g2_lim_i = 2.0 * e_lim * kEvToJ / kMuArAr * (1.0 - 1e-12);
     const double amax = 12.2 * h.sigma_a;
     h.a2_i = amax * amax;
     h.pb_shift = pb_shift(nb);
     h.pb_n = ((nb - 1) >> h.pb_shift) + 1;
     // what the particle loop tests (see CaseDev)
     const bool null_coll = (D.flags & EDP_NULL_COLLISION) != 0;
-    h.p_cand[0] = null_coll ? h.p_null_e : h.p_bound_e;
-    h.p_cand[1] = null_coll ? h.p_null_i : h.p_bound_i;
-    h.v2_cand[0] = null_coll ? HUGE_VAL : h.v2_lim_e;
-    h.v2_cand[1] = null_coll ? HUGE_VAL : h.g2_lim_i;
+    h.p_cand[0] = null_coll ? h.p_null_e : std::min(1.0, h.p_null_e * (1.0 + 1e-9));
+    h.p_cand[1] = null_coll ? h.p_null_i : std::min(1.0, h.p_null_i * (1.0 + 1e-9));
+    h.v2_cand[0] = null_coll ? HUGE_VAL : 2.0 * e_lim * kEvToJ / kEMass * (1.0 - 1e-12);
+    h.v2_cand[1] = null_coll ? HUGE_VAL : 2.0 * e_lim * kEvToJ / kMuArAr * (1.0 - 1e-12);
     const double blocks_per_row = std::ldexp(1.0, -h.pb_shift);
     h.blocks_per_v2[0] = 0.5 * kEMass / kEvToJ / ctx->de * (1.0 + 1e-12) * blocks_per_row;
     h.blocks_per_v2[1] = 0.5 * kMuArAr / kEvToJ / ctx->de * (1.0 + 1e-12) * blocks_per_row;

@@ -97,20 +97,18 @@ struct CaseDev {
   double n_gas;                     // gas density p / (k_B T_g)
   double nu_star_e, nu_star_i;      // null-collision maximum frequencies
   double p_null_e, p_null_i;        // 1 - exp(-nu* dt) per species
-  // collision candidates of the direct test: R below p_bound (P* with a
-  // relative margin), or electrons with v^2 > v2_lim_e, ions with
-  // 2 (v^2 + a2_i) > g2_lim_i (a2_i bounds the squared thermal target speed
-  // the generator can give), i.e. beyond the energy range P* covers
-  double p_bound_e, p_bound_i, v2_lim_e, g2_lim_i, a2_i;
-  // the same bound by energy: pbound[sp][b] bounds P over every table row
+  // an ion's squared relative speed is at most 2 (v^2 + a2_i): a2_i bounds the
+  // squared thermal target speed the generator can give
+  double a2_i;
+  // a bound of P by energy: pbound[sp][b] bounds P over every table row
   // up to the last of block b (rows r with r >> pb_shift <= b), a prefix
   // maximum, so that the block of any upper bound of a particle's energy
   // gives a bound of its P
   // (as the largest upper word of R's 64 bits with which R < P is possible)
   const uint32_t* pbound[2];
-  // per species: the bound over the whole table (or P* for null collisions),
-  // the same as an upper word, the squared speed it covers (infinite for
-  // null collisions), and blocks of the bound by energy per squared
+  // per species: the bound of P over the whole table (P* with a relative
+  // margin; for null collisions P* itself), the same as an upper word, the
+  // squared (relative) speed it covers (infinite for null collisions), and blocks of the bound by energy per squared
   // (relative) speed -- a multiple of rows, with a margin against the rounding
   // of the exact test's own squared speed and energy --, half a row in blocks
   // and the last row

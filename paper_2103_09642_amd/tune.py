@@ -57,9 +57,10 @@ from typing import Callable, Dict, List, Optional, Sequence, Tuple
 DEFAULT_CANDIDATES = (25, 50, 100, 200)  # sort intervals (steps)
 DEFAULT_WG_CANDIDATES = (0, 4, 3)        # particle workgroups per CU (0: all that fit)
 DEFAULT_GROUP_CANDIDATES = (2, 3, 4)     # lockstep groups of a multi-case batch
-# The values among those that the library runs differently: a CU holds four
-# particle workgroups (4 and more are 0, all that fit), and 2, 3 and 4 groups
-# are alike.  Not the defaults above, which callers and their caches know.
+# The values among those that the library runs differently: a CU holds at most
+# four particle workgroups (4 and more are 0, all that fit; with large grids and
+# measurements two may be all), and 2, 3 and 4 groups are alike.  Not the
+# defaults above, which callers and their caches know.
 DISTINCT_WG_CANDIDATES = (0, 3, 2)
 DISTINCT_GROUP_CANDIDATES = (1, 2)
 MAX_TRIAL_STEPS = 8000

@@ -277,11 +277,12 @@ int validate(const edp_case_desc* c) {
   if ((c->gamma_see[0] > 0.0 || c->gamma_see[1] > 0.0) && !(c->see_te_ev > 0.0))
     return fail(EDP_EINVAL, "see_te_ev must be > 0 with secondary emission");
   // particle-kernel LDS: E + deposit (16 B/node), with measurements 24-32 B/node
-  // more and the EEPF / IFEDF histograms
+  // more and the EEPF / IFEDF histograms; of a workgroup's 64 KiB, what is left
+  // beside 14 KiB (electrons) and 8 KiB (ions) for the kernels' own
   const uint32_t meas = EDP_DIAG_EEPF | EDP_DIAG_CURRENT | EDP_DIAG_MEANE | EDP_DIAG_XT | EDP_DIAG_IFED;
   if ((c->flags & meas) && c->n_grid > 1024) return fail(EDP_EINVAL, "measurements support n_grid <= 1024");
   for (int sp = 0; sp < 2; ++sp)
-    if (particle_lds_bytes(c->n_grid, c->flags, c->n_eepf, c->n_ifed, sp) + particle_static_lds(sp, 256) > 65536)
+    if (particle_lds_bytes(c->n_grid, c->flags, c->n_eepf, c->n_ifed, sp) + (sp == 0 ? 14336 : 8192) > 65536)
       return fail(EDP_EINVAL, "measurement histograms and grid exceed the workgroup's LDS");
   return EDP_OK;
 }

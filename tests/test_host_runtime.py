@@ -265,6 +265,25 @@ def scenario_wide_workgroups(lib):
             assert {q["block"] for q in lib.launches("11k_particles")} == {threads}
 
 
+def scenario_measurement_limits(lib):
+    """The largest measurement histograms a case may ask for beside 1000 nodes."""
+    ctx = lib.context(stream=lib.stream())
+
+    def accepts(**kw):
+        try:
+            return ctx.case_bytes(lib.w.base_case(n_grid=1000, **kw)) > 0
+        except lib.e.EdpError as err:
+            assert err.code == lib.e.EDP_EINVAL
+            return False
+
+    # electrons: 48 bytes a node with the xt arrays and 4 a bin, 51200 in all
+    for n, ok in ((800, True), (801, False), (1056, False), (1057, False)):
+        assert accepts(flags=["eepf", "xt"], n_eepf=n) == ok, n
+    # ions: 40 bytes a node and 8 a pair of bins, 57344 in all
+    for n, ok in ((2167, True), (2168, False), (2423, False), (2424, False)):
+        assert accepts(flags=["ifed"], n_ifed=n) == ok, n
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -325,3 +344,9 @@ def test_the_gpu_tests_of_wide_workgroups_launch_them(model):
     """Measurements, null collisions and surfaces run in workgroups of 512
     threads at the sizes of their tests, and of 256 by option."""
     _scenario(model, "wide_workgroups")
+
+
+def test_the_limits_of_measurement_histograms_stand(model):
+    """What a case may measure is a limit of the interface, not of how much
+    LDS the kernels leave free."""
+    _scenario(model, "measurement_limits")

@@ -58,7 +58,7 @@ DEFAULT_CANDIDATES = (25, 50, 100, 200)  # sort intervals (steps)
 DEFAULT_WG_CANDIDATES = (0, 4, 3)        # particle workgroups per CU (0: all that fit)
 DEFAULT_GROUP_CANDIDATES = (2, 3, 4)     # lockstep groups of a multi-case batch
 # The values among those that the library runs differently: a CU holds at most
-# four particle workgroups (4 and more are 0, all that fit; with large grids and
+# four workgroups of the electron kernel (4 and more are 0, all that fit; with large grids and
 # measurements two may be all), and 2, 3 and 4 groups are alike.  Not the
 # defaults above, which callers and their caches know.
 DISTINCT_WG_CANDIDATES = (0, 3, 2)

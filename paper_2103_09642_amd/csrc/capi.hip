@@ -1114,12 +1114,14 @@ struct Forked {
 };
 
 // Whether a case runs in the persistent one-workgroup-per-case kernel: few
-// enough slots (estimate) and its LDS with 256 threads within 64 KiB (run_small
-// takes 512 threads where every case of the call fits 80 KiB so).
+// enough slots (estimate) and at most 40 KiB of dynamic LDS with 256 threads
+// (run_small takes 512 where every case of the call fits 80 KiB so), as
+// measurements on large grids do not have: 64 cases of 2e3 electrons on 750
+// nodes with every measurement take 27 us a step in lockstep, 35 so.
 bool small_case(const edp_ctx* ctx, const Case* c) {
   if (ctx->small_max <= 0 || std::max(c->est[0], c->est[1]) > ctx->small_max) return false;
   const edp_case_desc& D = c->desc;
-  return small_lds_bytes(256, D.n_grid, D.flags, D.n_eepf, D.n_ifed) + small_static_lds(256) <= 65536;
+  return small_lds_bytes(256, D.n_grid, D.flags, D.n_eepf, D.n_ifed) <= 40960;
 }
 
 // The persistent small cases of an advance, on the context's small-case

@@ -147,6 +147,13 @@ def test_small_measurements_equal_lockstep(ctx, ng):
         assert np.array_equal(a, b, equal_nan=True)
 
 
+@pytest.mark.parametrize("ng", [543, 544, 686])
+def test_small_measurements_by_threads_equal_lockstep(ctx, ng):
+    """The same on the last grid for 512 threads with every measurement, and
+    the first and the last for 256."""
+    test_small_measurements_equal_lockstep(ctx, ng)
+
+
 MEASURE = ["density", "eepf", "current", "meane", "xt", "ifed"]
 SURFACES = {"gamma_see": (0.4, 0.3), "eta_refl": (0.3, 0.2), "see_te_ev": 2.0}
 

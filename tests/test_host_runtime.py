@@ -284,6 +284,21 @@ def scenario_measurement_limits(lib):
         assert accepts(flags=["ifed"], n_ifed=n) == ok, n
 
 
+def scenario_small_case_limit(lib):
+    """The path of a small case with every measurement by its grid (2000 EEPF bins: 48 bytes a node and 8000 of 40960),
+    and the threads of its workgroup."""
+    ctx = lib.context(stream=lib.stream())
+    ctx.set_option(lib.e.OPT_SMALL_MAX, 1 << 20)
+    for ng, small in ((400, 512), (543, 512), (544, 256), (686, 256), (687, 0), (793, 0), (1000, 0)):
+        g = lib.case(ctx, n_grid=ng, n_eepf=2000 if ng < 800 else 100,
+                     flags=["allow_unstable", "density", "eepf", "current", "meane", "xt", "ifed"])
+        lib.m.model_clear()
+        lib.ok(lib.advance(ctx, [g], [3]))
+        lib.m.model_finish()
+        assert [q["block"] for q in lib.launches("7k_small")] == [small] * bool(small), ng
+        assert bool(lib.launches("11k_particles")) != bool(small), ng
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -350,3 +365,9 @@ def test_the_limits_of_measurement_histograms_stand(model):
     """What a case may measure is a limit of the interface, not of how much
     LDS the kernels leave free."""
     _scenario(model, "measurement_limits")
+
+
+def test_which_small_cases_run_in_one_workgroup(model):
+    """Cases whose measurements leave the persistent kernel little LDS stay on
+    the lockstep path, which is the faster one for them."""
+    _scenario(model, "small_case_limit")

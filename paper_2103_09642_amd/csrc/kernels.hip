@@ -566,13 +566,17 @@ __device__ __forceinline__ void solve_field(CaseDev* __restrict__ Cw, const int 
       // precomputed on the host
       const EDP_GLOBAL double* __restrict__ rd = G(C->rden);
       const int m = ng - 2;
+      // (eight rows' reads in flight together, whichever kernel this is part of:
+      // one row at a time waits 77 ns for each, so 27)
       double prev = 0.0;
+#pragma unroll 8
       for (int p = 1; p <= m; ++p) {
         double d = sF[p];
         if (p == 1) d = d + V;
         prev = (d + prev) * rd[p];
         sF[p] = prev;
       }
+#pragma unroll 8
       for (int p = m - 1; p >= 1; --p) sF[p] = sF[p] + rd[p] * sF[p + 1];
       sF[0] = V;
       sF[ng - 1] = 0.0;

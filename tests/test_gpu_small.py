@@ -166,3 +166,33 @@ def test_small_matches_oracle(ctx, xs_default, orc, small):
     for sp in (0, 1):
         compare_states(g.get_state(sp), o.get_state(sp), 1e-9, f"sp{sp}")
     g.destroy()
+
+
+def test_thomas_solve_costs_the_same_in_one_workgroup(ctx):
+    """The sequential sweeps are the same work in either path: a small case
+    spends no more than half as much again on its steps as in lockstep (it was
+    twice as much where the sweeps waited for one row at a time)."""
+    import time
+
+    from paper_2103_09642_amd import edupic
+    say("test_thomas_solve_costs_the_same_in_one_workgroup")
+    took = {}
+    try:
+        ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_THOMAS)
+        for small in (0, 1 << 20):
+            ctx.set_option(edupic.OPT_SMALL_MAX, small)
+            g = ctx.create_case(base_case(n_grid=800, n_init_e=500, n_init_i=500, weight=1e5, cap_e=20_000, cap_i=20_000,
+                                          flags=["allow_unstable"]))
+            t = []
+            for _ in range(4):
+                ctx.sync()
+                t0 = time.perf_counter()
+                g.advance_steps(200)
+                ctx.sync()
+                t.append(time.perf_counter() - t0)
+            took[small] = min(t)
+            g.destroy()
+    finally:
+        ctx.set_option(edupic.OPT_SMALL_MAX, 0)
+        ctx.set_option(edupic.OPT_POISSON, edupic.POISSON_FLUX)
+    assert took[1 << 20] <= 1.5 * took[0], took

@@ -299,6 +299,20 @@ def scenario_small_case_limit(lib):
         assert bool(lib.launches("11k_particles")) != bool(small), ng
 
 
+def scenario_lds_granules(lib):
+    """Workgroups of 256 per CU of electron launches with 48 bytes a node, 8000 of the EEPF and the kernel's 12360."""
+    lib.m.model_cus(8)
+    ctx = lib.context(stream=lib.stream())
+    # three of 42 granules of 1280 bytes fit 160 KiB, three of 43 do not
+    for ng, per_cu in ((690, 3), (695, 3), (696, 2), (713, 2), (714, 2), (740, 2)):
+        g = lib.case(ctx, n_init_e=30_000, n_init_i=30_000, cap_e=40_000, cap_i=40_000, n_grid=ng,
+                     flags=["allow_unstable", "density", "eepf", "current", "meane", "xt", "ifed"])
+        lib.m.model_clear()
+        lib.ok(lib.advance(ctx, [g], [1]))
+        lib.m.model_finish()
+        assert [(q["grid"], q["block"]) for q in lib.launches("11k_particlesILi0")] == [(8 * per_cu, 256)], ng
+
+
 if __name__ == "__main__":
     sys.path.insert(0, ROOT)
     the_lib = Lib(sys.argv[1])
@@ -371,3 +385,9 @@ def test_which_small_cases_run_in_one_workgroup(model):
     """Cases whose measurements leave the persistent kernel little LDS stay on
     the lockstep path, which is the faster one for them."""
     _scenario(model, "small_case_limit")
+
+
+def test_a_launch_has_no_more_workgroups_than_the_lds_granules_hold(model):
+    """LDS is given out in granules, which the runtime's occupancy does not
+    count: a workgroup beyond what fits waits for a whole one to end."""
+    _scenario(model, "lds_granules")

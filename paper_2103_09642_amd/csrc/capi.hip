@@ -1346,6 +1346,9 @@ int side_window(edp_ctx* ctx, Group** G, std::vector<CaseList>& parts, bool& don
   if (done) return EDP_OK;
   const bool on_context = first_on_context(ctx, steps, bytes);
   HIPCHK(hipEventRecord(ctx->fork_ev, ctx->stream));
+  // a few steps of each in turn, so that none waits for the enqueueing of
+  // another's whole window
+  constexpr int64_t kTurn = 16;
   std::vector<Window> W(ng);
   int r = EDP_OK;
   for (size_t g = 0; g < ng && r == EDP_OK; ++g) {
@@ -1353,10 +1356,9 @@ int side_window(edp_ctx* ctx, Group** G, std::vector<CaseList>& parts, bool& don
     G[g]->side = true;
     if (G[g]->stream != ctx->stream) HIPCHK(hipStreamWaitEvent(G[g]->stream, ctx->fork_ev, 0));
     r = W[g].open(ctx, *G[g], parts[g].cases, parts[g].left);
+    // the first group's steps run while the second's voltages are uploaded
+    if (r == EDP_OK) r = W[g].some(ctx, *G[g], kTurn);
   }
-  // a few steps of each in turn, so that none waits for the enqueueing of
-  // another's whole window
-  constexpr int64_t kTurn = 16;
   for (bool more = true; more && r == EDP_OK;) {
     more = false;
     for (size_t g = 0; g < ng && r == EDP_OK; ++g) {

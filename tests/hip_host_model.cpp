@@ -256,6 +256,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
   std::lock_guard<std::recursive_mutex> l(mu);
   if (event_at(is_pinned(s) ? "copy from pinned" : "copy")) return hipErrorInvalidValue;
+  if (is_pinned(s)) say("upload stream=%d\n", stream_of(st)->n);
   if (is_pinned(s) || is_pinned(d)) {
     push(stream_of(st), [=] { memcpy(d, s, n); });
   } else {  // pageable memory is read by the call

@@ -220,6 +220,8 @@ def scenario_side_by_side(lib, n_cases, steps, own_stream, most):
         log = lib.m.model_log()
         assert log.count(b"order") <= most, log.decode()
         assert len({q["stream"] for q in lib.launches("11k_particlesILi0")}) >= 2
+        # the first group's steps do not wait for the second's voltages
+        assert log.index(b"k_particles") < log.rindex(b"upload")
         assert lib.m.hipStreamSynchronize(stream) == 0
         for k, g in enumerate(cases):
             assert lib.m.model_step(C.c_void_p(g.at)) == call * (steps + k // 2)
@@ -358,7 +360,8 @@ def test_a_state_load_does_not_wait_chunk_by_chunk(model, n):
 @pytest.mark.parametrize("n_cases,steps,own_stream,most", [(2, 5, 1, 2), (2, 3000, 1, 4), (4, 3000, 1, 8), (2, 5, 0, 4)])
 def test_groups_side_by_side_wait_once_a_window(model, n_cases, steps, own_stream, most):
     """Two groups side by side wait for the caller's stream and it for them
-    once a window, in a call of a few steps without a stream for each."""
+    once a window, in a call of a few steps without a stream for each, and the
+    first is under way before the second is prepared."""
     _scenario(model, "side_by_side", n_cases, steps, own_stream, most)
 
 

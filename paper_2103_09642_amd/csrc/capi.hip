@@ -171,6 +171,12 @@ struct Group {
   hipStream_t stream = nullptr;  // where this advance enqueues the group's work
   hipEvent_t last = nullptr;     // the end of what was enqueued with the tables
   bool side = false;             // another group's launches run beside this one's
+  // resident workgroups per CU of 256 and of 512 threads per species, for
+  // `lds` bytes of dynamic LDS (asking the runtime takes some us a window)
+  struct {
+    size_t lds = SIZE_MAX;
+    int n = 0;
+  } occ[2][2];
   // the allocation-free advance's group: its role table is the device's
   // file-scope array (roles_d, roles_cap fixed), it launches plainly (no
   // graph, no timing events) on the context's stream and never allocates
@@ -758,6 +764,16 @@ void particle_roles(std::vector<BlockRole>& roles, const std::vector<Case*>& cs,
 // Workgroups of a case's sort histogram and scatter.
 int sort_blocks(const edp_ctx* ctx, const Case* c, int sp) { return std::max(1, blocks_for(ctx, c->est[sp]) / 4); }
 
+// particle_occupancy, kept with the group while its LDS stays the same.
+int group_occupancy(Group& G, int sp, int nb, size_t lds) {
+  auto& o = G.occ[sp][nb == 512];
+  if (o.lds != lds) {
+    o.n = particle_occupancy(sp, nb, lds);
+    o.lds = lds;
+  }
+  return o.n;
+}
+
 // Threads of a species' particle workgroups in a launch of the cases `cs`
 // (most nodes max_ng, `lds` dynamic bytes).  Every workgroup solves its
 // case's field, takes in the whole grid and gives the whole grid's deposit
@@ -768,9 +784,9 @@ int sort_blocks(const edp_ctx* ctx, const Case* c, int sp) { return std::max(1, 
 // case of 777 nodes, 6e4 electrons 16.0 16.9, 1.8e5 20.3 20.9, 2.4e5 22.7
 // 21.5, 6e5 27.4 24.7; of 400 nodes, 1.8e5 19.8 20.1, 3e5 23.5 21.7; of 2048
 // nodes, 6e4 15.5 14.7, 3e5 21.6 20.1.
-int particle_block(const edp_ctx* ctx, const std::vector<Case*>& cs, int sp, int max_ng, size_t lds) {
+int particle_block(const edp_ctx* ctx, Group& G, const std::vector<Case*>& cs, int sp, int max_ng, size_t lds) {
   if (lds + particle_static_lds(sp, 512) > 65536) return 256;
-  const int occ = particle_occupancy(sp, 256, lds);
+  const int occ = group_occupancy(G, sp, 256, lds);
   // an explicit share that only workgroups of 256 give
   if (ctx->part_wg_per_cu % 2 != 0 && ctx->part_wg_per_cu < occ) return 256;
   int64_t chunks = 0;
@@ -799,13 +815,13 @@ int set_batch(edp_ctx* ctx, Group& G, const std::vector<Case*>& cs) {
     max_ng = std::max(max_ng, (int)c->desc.n_grid);
   }
   int nb[2];
-  for (int sp = 0; sp < 2; ++sp) nb[sp] = particle_block(ctx, cs, sp, max_ng, lds[sp]);
+  for (int sp = 0; sp < 2; ++sp) nb[sp] = particle_block(ctx, G, cs, sp, max_ng, lds[sp]);
   std::vector<int> want[2];
   for (int sp = 0; sp < 2; ++sp) {
     // the option counts workgroups of 256 threads (an odd number of them, fewer
     // than fit, is launched as such: see particle_block)
-    const int occ = particle_occupancy(sp, nb[sp], lds[sp]), cap = ctx->part_wg_per_cu;
-    const int per_cu = cap == 0 || cap >= particle_occupancy(sp, 256, lds[sp]) ? occ : std::min(cap * 256 / nb[sp], occ);
+    const int occ = group_occupancy(G, sp, nb[sp], lds[sp]), cap = ctx->part_wg_per_cu;
+    const int per_cu = cap == 0 || cap >= group_occupancy(G, sp, 256, lds[sp]) ? occ : std::min(cap * 256 / nb[sp], occ);
     // of two groups side by side each asks for three quarters of the slots: the
     // second's workgroups fill what the first's leave at their ends (all of
     // them, three quarters, half, us a step: 8 mixed cases 32.8 29.2 27.4, 32

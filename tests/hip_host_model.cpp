@@ -213,6 +213,7 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, i
   hipFuncAttributes a;
   (void)hipFuncGetAttributes(&a, f);
   *n = std::min<int>(1024 / b, (int)(163840 / (lds + a.sharedSizeBytes)));
+  say("occupancy\n");
   return hipSuccess;
 }
 

@@ -220,6 +220,8 @@ def scenario_side_by_side(lib, n_cases, steps, own_stream, most):
         log = lib.m.model_log()
         assert log.count(b"order") <= most, log.decode()
         assert len({q["stream"] for q in lib.launches("11k_particlesILi0")}) >= 2
+        # the runtime was asked for the groups' occupancies in the first call
+        assert call == 1 or b"occupancy" not in log, log.decode()
         # the first group's steps do not wait for the second's voltages
         assert log.index(b"k_particles") < log.rindex(b"upload")
         assert lib.m.hipStreamSynchronize(stream) == 0

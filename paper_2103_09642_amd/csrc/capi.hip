@@ -1570,6 +1570,7 @@ int edp_create(edp_ctx** out, int device, void* hip_stream) {
 
 int edp_destroy(edp_ctx* ctx) {
   if (!ctx) return EDP_OK;
+  const OnDevice on_device(ctx->device);
   (void)reset_groups(ctx);
   if (ctx->small_stream) (void)hipStreamSynchronize(ctx->small_stream);
   for (Group& G : ctx->grp) {

@@ -278,7 +278,7 @@ hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t st) {
   std::lock_guard<std::recursive_mutex> l(mu);
   Stream* s = stream_of(st);
-  say("wait stream=%d\n", s->n);
+  say("wait stream=%d dev=%d\n", s->n, s->dev);
   drain(s, INT64_MAX);
   return hipSuccess;
 }

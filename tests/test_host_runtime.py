@@ -130,6 +130,13 @@ def scenario_device(lib):
         call()
         assert all(q["dev"] == 1 for q in lib.launches()), (name, lib.launches())
         assert lib.m.model_device() == 0, f"{name} left another device current"
+    # the default stream whose work ends before the memory is given back is device 1's
+    lib.ok(lib.advance(ctx, [g], [7]))
+    lib.m.hipSetDevice(0)
+    lib.m.model_clear()
+    ctx.close()
+    waits = [line.split()[-1] for line in lib.m.model_log().decode().splitlines() if line.startswith("wait stream=0 ")]
+    assert waits and set(waits) == {"dev=1"} and lib.m.model_device() == 0, waits
 
 
 def scenario_small_failure(lib):
@@ -329,7 +336,8 @@ if __name__ == "__main__":
 # ---------------------------------------------------------------------------
 def test_reads_and_transfers_launch_on_the_contexts_device(model):
     """Reads and state transfers launch on their context's device, whichever
-    is current in the calling thread, and leave that one current."""
+    is current in the calling thread, and leave that one current; closing the
+    context waits for its own device."""
     _scenario(model, "device")
 
 
